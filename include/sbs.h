@@ -272,8 +272,9 @@ size_t sbs_refined_static_scratch_bytes(void);
  * the scheme of both benchmark problems (the explicit half of diffusion,
  * s C_{i-1} + (1 - 2s) C_i + s C_{i+1}, and of hyperdiffusion, is 2I - A for
  * their matrices A), with the explicit half taken from the handle's own rows,
- * periodic rows wrapping round.  The explicit half is fused into the solve:
- * each step reads and writes every unknown as one solve does.
+ * periodic rows wrapping round.  The explicit half is fused into the solve.
+ * Where the matrix has a partition plan all steps of a call run on chip: every
+ * unknown is read and written once per call; otherwise once per step.
  *  c      device, interleaved (n, m), dtype SBS_F64 or SBS_F32; overwritten.
  *  steps  >= 0 (0 and m == 0 do nothing).
  * Any kind of handle.  Asynchronous on `stream`.

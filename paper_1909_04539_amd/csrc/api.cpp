@@ -478,18 +478,15 @@ sbs_status sbs_cn_step(sbs_handle h, void *c, int64_t m, int32_t dtype, int32_t 
     if (h->constant_bands && h->kind == SBS_PENTA) {
         SepChoice sc;
         if (choose_sep(h, t, m, c, &sc, true) && sep_fills(h, t, m, sc)) {
-            for (int k = 0; k < steps; ++k)
-                if (launch_sep(h, sc, t, c, m, s) != hipSuccess) return SBS_ERR_DEVICE;
-            return SBS_OK;
+            return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
         }
     }
     PartChoice pc;
     const int cn = h->constant_bands ? 2 : 1;  // constant bands: coefficients by value, no band rows in LDS
-    const bool part = choose_partition(h, t, m, &pc, cn);
-    for (int k = 0; k < steps; ++k) {
-        const hipError_t e = part ? launch_partition(h, pc, t, t, t, c, c, m, s, cn) : launch_cn(h, t, c, m, s);
-        if (e != hipSuccess) return SBS_ERR_DEVICE;
-    }
+    if (choose_partition(h, t, m, &pc, cn))
+        return launch_partition(h, pc, t, t, t, c, c, m, s, cn, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    for (int k = 0; k < steps; ++k)
+        if (launch_cn(h, t, c, m, s) != hipSuccess) return SBS_ERR_DEVICE;
     return SBS_OK;
 }
 

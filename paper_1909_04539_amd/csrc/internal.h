@@ -224,8 +224,9 @@ struct PartChoice {
 bool choose_partition(const sbs_lhs *h, int tc, int64_t m, PartChoice *out, int cn = 0, bool rows = false);
 // A given pair-partition shape for a plain solve (block length lb, S).
 bool part_shape(const sbs_lhs *h, int tc, int64_t m, int lb, int S, PartChoice *out);
+// steps: how many Crank-Nicolson steps one launch runs (cn != 0).
 hipError_t launch_partition(const sbs_lhs *h, const PartChoice &c, int tc, int tin, int tout, const void *in,
-                            void *out, int64_t m, hipStream_t stream, int cn = 0);
+                            void *out, int64_t m, hipStream_t stream, int cn = 0, int steps = 1);
 // FP64 solve of m systems stored one after another (system j at x + j*n),
 // in place, on the partition chosen for them.
 hipError_t launch_partition_rows(const sbs_lhs *h, const PartChoice &c, double *x, int64_t m, hipStream_t stream);
@@ -262,8 +263,10 @@ struct SepChoice {
 bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *out, bool cn = false);
 // A given shape (block length lb, VEC, S, flags); false if it cannot run.
 bool sep_shape(const sbs_lhs *h, int tc, int64_t m, const void *x, int lb, int vec, int S, int flags, SepChoice *out);
-// In place on the interleaved (n, m) array x (tc: 0 f64, 1 f32).
-hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t stream);
+// In place on the interleaved (n, m) array x (tc: 0 f64, 1 f32); `steps`
+// Crank-Nicolson steps for a shape chosen for them.
+hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t stream,
+                      int steps = 1);
 // Whether the separator shape fills the GPU with whole 256-byte row runs.
 bool sep_fills(const sbs_lhs *h, int tc, int64_t m, const SepChoice &c);
 

@@ -107,6 +107,7 @@ struct SepArgs {
     int fac_bytes, spk_bytes, scf_bytes, sinv_bytes, map_bytes;
     int n, P, Nr, S, ngroups, periodic, flags;
     int kofs, kw;  // window of the S^{-1} product (kw = 0: every column)
+    int steps;     // Crank-Nicolson steps to run (1 for a solve)
     int64_t m;
     BandCoef coef;  // Crank-Nicolson steps: the matrix's constant band values
 };
@@ -350,13 +351,19 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // are stored after all of them are computed (a spike load issued after a
 // store would wait for that store).
 //
-// CN: one Crank-Nicolson step c <- A^{-1} (2I - A) c (Sections 3.2, 4.2) of a
-// matrix whose bands are constant (the values in a.coef): with u = A^{-1} c in
-// registers, row t of the output is 2 u_t - sum_e coef_e u_{t-H+e}.  The rows
+// CN: a.steps Crank-Nicolson steps c <- A^{-1} (2I - A) c (Sections 3.2, 4.2)
+// of a matrix whose bands are constant (the values in a.coef): with
+// u = A^{-1} c in registers, row t of the output is
+// 2 u_t - sum_e coef_e u_{t-H+e}.  The rows
 // above the block are the previous block's separators (known to the lane);
 // the first H rows of the next block come through LDS, one more barrier.
 // Values outside the matrix are 0, so the constant coefficients also give
-// the truncated rows at its ends.
+// the truncated rows at its ends.  The group's systems are whole in the
+// workgroup, so every step but the last leaves its rows in the registers
+// for the next one: HBM is crossed once in and once out however many steps a
+// call asks for, and a step costs its arithmetic and barriers only.
+// (Hyperdiffusion n = 1024, m = 65536, 8 steps per call: 686 us, with one
+// launch and one pass over HBM per step 1827 us.)
 template <int KIND, typename T, int LB, int VEC, int MAXT, bool GF, bool CN = false>
 __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ blob, SepArgs a, const T *in,
                                               T *out) {
@@ -461,210 +468,225 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             cr[c][d] = (2 * H - c + d < NB) ? cfp[c * NB + 2 * H - c + d] : T(0);
         }
     for (; g < a.ngroups; g += grid) {
-        // the lane's offsets into the separator buffers, made opaque each
-        // group so that the addresses derived from them are formed where they
-        // are used instead of being kept live (and spilled) across the loop
-        int o_own = s0 * ldr + H * p, o_prev = s0 * ldr + H * pp, o_col = s0 * ldr;
-        asm volatile("" : "+v"(o_own), "+v"(o_prev), "+v"(o_col));
-        // GF: the plan is read-only global memory, and its loads would be
-        // hoisted out of the loop (every row's coefficients live at once)
-        // unless its addresses are opaque here too
-        const Row *fr = fr0;
-        const T *sp = sp0;
-        if constexpr (GF) asm volatile("" : "+v"(fr), "+v"(sp));
+        for (int step = CN ? a.steps : 1; step > 0; --step) {
+            // the lane's offsets into the separator buffers, made opaque each
+            // group so that the addresses derived from them are formed where they
+            // are used instead of being kept live (and spilled) across the loop
+            int o_own = s0 * ldr + H * p, o_prev = s0 * ldr + H * pp, o_col = s0 * ldr;
+            asm volatile("" : "+v"(o_own), "+v"(o_prev), "+v"(o_col));
+            // GF: the plan is read-only global memory, and its loads would be
+            // hoisted out of the loop (every row's coefficients live at once)
+            // unless its addresses are opaque here too
+            const Row *fr = fr0;
+            const T *sp = sp0;
+            if constexpr (GF) asm volatile("" : "+v"(fr), "+v"(sp));
 
-        // 1. block sweeps (Section 3.1 / 4.1 recurrences, block factor);
-        // each group of G rows reads its coefficients while the previous
-        // group computes
-        block_sweeps<KIND, T, LB, VEC, GF>(fr, x);
-        // 2. the separator right-hand sides in two parts: the previous
-        // separator takes minus its couplings to this block's first rows
-        // (redr), the block's own separator takes f_sep minus its couplings to
-        // this block's last interior rows (redl); one barrier.  (In this order
-        // the first rows' values are dropped before the last rows' are used,
-        // which keeps the FP64 pentadiagonal kernel within its registers.)
-        if (has_prev) {
+            // 1. block sweeps (Section 3.1 / 4.1 recurrences, block factor);
+            // each group of G rows reads its coefficients while the previous
+            // group computes
+            block_sweeps<KIND, T, LB, VEC, GF>(fr, x);
+            // 2. the separator right-hand sides in two parts: the previous
+            // separator takes minus its couplings to this block's first rows
+            // (redr), the block's own separator takes f_sep minus its couplings to
+            // this block's last interior rows (redl); one barrier.  (In this order
+            // the first rows' values are dropped before the last rows' are used,
+            // which keeps the FP64 pentadiagonal kernel within its registers.)
+            if (has_prev) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v)
-#pragma unroll
-                for (int c = 0; c < H; ++c) {
-                    // band d = 2H - c + e of separator row c meets this block's row e
-                    T yh = T(0);
-#pragma unroll
-                    for (int e = 0; e + 2 * H - c < NB; ++e) yh = fma(-cr[c][e], x[e][v], yh);
-                    lredr[o_prev + v * ldr + c] = yh;
-                }
-        }
-        if (has_sep) {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v)
-#pragma unroll
-                for (int c = 0; c < H; ++c) {
-                    // separator rows are identity rows of the block factor: the
-                    // sweeps leave their right-hand sides in place
-                    T yh = x[NI + c][v];
-                    // band d < H - c of separator row c meets row NI + c + d - H
-#pragma unroll
-                    for (int d = 0; d + c < H; ++d) yh = fma(-cl[c][d], x[NI + c + d - H][v], yh);
-                    lredl[o_own + v * ldr + c] = yh;
-                }
-        }
-        __syncthreads();
-        // 3. separators
-        T zr[H][VEC], zl[H][VEC];
-        if (Nr == 0) {
-#pragma unroll
-            for (int c = 0; c < H; ++c)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) zr[c][v] = zl[c][v] = T(0);
-        } else if (MMA && blockDim.x % kWave == 0 &&
-                   (!alias || ((Nr + 15) / 16) * ((S + 15) / 16) <= (int)(blockDim.x / kWave))) {
-            if constexpr (MMA) {
-                // flags bit 6: every column of S^{-1}
-                const int kw = (a.flags & 64) ? 0 : a.kw;
-                if (alias)
-                    sep_mma<true>(lsinv, lredl, lredr, lz, Nr, S, ldr, a.kofs, kw);
-                else
-                    sep_mma<false>(lsinv, lredl, lredr, lz, Nr, S, ldr, a.kofs, kw);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int c = 0; c < H; ++c)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    // indices stay inside the separators even where unused
-                    const T zo = lz[(has_sep ? o_own : o_col) + v * ldr + c];
-                    const T zp = lz[(has_prev ? o_prev : o_col) + v * ldr + c];
-                    zr[c][v] = has_sep ? zo : T(0);
-                    zl[c][v] = has_prev ? zp : T(0);
-                }
-            // the separators are redL's storage: the next group writes redL
-            // only after every lane has read them
-            if (alias) __syncthreads();
-        } else {
-            // rows of S^{-1} for the own and the previous separator (a block
-            // without one reads the other's rows and discards the result)
-            const T *rr = lsinv + (size_t)H * (has_sep ? p : pp) * Nr;
-            const T *rl = lsinv + (size_t)H * (has_prev ? pp : p) * Nr;
-            T ar[H][VEC], al[H][VEC];
-#pragma unroll
-            for (int c = 0; c < H; ++c)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) ar[c][v] = al[c][v] = T(0);
-            for (int k = 0; k < Nr; ++k) {
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const T y = lredl[o_col + v * ldr + k] + lredr[o_col + v * ldr + k];
+                for (int v = 0; v < VEC; ++v)
 #pragma unroll
                     for (int c = 0; c < H; ++c) {
-                        ar[c][v] = fma(rr[c * Nr + k], y, ar[c][v]);
-                        al[c][v] = fma(rl[c * Nr + k], y, al[c][v]);
+                        // band d = 2H - c + e of separator row c meets this block's row e
+                        T yh = T(0);
+#pragma unroll
+                        for (int e = 0; e + 2 * H - c < NB; ++e) yh = fma(-cr[c][e], x[e][v], yh);
+                        lredr[o_prev + v * ldr + c] = yh;
                     }
-                }
             }
+            if (has_sep) {
 #pragma unroll
-            for (int c = 0; c < H; ++c)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    zr[c][v] = has_sep ? ar[c][v] : T(0);
-                    zl[c][v] = has_prev ? al[c][v] : T(0);
-                }
-            // every lane has read redL / redR before the next group writes them
-            __syncthreads();
-        }
-        // 4. correction and stores
-        T *dst = out + (int64_t)r0 * m + col(g);
-        // the spikes of GC rows per round trip; from global memory (GF) the
-        // next rows' spikes are loaded before the current rows are stored,
-        // since a load issued after a store waits for that store
-        constexpr int GC = GF ? 2 : G, NS = GF ? 2 : 1;
-        T spt[NS][GC][2 * H];
-        auto spikes = [&](int gr, T(&dstk)[GC][2 * H]) {
-            if constexpr (GF) asm volatile("" : "+v"(sp));
-#pragma unroll
-            for (int u = 0; u < GC; ++u)
-#pragma unroll
-                for (int k = 0; k < 2 * H; ++k) dstk[u][k] = sp[(gr * GC + u) * 2 * H + k];
-        };
-        if constexpr (GF) spikes(0, spt[0]);
-#pragma unroll
-        for (int gr = 0; gr < LB / GC; ++gr) {
-            T(&cur)[GC][2 * H] = spt[GF ? gr & 1 : 0];
-            if constexpr (GF) {
-                if (gr + 1 < LB / GC) spikes(gr + 1, spt[(gr + 1) & 1]);
-            } else {
-                spikes(gr, cur);
-            }
-#pragma unroll
-            for (int u = 0; u < GC; ++u) {
-                const int t = gr * GC + u;
-                T v2[VEC];
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    T val = x[t][v];
+                for (int v = 0; v < VEC; ++v)
 #pragma unroll
                     for (int c = 0; c < H; ++c) {
-                        val = fma(-cur[u][c], zr[c][v], val);
-                        val = fma(-cur[u][H + c], zl[c][v], val);
+                        // separator rows are identity rows of the block factor: the
+                        // sweeps leave their right-hand sides in place
+                        T yh = x[NI + c][v];
+                        // band d < H - c of separator row c meets row NI + c + d - H
+#pragma unroll
+                        for (int d = 0; d + c < H; ++d) yh = fma(-cl[c][d], x[NI + c + d - H][v], yh);
+                        lredl[o_own + v * ldr + c] = yh;
                     }
-                    if (t >= NI) val = has_sep ? zr[t >= NI ? t - NI : 0][v] : val;
-                    v2[v] = val;
+            }
+            __syncthreads();
+            // 3. separators
+            T zr[H][VEC], zl[H][VEC];
+            if (Nr == 0) {
+#pragma unroll
+                for (int c = 0; c < H; ++c)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) zr[c][v] = zl[c][v] = T(0);
+            } else if (MMA && blockDim.x % kWave == 0 &&
+                       (!alias || ((Nr + 15) / 16) * ((S + 15) / 16) <= (int)(blockDim.x / kWave))) {
+                if constexpr (MMA) {
+                    // flags bit 6: every column of S^{-1}
+                    const int kw = (a.flags & 64) ? 0 : a.kw;
+                    if (alias)
+                        sep_mma<true>(lsinv, lredl, lredr, lz, Nr, S, ldr, a.kofs, kw);
+                    else
+                        sep_mma<false>(lsinv, lredl, lredr, lz, Nr, S, ldr, a.kofs, kw);
                 }
-                if constexpr (CN) {
-                    // computed here, not sunk past the barrier below (which
-                    // would keep every row's spikes live until then)
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < H; ++c)
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) {
-                        x[t][v] = v2[v];
-                        asm volatile("" : "+v"(x[t][v]));
+                        // indices stay inside the separators even where unused
+                        const T zo = lz[(has_sep ? o_own : o_col) + v * ldr + c];
+                        const T zp = lz[(has_prev ? o_prev : o_col) + v * ldr + c];
+                        zr[c][v] = has_sep ? zo : T(0);
+                        zl[c][v] = has_prev ? zp : T(0);
                     }
-                } else if (full || r0 + t < n) {
-                    store_vec_nt<T, VEC>(dst + (int64_t)t * m, v2);
+                // the separators are redL's storage: the next group writes redL
+                // only after every lane has read them
+                if (alias) __syncthreads();
+            } else {
+                // rows of S^{-1} for the own and the previous separator (a block
+                // without one reads the other's rows and discards the result)
+                const T *rr = lsinv + (size_t)H * (has_sep ? p : pp) * Nr;
+                const T *rl = lsinv + (size_t)H * (has_prev ? pp : p) * Nr;
+                T ar[H][VEC], al[H][VEC];
+#pragma unroll
+                for (int c = 0; c < H; ++c)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) ar[c][v] = al[c][v] = T(0);
+                for (int k = 0; k < Nr; ++k) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) {
+                        const T y = lredl[o_col + v * ldr + k] + lredr[o_col + v * ldr + k];
+#pragma unroll
+                        for (int c = 0; c < H; ++c) {
+                            ar[c][v] = fma(rr[c * Nr + k], y, ar[c][v]);
+                            al[c][v] = fma(rl[c * Nr + k], y, al[c][v]);
+                        }
+                    }
                 }
+#pragma unroll
+                for (int c = 0; c < H; ++c)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) {
+                        zr[c][v] = has_sep ? ar[c][v] : T(0);
+                        zl[c][v] = has_prev ? al[c][v] : T(0);
+                    }
+                // every lane has read redL / redR before the next group writes them
+                __syncthreads();
             }
-            pin(zr[0][0]);
-        }
-        if constexpr (CN) {
-            // 5. Crank-Nicolson output rows from the block's solution
+            // 4. correction and stores
+            T *dst = out + (int64_t)r0 * m + col(g);
+            // the spikes of GC rows per round trip; from global memory (GF) the
+            // next rows' spikes are loaded before the current rows are stored,
+            // since a load issued after a store waits for that store
+            constexpr int GC = GF ? 2 : G, NS = GF ? 2 : 1;
+            T spt[NS][GC][2 * H];
+            auto spikes = [&](int gr, T(&dstk)[GC][2 * H]) {
+                if constexpr (GF) asm volatile("" : "+v"(sp));
 #pragma unroll
-            for (int v = 0; v < VEC; ++v)
+                for (int u = 0; u < GC; ++u)
 #pragma unroll
-                for (int c = 0; c < H; ++c) ltop[((s0 + v) * P + p) * H + c] = x[c][v];
-            __syncthreads();
-            const bool has_next = a.periodic || p < P - 1;
-            const int pn = p == P - 1 ? 0 : p + 1;
-            T dn[H][VEC];
+                    for (int k = 0; k < 2 * H; ++k) dstk[u][k] = sp[(gr * GC + u) * 2 * H + k];
+            };
+            if constexpr (GF) spikes(0, spt[0]);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v)
-#pragma unroll
-                for (int c = 0; c < H; ++c) {
-                    const T t0 = ltop[((s0 + v) * P + pn) * H + c];
-                    dn[c][v] = has_next ? t0 : T(0);
+            for (int gr = 0; gr < LB / GC; ++gr) {
+                T(&cur)[GC][2 * H] = spt[GF ? gr & 1 : 0];
+                if constexpr (GF) {
+                    if (gr + 1 < LB / GC) spikes(gr + 1, spt[(gr + 1) & 1]);
+                } else {
+                    spikes(gr, cur);
                 }
-            // rows above the block: the previous block's separators (0 above
-            // the first block of a matrix that does not wrap round)
-            const T c0 = (T)a.coef.c[0];
-            // one store pointer stepped row by row (opaque, so that the
-            // rows' addresses are not all formed up front and kept live)
-            T *q = dst;
 #pragma unroll
-            for (int t = 0; t < LB; ++t) {
-                T v2[VEC];
+                for (int u = 0; u < GC; ++u) {
+                    const int t = gr * GC + u;
+                    T v2[VEC];
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    T ax = T(0);
+                    for (int v = 0; v < VEC; ++v) {
+                        T val = x[t][v];
 #pragma unroll
-                    for (int e = 0; e < NB; ++e) {
-                        const int i = t - H + e;
-                        const T u = i < 0 ? zl[i + H][v] : (i >= LB ? dn[i - LB][v] : x[i][v]);
-                        ax = e == 0 ? c0 * u : fma((T)a.coef.c[e], u, ax);
+                        for (int c = 0; c < H; ++c) {
+                            val = fma(-cur[u][c], zr[c][v], val);
+                            val = fma(-cur[u][H + c], zl[c][v], val);
+                        }
+                        if (t >= NI) val = has_sep ? zr[t >= NI ? t - NI : 0][v] : val;
+                        v2[v] = val;
                     }
-                    v2[v] = T(2) * x[t][v] - ax;
+                    if constexpr (CN) {
+                        // computed here, not sunk past the barrier below (which
+                        // would keep every row's spikes live until then)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) {
+                            x[t][v] = v2[v];
+                            asm volatile("" : "+v"(x[t][v]));
+                        }
+                    } else if (full || r0 + t < n) {
+                        store_vec_nt<T, VEC>(dst + (int64_t)t * m, v2);
+                    }
                 }
-                if (full || r0 + t < n) store_vec_nt<T, VEC>(q, v2);
-                q += m;
-                asm volatile("" : "+v"(q));
-                if (t % G == G - 1) pin(v2[0]);
+                pin(zr[0][0]);
+            }
+            if constexpr (CN) {
+                // 5. Crank-Nicolson output rows from the block's solution
+#pragma unroll
+                for (int v = 0; v < VEC; ++v)
+#pragma unroll
+                    for (int c = 0; c < H; ++c) ltop[((s0 + v) * P + p) * H + c] = x[c][v];
+                __syncthreads();
+                const bool has_next = a.periodic || p < P - 1;
+                const int pn = p == P - 1 ? 0 : p + 1;
+                T dn[H][VEC];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v)
+#pragma unroll
+                    for (int c = 0; c < H; ++c) {
+                        const T t0 = ltop[((s0 + v) * P + pn) * H + c];
+                        dn[c][v] = has_next ? t0 : T(0);
+                    }
+                // rows above the block: the previous block's separators (0 above
+                // the first block of a matrix that does not wrap round)
+                const T c0 = (T)a.coef.c[0];
+                // one store pointer stepped row by row (opaque, so that the
+                // rows' addresses are not all formed up front and kept live)
+                T *q = dst;
+                T up[H][VEC];  // the H rows above row t, before their own update
+#pragma unroll
+                for (int c = 0; c < H; ++c)
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) up[c][v] = zl[c][v];
+#pragma unroll
+                for (int t = 0; t < LB; ++t) {
+                    T v2[VEC];
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) {
+                        T ax = T(0);
+#pragma unroll
+                        for (int e = 0; e < NB; ++e) {
+                            const int i = t - H + e;
+                            const T u = e < H ? up[e][v] : (i >= LB ? dn[i - LB][v] : x[i][v]);
+                            ax = e == 0 ? c0 * u : fma((T)a.coef.c[e], u, ax);
+                        }
+                        v2[v] = T(2) * x[t][v] - ax;
+#pragma unroll
+                        for (int c = 0; c < H; ++c) up[c][v] = c + 1 < H ? up[c + 1][v] : x[t][v];
+                    }
+                    if (step > 1) {
+                        // rows past the matrix stay 0
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < n ? v2[v] : T(0);
+                    } else {
+                        if (full || r0 + t < n) store_vec_nt<T, VEC>(q, v2);
+                        q += m;
+                        asm volatile("" : "+v"(q));
+                    }
+                    if (t % G == G - 1) pin(v2[0]);
+                }
             }
         }
         if (g + grid < a.ngroups) load_group(g + grid);
@@ -836,7 +858,7 @@ bool sep_shape(const sbs_lhs *h, int tc, int64_t m, const void *x, int lb, int v
     return false;
 }
 
-hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t s) {
+hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t s, int steps) {
     if (m <= 0) return hipSuccess;
     const SepPlan &sp = h->sep[c.plan];
     const void *fn = nullptr;
@@ -861,6 +883,7 @@ hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int
     a.flags = c.flags;
     a.kofs = sp.kofs;
     a.kw = sp.kw;
+    a.steps = steps;
     a.m = m;
     a.coef = h->coef;
     const int grid = (int)std::min<int64_t>(ngroups, (int64_t)cu_count(h->device) * std::max(1, c.wgs));
