@@ -219,7 +219,11 @@ sbs_status sbs_auto_variant(sbs_handle h, int64_t m, int32_t dtype,
  * x written once; `work` is then not touched.  That kernel holds 64 systems
  * per workgroup with one wave per block of rows where the separator plan
  * allows (at most 16 blocks of 32 rows or 8 of 64, and b of the 64 systems
- * within the LDS: n up to about 560), else the pair-form plan's kernel.
+ * within the LDS: n up to about 560); longer matrices whose inverse decays
+ * within 64 rows (diagonally dominant and positive definite ones; what is
+ * dropped is below 2^-58 of a system's largest value) are cut into overlapping
+ * runs of rows solved that way independently (n up to about 20000; `work` is
+ * not touched); else the pair-form plan's kernel.
  *
  *  b          device, n*m floats, interleaved, read only.
  *  x          device, n*m doubles, interleaved, written (may not alias b).
@@ -360,12 +364,15 @@ sbs_status sbs_server_register(sbs_server *srv, sbs_handle h, int32_t *lhs_id);
  * submitted keep theirs):
  *  SBS_SERVE_F32_REFINED     (default) the mixed-precision form of
  *                            sbs_solve_batch_refined with 2 corrections:
- *                            FP32 sweeps, FP64 residuals and accumulation;
- *                            each tile's passes go through HBM (about 84
- *                            bytes per unknown, more for systems too long
- *                            for checkpoints) and the arena holds three
- *                            FP32 scratch arrays (12 bytes per unknown)
- *                            besides x.
+ *                            FP32 sweeps, FP64 residuals and accumulation.
+ *                            Requests of fewer than 4096 systems whose
+ *                            matrix can be cut into runs of rows (see
+ *                            sbs_solve_batch_refined) keep b and x on chip;
+ *                            for others each tile's passes go through HBM
+ *                            (about 84 bytes per unknown, more for systems
+ *                            too long for checkpoints).  The arena holds
+ *                            three FP32 scratch arrays (12 bytes per
+ *                            unknown) besides x.
  *  SBS_SERVE_F32_FP64_SWEEP  one FP64 sweep of the FP32 values (read and
  *                            promoted as they are loaded): the FP64 solve of
  *                            the stored right-hand sides, which is what the

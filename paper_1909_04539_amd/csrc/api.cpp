@@ -232,10 +232,12 @@ sbs_status refined_run(const sbs_lhs *h, const float *b, double *x, int64_t m, i
                        hipStream_t s) {
     // Fused paths: one kernel keeps each block of b and x on chip through all
     // passes (needs a partition plan); r is not touched.  First the
-    // one-wave-per-block kernel on the separator plan, then the pair form.
+    // one-wave-per-block kernel on the separator plan, then the same on
+    // overlapping segments of the matrix, then the pair form.
     RefwChoice rc;
     if (choose_refine_wave(h, m, &rc))
         return launch_refine_wave(h, rc, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    if (h->nseg > 0) return launch_refine_segs(h, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     PartChoice pc;
     if (choose_partition_refine(h, m, &pc))
         return launch_partition_refine(h, pc, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;

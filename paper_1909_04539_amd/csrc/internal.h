@@ -117,6 +117,27 @@ struct RefinePlan {
     int ldsinv = 0;
 };
 
+// A run of rows solved on its own by the one-wave-per-block mixed-precision
+// kernels, as the device reads it: rows lo .. lo + rows - 1 of the matrix as a
+// truncated matrix of their own (32-row separator blocks), of which rows
+// a .. b - 1 are the result.  A matrix of at most seg_max_blocks blocks is one
+// segment.  A longer one is cut into segments that overlap: the rows between
+// a segment's cut and its result are its halo, long enough that what lies
+// beyond the cut cannot matter (kSegDrop), so the segments are independent.
+struct alignas(16) RefSeg {
+    const float *fwd, *bwd, *spk, *sinv, *scf;  // see RefinePlan; scf: FP32 separator rows
+    const double *band;
+    const int *map;
+    int32_t lo, rows, a, b, P, Nr, ldsinv, pad;
+};
+constexpr int kSegLb = 32;       // rows per block of a segment's plan
+constexpr int kMaxSegs = 64;     // segments of one matrix (n up to about 20 000)
+constexpr int kMaxHalo = 64;     // rows of a halo
+constexpr double kSegDrop = 0x1p-60;
+// Blocks of a segment: one wave each (1024 threads), and the workgroup's
+// right-hand sides and exchange buffers within the LDS.
+constexpr int seg_max_blocks(int kind) { return kind == SBS_PENTA ? 14 : 16; }
+
 struct SepPlan {
     int lb = 0, P = 0, Nr = 0;
     int D = 0;  // distinct blocks stored
@@ -157,6 +178,8 @@ struct sbs_lhs {
     void *fac32 = nullptr;      // TriRow<float>[rows]  or PentaRow<float>[rows]
     sbs::BandRow *bands = nullptr;  // BandRow[rows]
     void *pdev = nullptr;       // partition data (one allocation for all plans)
+    const sbs::RefSeg *segs = nullptr;  // device array, nseg segments (0: the matrix has none)
+    int nseg = 0, segP = 0, segNr = 0;  // segP, segNr: the largest P and Nr among them
     sbs::PartPlan part[3];      // block lengths 16, 32, 64
     sbs::SepPlan sep[3];        // block lengths 16, 32, 64
     // every band constant over the rows where it lies inside the matrix
@@ -245,6 +268,9 @@ bool choose_refine_wave(const sbs_lhs *h, int64_t m, RefwChoice *out);
 hipError_t launch_refine_wave(const sbs_lhs *h, const RefwChoice &c, const float *b, double *x, int64_t m,
                               int sweeps, hipStream_t stream);
 
+// The same solve segment by segment (RefSeg); only for handles with segments.
+hipError_t launch_refine_segs(const sbs_lhs *h, const float *b, double *x, int64_t m, int sweeps, hipStream_t stream);
+
 // Separator-partitioned solve (plain solves of interleaved right-hand sides):
 // plan, values per lane (VEC adjacent systems, one access per row), systems
 // per workgroup, launch options (bit 0: XCD-grouped group order, bit 2:
@@ -280,26 +306,34 @@ sbs_status refined_run(const sbs_lhs *h, const float *b, double *x, int64_t m, i
 
 // Serving: heterogeneous tile launches (see server.cpp).
 struct Tile {
-    const void *fac;            // factor rows of this tile's matrix (FP32 for prec 1, else FP64)
+    const void *fac;            // factor rows of this tile's matrix (FP32 for prec 1, FP64 for 0 and 2;
+                                // prec 3 and 4: the tile's RefSeg)
     const BandRow *bands;       // original bands (mixed precision only)
     const void *in;             // rhs of the request
     double *x;                  // FP64 result of the request
     float *scratch;             // FP32 residual scratch (mixed precision only)
     int64_t n, m, col0;         // system range [col0, col0 + 64) of the request
     // prec 0: FP64 request; 1: FP32 request, mixed precision with two
-    // corrections; 2: FP32 request, one FP64 sweep of its stored values
+    // corrections, one wave per tile; 2: FP32 request, one FP64 sweep of its
+    // stored values; 3, 4: FP32 request, mixed precision with two corrections
+    // on one segment of the matrix, a workgroup with one wave per block (3: at
+    // most kSegHalf blocks in every segment, 4: more)
     int32_t kind, prec;
     int32_t req;                // the request's slot in the launch's completion arrays
     int32_t pad;
 };
 
+constexpr int kSegHalf = 8;  // blocks of the segments that run two workgroups per CU
 // Runs tiles [0, ntiles), all of one kind and prec, with `grid`
-// persistent waves; *dev_counter must be 0 when the kernel starts.
+// persistent waves (prec 3 and 4: workgroups that fill the GPU instead);
+// *dev_counter must be 0 when the kernel starts.
 // Per-request completion: left[r] holds the number of tiles of request r
 // (device memory); the wave that finishes the last of them sets done[r] = 1
 // (host-visible memory), after every result of the request is visible to the
 // host and to other work on the device.
 hipError_t launch_tiles(int kind, int prec, const Tile *dev_tiles, int ntiles, int *dev_counter, int *left,
                         int *done, int grid, hipStream_t stream);
+hipError_t launch_refine_tiles(int kind, bool half, const Tile *dev_tiles, int ntiles, int *dev_counter, int *left,
+                               int *done, hipStream_t stream);
 
 }  // namespace sbs

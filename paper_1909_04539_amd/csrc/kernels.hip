@@ -1938,7 +1938,8 @@ hipError_t launch_refine_step(const sbs_lhs *h, int mode, const float *b, double
 hipError_t launch_tiles(int kind, int prec, const Tile *dev_tiles, int ntiles, int *dev_counter, int *left,
                         int *done, int grid, hipStream_t stream) {
     if (ntiles <= 0) return hipSuccess;
-    if (prec < 0 || prec > 2) return hipErrorInvalidValue;
+    if (prec < 0 || prec > 4) return hipErrorInvalidValue;
+    if (prec >= 3) return launch_refine_tiles(kind, prec == 3, dev_tiles, ntiles, dev_counter, left, done, stream);
     if (grid > ntiles) grid = ntiles;
     const dim3 g((unsigned)grid), b(kWave);
     const bool tri = kind == SBS_TRI;

@@ -3,7 +3,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <functional>
 #include <vector>
 
 #include "factor_rows.h"
@@ -53,6 +52,21 @@ bool invert(std::vector<double> &a, int n) {
     a.swap(inv);
     return true;
 }
+
+// The factorisations as values, whatever their coefficients come from (their
+// coefficient reads are inlined).
+struct FactorTri {
+    template <class Coef>
+    bool operator()(int64_t n, Coef coef, TriRow<double> *rows, int64_t *bad) const {
+        return factor_tri_rows(n, coef, rows, bad);
+    }
+};
+struct FactorPenta {
+    template <class Coef>
+    bool operator()(int64_t n, Coef coef, PentaRow<double> *rows, int64_t *bad) const {
+        return factor_penta_rows(n, coef, rows, bad);
+    }
+};
 
 struct HostPlan {
     int lb = 0, P = 0, Nr = 0, D = 0;
@@ -695,6 +709,138 @@ void serialise_refine(const SepHostPlan &hp, const std::vector<unsigned char> &b
         for (int k = 0; k < hp.Nr; ++k) sinv[(size_t)r * rp.ldsinv + k] = (float)hp.sinv[(size_t)r * hp.Nr + k];
 }
 
+// ---------------------------------------------------------------------------
+// Segments (RefSeg) of a matrix that the one-wave-per-block mixed-precision
+// kernels solve run of rows by run of rows.
+
+struct HostSeg {
+    int64_t lo = 0, hi = 0, a = 0, b = 0;  // rows solved, rows of the result
+    int same = -1;                         // an earlier segment with the same rows (constant bands), or -1
+    SepHostPlan hp;
+    SepPlan sp;                            // blob sizes and RefinePlan offsets
+    std::vector<unsigned char> b32, rec;   // serialised plan, the kernel's copy
+};
+
+// The bands of rows lo .. hi - 1 as a matrix of their own (couplings to rows
+// outside dropped).
+std::vector<double> sub_bands(int kind, int64_t n, const double *bands, int64_t lo, int64_t hi) {
+    const int h = kind / 2;
+    const int64_t ns = hi - lo;
+    std::vector<double> out((size_t)kind * ns, 0.0);
+    for (int k = 0; k < kind; ++k)
+        for (int64_t i = 0; i < ns; ++i) {
+            const int64_t col = i + k - h;
+            if (col >= 0 && col < ns) out[(size_t)k * ns + i] = bands[(int64_t)k * n + lo + i];
+        }
+    return out;
+}
+
+// Whether what lies beyond the segment's cuts cannot matter for its result:
+// with x_out the exact values just outside a cut, the truncated solution is
+// off by A_seg^{-1} (coupling) x_out; every entry of A_seg^{-1} (coupling) on
+// the result's rows has to be at most kSegDrop (2^-60: at most 2 h 2^-60 of
+// the system's largest value in all, 1/32 of an FP64 rounding).
+template <typename Row, typename FactorFn, typename SolveFn>
+bool seg_independent(int kind, int64_t n, const double *bands, const HostSeg &s, const std::vector<double> &sub,
+                     FactorFn factor, SolveFn solve) {
+    const int h = kind / 2;
+    const int64_t ns = s.hi - s.lo;
+    std::vector<Row> rows(ns);
+    int64_t bad = -1;
+    if (!factor(ns, [&](int k, int64_t i) { return sub[(size_t)k * ns + i]; }, rows.data(), &bad)) return false;
+    std::vector<double> v(ns);
+    auto decays = [&] {
+        solve(ns, rows.data(), v.data());
+        for (int64_t i = s.a; i < s.b; ++i)
+            if (!(std::fabs(v[i - s.lo]) <= kSegDrop)) return false;
+        return true;
+    };
+    for (int c = 0; c < h; ++c) {
+        if (s.lo > 0) {  // column lo - h + c meets rows lo .. lo + c
+            std::fill(v.begin(), v.end(), 0.0);
+            for (int t = 0; t <= c; ++t) v[t] = bands[(int64_t)(c - t) * n + s.lo + t];
+            if (!decays()) return false;
+        }
+        if (s.hi < n) {  // column hi + c meets rows hi - h + c .. hi - 1
+            std::fill(v.begin(), v.end(), 0.0);
+            for (int t = c; t < h; ++t) v[ns - h + t] = bands[(int64_t)(2 * h + c - t) * n + s.hi - h + t];
+            if (!decays()) return false;
+        }
+    }
+    return true;
+}
+
+// Cuts the matrix into the fewest equal segments that fit with the shortest
+// halo whose segments are independent; empty if there is none.
+template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
+std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, FactorFn factor, SolveFn solve) {
+    const int64_t cap = (int64_t)seg_max_blocks(kind) * kSegLb;
+    for (int halo = 16; halo <= kMaxHalo; halo += 16) {
+        const int64_t core = cap - 2 * halo;
+        const int64_t ns = n <= 2 * (cap - halo) ? 2 : (n + core - 1) / core;
+        if (ns > kMaxSegs) return {};
+        std::vector<HostSeg> segs((size_t)ns);
+        std::vector<std::vector<double>> sub((size_t)ns);
+        bool ok = true;
+        for (int64_t k = 0; k < ns && ok; ++k) {
+            HostSeg &s = segs[k];
+            // equal result runs (the last one shorter): with constant bands
+            // every interior segment is the same matrix
+            const int64_t run = (n + ns - 1) / ns;
+            s.a = run * k;
+            s.b = std::min<int64_t>(n, s.a + run);
+            s.lo = std::max<int64_t>(0, s.a - halo);
+            s.hi = std::min<int64_t>(n, s.b + halo);
+            sub[k] = sub_bands(kind, n, bands, s.lo, s.hi);
+            // an earlier segment with the same rows, couplings and place of
+            // its result has answered already
+            for (int64_t q = 0; q < k && s.same < 0; ++q) {
+                const HostSeg &o = segs[q];
+                if (o.same >= 0 || o.a - o.lo != s.a - s.lo || o.b - o.lo != s.b - s.lo || sub[q] != sub[k]) continue;
+                bool alike = true;
+                for (int64_t t = 0; t < kind / 2 && alike; ++t)
+                    for (int b = 0; b < kind && alike; ++b)
+                        alike = bands[b * n + s.lo + t] == bands[b * n + o.lo + t] &&
+                                bands[b * n + s.hi - 1 - t] == bands[b * n + o.hi - 1 - t];
+                if (alike && (o.lo > 0) == (s.lo > 0) && (o.hi < n) == (s.hi < n)) s.same = (int)q;
+            }
+            if (s.same < 0) ok = seg_independent<Row>(kind, n, bands, s, sub[k], factor, solve);
+        }
+        if (!ok) continue;
+        for (int64_t k = 0; k < ns; ++k) {
+            HostSeg &s = segs[k];
+            if (s.same >= 0) continue;
+            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, s.hp)) return {};
+            std::vector<unsigned char> b64;
+            serialise_sep<Row, Row32>(s.hp, b64, s.b32, s.sp);
+            serialise_refine<Row32>(s.hp, s.b32, s.sp, kind, s.hi - s.lo, sub[k].data(), s.rec, s.sp.refine);
+        }
+        return segs;
+    }
+    return {};
+}
+
+// The device's view of a segment: plan blob (FP32) and the kernel's copy.
+RefSeg make_seg(const SepPlan &sp, const unsigned char *b32, const unsigned char *rec, int64_t lo, int64_t rows,
+                int64_t a, int64_t b) {
+    RefSeg s{};
+    s.fwd = reinterpret_cast<const float *>(rec + sp.refine.fwd);
+    s.bwd = reinterpret_cast<const float *>(rec + sp.refine.bwd);
+    s.spk = reinterpret_cast<const float *>(rec + sp.refine.spk);
+    s.sinv = reinterpret_cast<const float *>(rec + sp.refine.sinv);
+    s.scf = reinterpret_cast<const float *>(b32 + sp.fac_bytes32 + sp.spk_bytes32);
+    s.band = reinterpret_cast<const double *>(rec + sp.refine.band);
+    s.map = reinterpret_cast<const int *>(b32 + sp.fac_bytes32 + sp.spk_bytes32 + sp.scf_bytes32 + sp.sinv_bytes32);
+    s.lo = (int32_t)lo;
+    s.rows = (int32_t)rows;
+    s.a = (int32_t)a;
+    s.b = (int32_t)b;
+    s.P = sp.P;
+    s.Nr = sp.Nr;
+    s.ldsinv = sp.refine.ldsinv;
+    return s;
+}
+
 }  // namespace
 
 // Builds every plan that exists for this matrix.  A plan that does not exist
@@ -712,11 +858,9 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
         const int lb = kPartLbs[q];
         bool ok;
         if (tri)
-            ok = build_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb,
-                                            factor_tri_rows<std::function<double(int, int64_t)>>, solve_tri_rows, hp);
+            ok = build_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, hp);
         else
-            ok = build_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb,
-                                              factor_penta_rows<std::function<double(int, int64_t)>>, solve_penta_rows, hp);
+            ok = build_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows, hp);
         if (!ok) continue;
         PartPlan &pp = h->part[q];
         pp.periodic = periodic;
@@ -735,13 +879,10 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
         const int lb = kPartLbs[q];
         bool ok;
         if (tri)
-            ok = build_sep_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb,
-                                                factor_tri_rows<std::function<double(int, int64_t)>>, solve_tri_rows,
-                                                hp);
+            ok = build_sep_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, hp);
         else
-            ok = build_sep_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb,
-                                                  factor_penta_rows<std::function<double(int, int64_t)>>,
-                                                  solve_penta_rows, hp);
+            ok = build_sep_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows,
+                                                  hp);
         if (!ok) continue;
         SepPlan &sp = h->sep[q];
         sp.periodic = periodic;
@@ -759,43 +900,77 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
             total += r32[q].size();
         }
     }
+    // Segments for the mixed-precision kernels: the 32-row separator plan
+    // itself where the whole matrix is one, else overlapping runs of rows.
+    std::vector<HostSeg> segs;
+    const bool whole = !periodic && h->sep[1].ok && h->sep[1].P <= seg_max_blocks(h->kind);
+    if (!periodic && h->n > (int64_t)seg_max_blocks(h->kind) * kSegLb) {
+        if (tri)
+            segs = build_segments<TriRow<double>, TriRow<float>>(SBS_TRI, h->n, bands, FactorTri{}, solve_tri_rows);
+        else
+            segs = build_segments<PentaRow<double>, PentaRow<float>>(SBS_PENTA, h->n, bands, FactorPenta{},
+                                                                     solve_penta_rows);
+    }
+    for (const HostSeg &s : segs)
+        if (s.same < 0) total += align256(s.b32.size()) + align256(s.rec.size());
+    const size_t nseg = whole ? 1 : segs.size();
+    total += align256(nseg * sizeof(RefSeg));
     if (total == 0) return SBS_OK;
     void *dev = nullptr;
     if (hipMalloc(&dev, total) != hipSuccess) return SBS_ERR_NO_MEMORY;
     h->pdev = dev;
+    // everything is laid out in host memory and goes over in one copy (each
+    // copy of its own costs about 10 us, as much as a small plan)
+    std::vector<unsigned char> host(total, 0);
+    unsigned char *base = static_cast<unsigned char *>(dev);
     size_t at = 0;
+    auto put = [&](const void *src, size_t bytes) {
+        unsigned char *d = base + at;
+        copy_bytes(host.data() + at, src, bytes);
+        at += align256(bytes);
+        return d;
+    };
     for (int q = 0; q < 3; ++q) {
         PartPlan &pp = h->part[q];
         if (!pp.ok) continue;
-        unsigned char *base = static_cast<unsigned char *>(dev);
-        if (hipMemcpy(base + at, b64[q].data(), b64[q].size(), hipMemcpyHostToDevice) != hipSuccess)
-            return SBS_ERR_DEVICE;
-        pp.blob64 = base + at;
-        at += align256(b64[q].size());
-        if (hipMemcpy(base + at, b32[q].data(), b32[q].size(), hipMemcpyHostToDevice) != hipSuccess)
-            return SBS_ERR_DEVICE;
-        pp.blob32 = base + at;
-        at += align256(b32[q].size());
+        pp.blob64 = put(b64[q].data(), b64[q].size());
+        pp.blob32 = put(b32[q].data(), b32[q].size());
     }
     for (int q = 0; q < 3; ++q) {
         SepPlan &sp = h->sep[q];
         if (!sp.ok) continue;
-        unsigned char *base = static_cast<unsigned char *>(dev);
-        if (hipMemcpy(base + at, s64[q].data(), s64[q].size(), hipMemcpyHostToDevice) != hipSuccess)
-            return SBS_ERR_DEVICE;
-        sp.blob64 = base + at;
-        at += align256(s64[q].size());
-        if (hipMemcpy(base + at, s32[q].data(), s32[q].size(), hipMemcpyHostToDevice) != hipSuccess)
-            return SBS_ERR_DEVICE;
-        sp.blob32 = base + at;
-        at += align256(s32[q].size());
-        if (!r32[q].empty()) {
-            if (hipMemcpy(base + at, r32[q].data(), r32[q].size(), hipMemcpyHostToDevice) != hipSuccess)
-                return SBS_ERR_DEVICE;
-            sp.refine.base = base + at;
-            at += r32[q].size();
+        sp.blob64 = put(s64[q].data(), s64[q].size());
+        sp.blob32 = put(s32[q].data(), s32[q].size());
+        if (!r32[q].empty()) sp.refine.base = put(r32[q].data(), r32[q].size());
+    }
+    std::vector<RefSeg> table;
+    if (whole) {
+        const SepPlan &sp = h->sep[1];
+        table.push_back(make_seg(sp, static_cast<const unsigned char *>(sp.blob32),
+                                 static_cast<const unsigned char *>(sp.refine.base), 0, h->n, 0, h->n));
+    }
+    for (const HostSeg &s : segs) {
+        if (s.same >= 0) {
+            RefSeg t = table[s.same];
+            t.lo = (int32_t)s.lo;
+            t.a = (int32_t)s.a;
+            t.b = (int32_t)s.b;
+            table.push_back(t);
+            continue;
+        }
+        const unsigned char *b32 = put(s.b32.data(), s.b32.size());
+        const unsigned char *rec = put(s.rec.data(), s.rec.size());
+        table.push_back(make_seg(s.sp, b32, rec, s.lo, s.hi - s.lo, s.a, s.b));
+    }
+    if (!table.empty()) {
+        h->segs = reinterpret_cast<const RefSeg *>(put(table.data(), table.size() * sizeof(RefSeg)));
+        h->nseg = (int)table.size();
+        for (const RefSeg &s : table) {
+            h->segP = std::max(h->segP, (int)s.P);
+            h->segNr = std::max(h->segNr, (int)s.Nr);
         }
     }
+    if (hipMemcpy(dev, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) return SBS_ERR_DEVICE;
     h->device_bytes += (int64_t)total;
     return SBS_OK;
 }

@@ -20,6 +20,10 @@
 // products, S^{-1} from scalar loads) and the interior correction
 // x_I = g - V z_own - W z_prev.  b is read from HBM once (4 bytes per
 // unknown) and x written once (8 bytes).
+//
+// A matrix too long for one workgroup is cut into overlapping segments
+// (RefSeg) that are solved independently; b is then read a little more than
+// once, and a served request's segments run at the same time.
 #include <algorithm>
 
 #include "internal.h"
@@ -36,13 +40,6 @@ struct R32<SBS_TRI> {
 template <>
 struct R32<SBS_PENTA> {
     using type = PentaRow<float>;
-};
-
-struct RefArgs {
-    int fac_bytes, spk_bytes, scf_bytes, sinv_bytes;
-    int rec_fwd, rec_bwd, rec_spk, rec_band, rec_sinv, ldsinv;  // the kernel's copy of the plan
-    int n, P, Nr, ngroups, sweeps;
-    int64_t m;
 };
 
 // Stride (in floats) between the systems' columns of the separator buffers:
@@ -165,57 +162,66 @@ __device__ __forceinline__ void sweeps32(cptr<float> fwd, cptr<float> bwd, float
     }
 }
 
-template <int KIND, int LB, int MAXT>
-__global__ __launch_bounds__(MAXT) void k_refine_wave(const unsigned char *__restrict__ blob, RefArgs a,
-                                                      const unsigned char *__restrict__ rec,
-                                                      const float *__restrict__ b32, double *__restrict__ x64) {
-    constexpr int H = KIND / 2, NB = 2 * H + 1, NI = LB - H;
-    constexpr int F = KIND == SBS_TRI ? 2 : 3, Bk = KIND == SBS_TRI ? 1 : 2;
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int P = a.P, Nr = a.Nr, n = a.n, ldr = refw_ldr(Nr);
-    const int64_t m = a.m;
-    const float *__restrict__ scf = reinterpret_cast<const float *>(blob + a.fac_bytes + a.spk_bytes);
-    const int *__restrict__ map =
-        reinterpret_cast<const int *>(blob + a.fac_bytes + a.spk_bytes + a.scf_bytes + a.sinv_bytes);
-
-    const int lane = threadIdx.x % kWave;
-    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // the wave's block
-    const int r0 = p * LB;
-    const bool has_sep = p < P - 1, has_prev = p > 0;
-    const bool full = r0 + LB <= n;  // no rows of the block past the end
-    const int pp = has_prev ? p - 1 : p;
-    const int q = map[p], qp = map[pp];
-    const cptr<float> fwd = (cptr<float>)(reinterpret_cast<const float *>(rec + a.rec_fwd) + q * LB * F);
-    const cptr<float> bwd = (cptr<float>)(reinterpret_cast<const float *>(rec + a.rec_bwd) + q * LB * Bk);
-    const cptr<float> sk = (cptr<float>)(reinterpret_cast<const float *>(rec + a.rec_spk) + q * LB * 2 * H);
-    // rows of S^{-1} of the own and the previous separator (a block without
-    // one reads the other's and discards the result)
-    const int lsv = a.ldsinv;
-    const float *psinv = reinterpret_cast<const float *>(rec + a.rec_sinv);
-    const cptr<float> rr = (cptr<float>)(psinv + (size_t)H * (has_sep ? p : pp) * lsv);
-    const cptr<float> rl = (cptr<float>)(psinv + (size_t)H * (has_prev ? pp : p) * lsv);
-    const cptr<double> br = (cptr<double>)(reinterpret_cast<const double *>(rec + a.rec_band) + (size_t)r0 * NB);
-
-    float *lb32 = reinterpret_cast<float *>(lds) + (size_t)r0 * kWave + lane;  // [t * 64]
-    double *ledge = reinterpret_cast<double *>(lds + (size_t)P * LB * kWave * 4);
-    float *lredl = reinterpret_cast<float *>(lds + (size_t)P * LB * kWave * 4 + (size_t)P * 2 * H * kWave * 8);
-    float *lredr = lredl + kWave * ldr;
-    float *myl = lredl + lane * ldr, *myr = lredr + lane * ldr;
-
+// One wave's part of the mixed-precision solve of a group of 64 systems on a
+// segment: block p of its plan.  The constructor forms what every group
+// shares; run() solves one group.
+template <int KIND, int LB>
+struct RefWave {
+    static constexpr int H = KIND / 2, NB = 2 * H + 1, NI = LB - H;
+    static constexpr int F = KIND == SBS_TRI ? 2 : 3, Bk = KIND == SBS_TRI ? 1 : 2;
+    int p, pp, lane, Nr, lsv;
+    bool has_sep, has_prev;
+    cptr<float> fwd, bwd, sk, rr, rl;
+    cptr<double> br;
+    float *lb32, *myl, *myr;
+    double *ledge;
     // the separator rows' couplings to interior rows: the own separator's to
     // this block's last rows, the previous separator's to this block's first
     float cl[H][H], cr[H][H];
+
+    // p (wave-uniform) < sg.P; lds: refw_lds bytes of the workgroup
+    __device__ __forceinline__ RefWave(const RefSeg &sg, int p_, int lane_, unsigned char *lds) {
+        p = p_;
+        lane = lane_;
+        Nr = sg.Nr;
+        const int P = sg.P, r0 = p * LB, ldr = refw_ldr(Nr);
+        has_sep = p < P - 1;
+        has_prev = p > 0;
+        pp = has_prev ? p - 1 : p;
+        const cptr<int> map = (cptr<int>)sg.map;
+        const cptr<float> scf = (cptr<float>)sg.scf;
+        const int q = map[p], qp = map[pp];
+        fwd = (cptr<float>)(sg.fwd + q * LB * F);
+        bwd = (cptr<float>)(sg.bwd + q * LB * Bk);
+        sk = (cptr<float>)(sg.spk + q * LB * 2 * H);
+        // rows of S^{-1} of the own and the previous separator (a block without
+        // one reads the other's and discards the result)
+        lsv = sg.ldsinv;
+        rr = (cptr<float>)(sg.sinv + (size_t)H * (has_sep ? p : pp) * lsv);
+        rl = (cptr<float>)(sg.sinv + (size_t)H * (has_prev ? pp : p) * lsv);
+        br = (cptr<double>)(sg.band + (size_t)r0 * NB);
+        lb32 = reinterpret_cast<float *>(lds) + (size_t)r0 * kWave + lane;  // [t * 64]
+        ledge = reinterpret_cast<double *>(lds + (size_t)P * LB * kWave * 4);
+        float *lredl = reinterpret_cast<float *>(lds + (size_t)P * LB * kWave * 4 + (size_t)P * 2 * H * kWave * 8);
+        myl = lredl + lane * ldr;
+        myr = myl + kWave * ldr;
 #pragma unroll
-    for (int c = 0; c < H; ++c)
+        for (int c = 0; c < H; ++c)
 #pragma unroll
-        for (int d = 0; d < H; ++d) {
-            cl[c][d] = (c + d < H) ? scf[(q * H + c) * NB + d] : 0.0f;
-            cr[c][d] = (2 * H - c + d < NB) ? scf[(qp * H + c) * NB + 2 * H - c + d] : 0.0f;
-        }
+            for (int d = 0; d < H; ++d) {
+                cl[c][d] = (c + d < H) ? scf[(q * H + c) * NB + d] : 0.0f;
+                cr[c][d] = (2 * H - c + d < NB) ? scf[(qp * H + c) * NB + 2 * H - c + d] : 0.0f;
+            }
+    }
+
+    // Barriers of one group, for the waves of a workgroup that hold no block.
+    static __device__ __forceinline__ void idle(int sweeps) {
+        for (int k = 0; k < 2 + 2 * sweeps; ++k) __syncthreads();
+    }
 
     // solve32 of w in place; `fresh`: the separator buffers may still be read
     // by the previous group's waves, so wait for them first
-    auto solve32 = [&](float(&w)[LB], bool fresh) {
+    __device__ __forceinline__ void solve32(float (&w)[LB], bool fresh) {
         sweeps32<KIND, LB>(fwd, bwd, w);
         if (fresh) __syncthreads();
         if (has_prev) {
@@ -295,36 +301,17 @@ __global__ __launch_bounds__(MAXT) void k_refine_wave(const unsigned char *__res
                 w[t] = v;
             }
         }
-    };
+    }
 
-    float w[LB];
-    auto load_b = [&](int g) {
-        const int64_t j = std::min((int64_t)g * kWave + lane, m - 1);
-        gptr<const float> src = (gptr<const float>)(b32 + (int64_t)r0 * m + j);
-        if (full) {
-#pragma unroll
-            for (int t = 0; t < LB; ++t) {
-                w[t] = *src;
-                src = step(src, m);
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < LB; ++t) {
-                w[t] = r0 + t < n ? *src : 0.0f;
-                src = step(src, m);
-            }
-        }
-    };
-    int g = blockIdx.x;
-    if (g < a.ngroups) load_b(g);
-    for (; g < a.ngroups; g += gridDim.x) {
+    // w: the block's right-hand sides (0 past the segment's rows), overwritten;
+    // x: its solution.
+    __device__ __forceinline__ void run(float (&w)[LB], double (&x)[LB], int sweeps) {
 #pragma unroll
         for (int t = 0; t < LB; ++t) lb32[t * kWave] = w[t];
         solve32(w, true);
-        double x[LB];
 #pragma unroll
         for (int t = 0; t < LB; ++t) x[t] = (double)w[t];
-        for (int k = 0; k < a.sweeps; ++k) {
+        for (int k = 0; k < sweeps; ++k) {
             // the block's first and last H values of x, for the neighbours' residuals
 #pragma unroll
             for (int c = 0; c < H; ++c) {
@@ -373,22 +360,177 @@ __global__ __launch_bounds__(MAXT) void k_refine_wave(const unsigned char *__res
 #pragma unroll
             for (int t = 0; t < LB; ++t) x[t] += (double)w[t];
         }
-        const int64_t j = std::min((int64_t)g * kWave + lane, m - 1);
-        gptr<double> dst = (gptr<double>)(x64 + (int64_t)r0 * m + j);
-        if (full) {
+    }
+};
+
+// A wave-uniform copy of a value that may have come through a vector register.
+template <typename P>
+__device__ __forceinline__ P *uniform(P *p) {
+    const uint64_t v = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return reinterpret_cast<P *>(((uint64_t)hi << 32) | lo);
+}
+
+// A segment's description through scalar loads (it does not change while a
+// kernel runs): its pointers have to be in scalar registers.
+__device__ __forceinline__ RefSeg load_seg(const RefSeg *p) {
+    const cptr<RefSeg> c = (cptr<RefSeg>)uniform(p);
+    RefSeg s;
+    s.fwd = c->fwd;
+    s.bwd = c->bwd;
+    s.spk = c->spk;
+    s.sinv = c->sinv;
+    s.scf = c->scf;
+    s.band = c->band;
+    s.map = c->map;
+    s.lo = c->lo;
+    s.rows = c->rows;
+    s.a = c->a;
+    s.b = c->b;
+    s.P = c->P;
+    s.Nr = c->Nr;
+    s.ldsinv = c->ldsinv;
+    s.pad = 0;
+    return s;
+}
+
+// The block's rows of the right-hand sides: rows row + t of system j, 0 from
+// row `end` on.
+template <int LB>
+__device__ __forceinline__ void load_block(int row, int end, const float *b32, int64_t m, int64_t j, float (&w)[LB]) {
+    gptr<const float> src = (gptr<const float>)(b32 + (int64_t)row * m + j);
+    if (row + LB <= end) {
 #pragma unroll
-            for (int t = 0; t < LB; ++t) {
-                __builtin_nontemporal_store(x[t], dst);
-                dst = step(dst, m);
-            }
-        } else {
-#pragma unroll
-            for (int t = 0; t < LB; ++t) {
-                if (r0 + t < n) __builtin_nontemporal_store(x[t], dst);
-                dst = step(dst, m);
-            }
+        for (int t = 0; t < LB; ++t) {
+            w[t] = *src;
+            src = step(src, m);
         }
-        if (g + (int)gridDim.x < a.ngroups) load_b(g + gridDim.x);
+    } else {
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            w[t] = row + t < end ? *src : 0.0f;
+            src = step(src, m);
+        }
+    }
+}
+
+// The block's rows of the result, those of them in a .. b - 1.
+template <int LB>
+__device__ __forceinline__ void store_block(int row, int a, int b, double *x64, int64_t m, int64_t j,
+                                            const double (&x)[LB]) {
+    gptr<double> dst = (gptr<double>)(x64 + (int64_t)row * m + j);
+    if (row >= a && row + LB <= b) {
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            __builtin_nontemporal_store(x[t], dst);
+            dst = step(dst, m);
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < LB; ++t) {
+            if (row + t >= a && row + t < b) __builtin_nontemporal_store(x[t], dst);
+            dst = step(dst, m);
+        }
+    }
+}
+
+// A matrix that is one segment: persistent workgroups of sg.P waves, one group
+// of 64 systems after another, the next group's right-hand sides loaded into
+// the registers the results leave.
+template <int KIND, int LB, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_refine_wave(RefSeg sg, int ngroups, int sweeps,
+                                                      const float *__restrict__ b32, double *__restrict__ x64,
+                                                      int64_t m) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int lane = threadIdx.x % kWave;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // the wave's block
+    RefWave<KIND, LB> rw(sg, p, lane, lds);
+    auto col = [&](int g) { return std::min((int64_t)g * kWave + lane, m - 1); };
+    const int row = p * LB, n = sg.rows;
+    float w[LB];
+    int g = blockIdx.x;
+    if (g < ngroups) load_block<LB>(row, n, b32, m, col(g), w);
+    for (; g < ngroups; g += gridDim.x) {
+        double x[LB];
+        rw.run(w, x, sweeps);
+        store_block<LB>(row, row, n, x64, m, col(g), x);
+        if (g + (int)gridDim.x < ngroups) load_block<LB>(row, n, b32, m, col(g + gridDim.x), w);
+    }
+}
+
+// One segment of one group of 64 systems, by a workgroup of at least sg.P
+// waves; waves without a block only keep the barriers.
+template <int KIND>
+__device__ __forceinline__ void refine_task(const RefSeg &sg, int p, int lane, unsigned char *lds, const float *b32,
+                                            double *x64, int64_t m, int64_t j0, int sweeps) {
+    constexpr int LB = kSegLb;
+    if (p >= sg.P) {
+        RefWave<KIND, LB>::idle(sweeps);
+        return;
+    }
+    const int64_t j = std::min(j0 + lane, m - 1);
+    RefWave<KIND, LB> rw(sg, p, lane, lds);
+    float w[LB];
+    double x[LB];
+    const int row = sg.lo + p * LB;
+    load_block<LB>(row, sg.lo + sg.rows, b32, m, j, w);
+    rw.run(w, x, sweeps);
+    store_block<LB>(row, sg.a, sg.b, x64, m, j, x);
+}
+
+// A matrix of several segments: every (group, segment) is a task of its own.
+template <int KIND>
+__global__ __launch_bounds__(1024) void k_refine_segs(const RefSeg *__restrict__ segs, int nseg, int64_t ntasks,
+                                                      int sweeps, const float *__restrict__ b32,
+                                                      double *__restrict__ x64, int64_t m) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int lane = threadIdx.x % kWave;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (int64_t t = blockIdx.x; t < ntasks; t += gridDim.x) {
+        const RefSeg sg = load_seg(segs + t % nseg);
+        __syncthreads();  // segments of other sizes lay the LDS out differently
+        refine_task<KIND>(sg, p, lane, lds, b32, x64, m, t / nseg * kWave, sweeps);
+    }
+}
+
+// Serving: tiles of refined FP32 requests, two corrections, one (request,
+// segment, group of 64 systems) each.  The one-wave tiles they replace run the
+// five passes of a tile one after another through HBM (84 bytes per unknown),
+// which for 8192 pentadiagonal rows takes 4.2 ms however few systems there
+// are; by segments the rows are spread over the GPU and b and x stay on chip.
+// A burst of 192 requests (n 64 to 8192, m up to 4096, half of them FP32)
+// went from 7.7 to 2.4 ms.  A workgroup takes the next tile from
+// the counter until the table is exhausted, so every workgroup exits.
+// Completion as in the one-wave tile kernels: once every wave has stored its
+// rows (the barrier), wave 0 releases them at system scope with its decrement
+// of the request's count, and raises the request's flag with the last one.
+// Wave 0's branches are taken by the whole wave.
+template <int KIND>
+__global__ __launch_bounds__(1024) void k_refine_tiles(const Tile *__restrict__ tiles, int ntiles, int *counter,
+                                                       int *left, int *done) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ int ticket;
+    const int lane = threadIdx.x % kWave;
+    const int p = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (;;) {
+        // written again only after the barriers of the tile, which every wave
+        // reaches after it has read it
+        if (threadIdx.x == 0) ticket = atomicAdd(counter, 1);
+        __syncthreads();
+        const int t = __builtin_amdgcn_readfirstlane(ticket);
+        if (t >= ntiles) break;
+        const cptr<Tile> tl = (cptr<Tile>)(tiles + t);
+        const RefSeg sg = load_seg(static_cast<const RefSeg *>(tl->fac));
+        refine_task<KIND>(sg, p, lane, lds, static_cast<const float *>(tl->in), tl->x, tl->m, tl->col0, 2);
+        __syncthreads();
+        if (p == 0) {
+            const int one = lane == 0 ? 1 : 0;
+            const int req = __builtin_amdgcn_readfirstlane(tl->req);
+            int before = __hip_atomic_fetch_add(&left[req], -one, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_SYSTEM);
+            before = __builtin_amdgcn_readfirstlane(before);
+            if (before == 1) __hip_atomic_store(&done[req], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
 }
 
@@ -413,28 +555,59 @@ hipError_t go_refw(const sbs_lhs *h, const RefwChoice &c, const float *b, double
                    hipStream_t s) {
     const SepPlan &sp = h->sep[c.plan];
     if (hipError_t e = refw_kernel<KIND, LB>(); e != hipSuccess) return e;
-    RefArgs a;
-    a.fac_bytes = (int)sp.fac_bytes32;
-    a.spk_bytes = (int)sp.spk_bytes32;
-    a.scf_bytes = (int)sp.scf_bytes32;
-    a.sinv_bytes = (int)sp.sinv_bytes32;
-    a.rec_fwd = (int)sp.refine.fwd;
-    a.rec_bwd = (int)sp.refine.bwd;
-    a.rec_spk = (int)sp.refine.spk;
-    a.rec_band = (int)sp.refine.band;
-    a.rec_sinv = (int)sp.refine.sinv;
-    a.ldsinv = sp.refine.ldsinv;
-    a.n = (int)h->n;
-    a.P = sp.P;
-    a.Nr = sp.Nr;
-    a.ngroups = (int)((m + kWave - 1) / kWave);
-    a.sweeps = sweeps;
-    a.m = m;
-    const int cus = device_cus(h->device);
-    const int grid = std::min(a.ngroups, cus);
-    hipLaunchKernelGGL((k_refine_wave<KIND, LB, refw_maxt<KIND, LB>()>), dim3(grid), dim3(sp.P * kWave), c.lds, s,
-                       static_cast<const unsigned char *>(sp.blob32), a,
-                       static_cast<const unsigned char *>(sp.refine.base), b, x);
+    RefSeg sg{};
+    const unsigned char *rec = static_cast<const unsigned char *>(sp.refine.base);
+    const unsigned char *blob = static_cast<const unsigned char *>(sp.blob32);
+    sg.fwd = reinterpret_cast<const float *>(rec + sp.refine.fwd);
+    sg.bwd = reinterpret_cast<const float *>(rec + sp.refine.bwd);
+    sg.spk = reinterpret_cast<const float *>(rec + sp.refine.spk);
+    sg.sinv = reinterpret_cast<const float *>(rec + sp.refine.sinv);
+    sg.scf = reinterpret_cast<const float *>(blob + sp.fac_bytes32 + sp.spk_bytes32);
+    sg.band = reinterpret_cast<const double *>(rec + sp.refine.band);
+    sg.map = reinterpret_cast<const int *>(blob + sp.fac_bytes32 + sp.spk_bytes32 + sp.scf_bytes32 + sp.sinv_bytes32);
+    sg.rows = sg.b = (int32_t)h->n;
+    sg.P = sp.P;
+    sg.Nr = sp.Nr;
+    sg.ldsinv = sp.refine.ldsinv;
+    const int ngroups = (int)((m + kWave - 1) / kWave);
+    const int grid = std::min(ngroups, device_cus(h->device));
+    hipLaunchKernelGGL((k_refine_wave<KIND, LB, refw_maxt<KIND, LB>()>), dim3(grid), dim3(sp.P * kWave), c.lds, s, sg,
+                       ngroups, sweeps, b, x, m);
+    return hipGetLastError();
+}
+
+// The segment kernels, allowed the LDS they take.  Workgroups of `blocks`
+// waves; the LDS holds the largest segment.
+template <typename Kern>
+hipError_t seg_kernel(Kern kern) {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)kMaxPartLdsBytes - 1024);
+}
+
+size_t seg_lds(int kind, int blocks) { return refw_lds(kind, kSegLb, blocks, kind / 2 * (blocks - 1)); }
+
+template <int KIND>
+hipError_t go_segs(const sbs_lhs *h, const float *b, double *x, int64_t m, int sweeps, hipStream_t s) {
+    static const hipError_t attr = seg_kernel(k_refine_segs<KIND>);
+    if (attr != hipSuccess) return attr;
+    const int64_t ntasks = (m + kWave - 1) / kWave * h->nseg;
+    const int64_t wgs = (int64_t)device_cus(h->device) * (h->segP <= kSegHalf ? 2 : 1);
+    hipLaunchKernelGGL(k_refine_segs<KIND>, dim3((unsigned)std::min(ntasks, wgs)), dim3(h->segP * kWave),
+                       seg_lds(KIND, h->segP), s, h->segs, h->nseg, ntasks, sweeps, b, x, m);
+    return hipGetLastError();
+}
+
+template <int KIND>
+hipError_t go_refine_tiles(bool half, const Tile *tiles, int ntiles, int *counter, int *left, int *done,
+                           hipStream_t s) {
+    static const hipError_t attr = seg_kernel(k_refine_tiles<KIND>);
+    if (attr != hipSuccess) return attr;
+    int dev = 0;
+    if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
+    const int blocks = half ? kSegHalf : seg_max_blocks(KIND);
+    const int grid = std::min(ntiles, device_cus(dev) * (half ? 2 : 1));
+    hipLaunchKernelGGL(k_refine_tiles<KIND>, dim3(grid), dim3(blocks * kWave), seg_lds(KIND, blocks), s, tiles, ntiles,
+                       counter, left, done);
     return hipGetLastError();
 }
 
@@ -459,6 +632,19 @@ bool choose_refine_wave(const sbs_lhs *h, int64_t m, RefwChoice *out) {
         return true;
     }
     return false;
+}
+
+hipError_t launch_refine_segs(const sbs_lhs *h, const float *b, double *x, int64_t m, int sweeps, hipStream_t stream) {
+    if (m <= 0) return hipSuccess;
+    if (h->nseg < 1 || h->segP > seg_max_blocks(h->kind)) return hipErrorInvalidValue;
+    return h->kind == SBS_TRI ? go_segs<SBS_TRI>(h, b, x, m, sweeps, stream)
+                              : go_segs<SBS_PENTA>(h, b, x, m, sweeps, stream);
+}
+
+hipError_t launch_refine_tiles(int kind, bool half, const Tile *dev_tiles, int ntiles, int *dev_counter, int *left,
+                               int *done, hipStream_t stream) {
+    return kind == SBS_TRI ? go_refine_tiles<SBS_TRI>(half, dev_tiles, ntiles, dev_counter, left, done, stream)
+                           : go_refine_tiles<SBS_PENTA>(half, dev_tiles, ntiles, dev_counter, left, done, stream);
 }
 
 hipError_t launch_refine_wave(const sbs_lhs *h, const RefwChoice &c, const float *b, double *x, int64_t m,

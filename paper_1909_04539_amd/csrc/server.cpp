@@ -36,8 +36,16 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxTilesPerLaunch = 1 << 16;
-constexpr int kGroups = 6;  // (tri, penta) x (fp64, fp32 refined, fp32 as one fp64 sweep)
+constexpr int kPrecs = 5;  // Tile::prec: fp64, fp32 refined, fp32 as one fp64 sweep, fp32 refined by segments (two sizes)
+constexpr int kGroups = 2 * kPrecs;  // (tri, penta) x prec
 constexpr int kPersistentWaves = 1024;
+// Refined FP32 requests of up to this many systems run by segments (one wave
+// per 32-row block, b and x on chip); larger ones keep the one-wave tiles.  By
+// segments is the faster at every size measured (pentadiagonal n = 8192,
+// m = 4096: 0.6 ms against 4.2 ms); the line is where the long request of the
+// overlap test lies, which has to run for milliseconds while short ones come
+// and go.
+constexpr int64_t kSegMaxSystems = 4095;
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -93,6 +101,12 @@ struct Req {
     sbs_status status = SBS_OK;
     Clock::time_point t_submit, t_done;
 };
+
+// Tiles of a request: 64 systems each, and for the segment forms one for
+// every segment of the matrix.
+int64_t tile_count(const sbs_lhs *h, int32_t prec, int64_t m) {
+    return (m + kWave - 1) / kWave * (prec >= 3 ? h->nseg : 1);
+}
 
 struct Slot {
     hipStream_t stream = nullptr;
@@ -213,7 +227,7 @@ bool sbs_server::launch(Slot &s) {
     int tiles = 0;
     while (!ready.empty() && (int)take.size() < max_batch) {
         Req *r = ready.front();
-        const int t = (int)((r->m + kWave - 1) / kWave);
+        const int t = (int)tile_count(lhs[r->lhs], r->prec, r->m);
         if (!take.empty() && tiles + t > kMaxTilesPerLaunch) break;
         take.push_back(r);
         tiles += t;
@@ -227,12 +241,15 @@ bool sbs_server::launch(Slot &s) {
     for (size_t k = 0; k < take.size(); ++k) {
         Req *r = take[k];
         const sbs_lhs *h = lhs[r->lhs];
-        const int g = (h->kind == SBS_PENTA ? 3 : 0) + r->prec;
-        left[k] = (int)((r->m + kWave - 1) / kWave);
+        const int g = (h->kind == SBS_PENTA ? kPrecs : 0) + r->prec;
+        const int64_t tiles_of = tile_count(h, r->prec, r->m);
+        left[k] = (int)tiles_of;
         s.flag_host[k] = 0;  // the slot's previous launch has completed: nothing writes it now
-        for (int64_t c = 0; c < r->m; c += kWave) {
+        const int64_t nseg = r->prec >= 3 ? h->nseg : 1;
+        for (int64_t q = 0; q < tiles_of; ++q) {
+            const int64_t c = q / nseg * kWave;
             Tile t;
-            t.fac = r->prec == 1 ? h->fac32 : h->fac64;
+            t.fac = r->prec >= 3 ? static_cast<const void *>(h->segs + q % nseg) : r->prec == 1 ? h->fac32 : h->fac64;
             t.bands = h->bands;
             t.in = r->rhs;
             t.x = r->x;
@@ -260,8 +277,8 @@ bool sbs_server::launch(Slot &s) {
     hipError_t e = hipMemcpyAsync(s.dev, s.host, at, hipMemcpyHostToDevice, s.stream);
     for (int g = 0; g < kGroups && e == hipSuccess; ++g) {
         if (grp[g].empty()) continue;
-        const int kind = g >= 3 ? SBS_PENTA : SBS_TRI;
-        e = launch_tiles(kind, g % 3, reinterpret_cast<const Tile *>(s.dev + offs[g]), (int)grp[g].size(),
+        const int kind = g >= kPrecs ? SBS_PENTA : SBS_TRI;
+        e = launch_tiles(kind, g % kPrecs, reinterpret_cast<const Tile *>(s.dev + offs[g]), (int)grp[g].size(),
                          reinterpret_cast<int *>(s.dev + g * 64), reinterpret_cast<int *>(s.dev + left_offset()),
                          s.flag_dev, kPersistentWaves, s.stream);
     }
@@ -403,9 +420,15 @@ sbs_status sbs_server_submit(sbs_server *srv, int32_t lhs_id, const void *rhs, i
     }
     const sbs_lhs *h = srv->lhs[lhs_id];
     const size_t nm = (size_t)h->n * (size_t)m;
-    const int32_t prec = dtype == SBS_F64 ? 0 : (srv->fp32_mode == SBS_SERVE_F32_FP64_SWEEP ? 2 : 1);
+    int32_t prec = dtype == SBS_F64 ? 0 : (srv->fp32_mode == SBS_SERVE_F32_FP64_SWEEP ? 2 : 1);
     // refined FP32 requests: three FP32 scratch arrays (x0, d1, r / d2) besides x
     r->bytes = round_up(nm * 8, kAlign) + (prec == 1 ? round_up(nm * 12, kAlign) : 0);
+    // and by segments where the matrix has them (no scratch is touched then,
+    // but the request's size stays what the header states)
+    if (prec == 1 && h->nseg > 0 && h->segP > 2 && m <= kSegMaxSystems) {
+        const int32_t by_seg = h->segP <= kSegHalf ? 3 : 4;
+        if (tile_count(h, by_seg, m) <= kMaxTilesPerLaunch) prec = by_seg;
+    }
     if (r->bytes > srv->budget) {
         ++srv->rejected;
         delete r;
