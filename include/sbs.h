@@ -194,9 +194,15 @@ sbs_status sbs_solve_batch_partition(sbs_handle h, void *rhs, int64_t m,
                                      int32_t vec, int32_t S, int32_t flags,
                                      void *stream);
 
-/* The partitioned shape AUTO runs for m systems of this dtype at rhs (host
- * only, rhs is not read: its alignment decides vec).  Returns
- * SBS_ERR_NOT_FOUND (outputs 0) if AUTO runs the sweeps. */
+/* The partitioned shape AUTO runs for m systems of this dtype at rhs when each
+ * system is solved whole (host only, rhs is not read: its alignment decides
+ * vec).  Returns SBS_ERR_NOT_FOUND (outputs 0) if that is the sweeps.
+ * Long systems and large batches of matrices whose inverse decays within 192
+ * rows (diagonally dominant and positive definite ones) AUTO may cut instead:
+ * the unknowns of a few rows come first, from the rows of the inverse around
+ * them (what is dropped is below 2^-57 of a row's largest entry), and the
+ * segments of 256 rows between them are then solved independently.  This
+ * call and sbs_auto_variant report the whole-system form there too. */
 sbs_status sbs_partition_shape(sbs_handle h, int64_t m, int32_t dtype,
                                const void *rhs, int32_t *form, int32_t *lb,
                                int32_t *vec, int32_t *S);

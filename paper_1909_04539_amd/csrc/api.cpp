@@ -147,15 +147,43 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
     return 0;
 }
 
+// Whether AUTO takes the cut form (two kernels, segments of 256 rows in runs of
+// up to 1 KiB) instead of `form`.  Always where a workgroup cannot hold a whole
+// system with its plan in LDS: the sweeps run one lane per system
+// (pentadiagonal n = 5000, m = 500: 25 against 427 us; tridiagonal n = 8192,
+// m = 4096: 122 against 618 us) and a plan in memory costs a trip per block
+// (pentadiagonal n = 1500 random, m = 2048: 24 against 127 us).  Else where the
+// right-hand sides no longer stay in the 256 MB memory-side cache from one
+// launch to the next, so that the length of the runs decides (pentadiagonal
+// n = 1024, m = 65536: 230 against 253 us; tridiagonal n = 2000, m = 16384:
+// 110 against 153 us; FP32 n = 2000, m = 50001: 216 against 343 us); below,
+// the second kernel costs more than the runs gain (n = 1000, m = 8192:
+// tridiagonal 31 against 24, pentadiagonal 34 against 26 us).  The line lies
+// between 131 MB (n = 1000, m = 16384: tridiagonal 54 against 56,
+// pentadiagonal 59 against 57 us) and 262 MB (m = 32769: 121 against 148, 127
+// against 149 us), and where the whole-system form has runs under 256 bytes
+// between 66 MB (n = 2000, m = 4096: 31 against 30 us) and 98 MB (n = 1500,
+// m = 8192: 46 against 50, 49 against 68 us).
+bool takes_cut(const sbs_lhs *h, int t, int64_t m, int form, const sbs::SepChoice &sc, const sbs::PartChoice &pc) {
+    if (form == 0 || (form == 1 && sc.gf)) return true;
+    const int64_t elem = t == 0 ? 8 : 4, bytes = h->n * m * elem;
+    const int64_t run = (form == 1 ? sc.S : pc.S) * elem;
+    return bytes >= (run < 256 ? 90000000 : int64_t(1) << 27);
+}
+
 // The choice depends on the handle, the dtype, m, whether rhs is aligned for
 // two systems per lane and AUTO or not; it is made once and kept (weighing
 // every shape costs several microseconds, as much as a small solve).
+//
+// cut (optional): the cut form where AUTO takes it instead (takes_cut); S 0 if
+// it does not.  The queries report the whole-system form.
 int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_auto, sbs::SepChoice *sc,
-                   sbs::PartChoice *pc) {
+                   sbs::PartChoice *pc, sbs::CutChoice *cut = nullptr) {
     struct Pick {
         int form;
         sbs::SepChoice sc;
         sbs::PartChoice pc;
+        sbs::CutChoice cut;
     };
     static std::mutex mu;
     static std::map<std::tuple<uint64_t, int, int64_t, bool, bool>, Pick> known;
@@ -167,13 +195,17 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
         if (it != known.end()) {
             *sc = it->second.sc;
             *pc = it->second.pc;
+            if (cut) *cut = it->second.cut;
             return it->second.form;
         }
     }
     const int form = pick_uncached(h, t, m, rhs, for_auto, sc, pc);
+    sbs::CutChoice cc;
+    if (for_auto && takes_cut(h, t, m, form, *sc, *pc)) sbs::choose_cut(h, t, m, &cc);
+    if (cut) *cut = cc;
     std::lock_guard<std::mutex> g(mu);
     if (known.size() >= 4096) known.clear();  // bounded: many batch sizes only cost a new choice
-    known[key] = Pick{form, *sc, *pc};
+    known[key] = Pick{form, *sc, *pc, cc};
     return form;
 }
 
@@ -376,9 +408,12 @@ sbs_status sbs_solve_batch_variant(sbs_handle h, void *rhs, int64_t m, int32_t d
     if (variant == SBS_VARIANT_AUTO || variant == SBS_VARIANT_PARTITION) {
         SepChoice sc;
         PartChoice pc;
-        const int form = pick_partition(h, t, m, rhs, variant == SBS_VARIANT_AUTO, &sc, &pc);
+        CutChoice cut;
+        const int form = pick_partition(h, t, m, rhs, variant == SBS_VARIANT_AUTO, &sc, &pc, &cut);
         hipStream_t s = static_cast<hipStream_t>(stream);
-        if (form == 1)
+        if (cut.S)
+            e = launch_cut(h, cut, t, rhs, m, s);
+        else if (form == 1)
             e = launch_sep(h, sc, t, rhs, m, s);
         else if (form == 2)
             e = launch_partition(h, pc, t, t, t, rhs, rhs, m, s);

@@ -167,6 +167,38 @@ struct SepPlan {
     }
 };
 
+// Cut form of a plain solve (systems too long for one workgroup).  The matrix
+// is cut at Q - 1 places, h rows each; the rows between two cuts are a segment.
+// With the unknowns of the cut rows known the segments decouple.  Those
+// unknowns come first: row c of A^{-1} times the right-hand side, of which only
+// the entries near the diagonal matter where the inverse decays (CutWin), and
+// they are stored in place of their right-hand sides.  Then every segment is
+// solved on its own by the separator kernel, its first and last h right-hand
+// sides less their couplings to the cut rows beside them.
+struct alignas(16) CutSeg {
+    const unsigned char *blob[2];          // the segment's separator plan, FP64 and FP32
+    int32_t fac[2], spk[2], scf[2], sinv[2], map;  // its parts' bytes
+    int32_t row0, rows, P, Nr, kofs, kw;
+    int32_t has_lo, has_hi, pad;           // whether a cut lies before / after the segment
+    double lo[2][2];  // coefficient of the segment's row t on unknown c of the cut before it
+    double hi[2][2];  // of its row rows - h + t on unknown c of the cut after it
+};
+struct alignas(16) CutWin {
+    const double *w;      // [len][h]: entries first .. first + len - 1 of the h rows of A^{-1}
+    int32_t row, first, len, pad;  // the cut's first row
+};
+constexpr int kCutRows = 256;      // rows of a segment, at most
+constexpr int kMaxCutSegs = 512;   // segments of one matrix (n up to about 130 000)
+constexpr int kMaxCutReach = 192;  // rows of A^{-1} kept on either side of a cut
+
+struct CutPlan {
+    const CutSeg *segs = nullptr;  // device arrays
+    const CutWin *wins = nullptr;
+    int Q = 0;                     // segments (0: the matrix has no cut form)
+    int P = 0, Nr = 0;             // the largest of them
+    size_t blob_bytes[2] = {0, 0};
+};
+
 }  // namespace sbs
 
 struct sbs_lhs {
@@ -180,6 +212,7 @@ struct sbs_lhs {
     void *pdev = nullptr;       // partition data (one allocation for all plans)
     const sbs::RefSeg *segs = nullptr;  // device array, nseg segments (0: the matrix has none)
     int nseg = 0, segP = 0, segNr = 0;  // segP, segNr: the largest P and Nr among them
+    sbs::CutPlan cut;
     sbs::PartPlan part[3];      // block lengths 16, 32, 64
     sbs::SepPlan sep[3];        // block lengths 16, 32, 64
     // every band constant over the rows where it lies inside the matrix
@@ -293,6 +326,14 @@ bool sep_shape(const sbs_lhs *h, int tc, int64_t m, const void *x, int lb, int v
 // Crank-Nicolson steps for a shape chosen for them.
 hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t stream,
                       int steps = 1);
+// The cut form of a plain solve: systems per workgroup (two per lane).
+struct CutChoice {
+    int S = 0, threads = 0;  // S 0: none
+    size_t lds = 0;
+    int wgs = 1;
+};
+bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out);
+hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, hipStream_t stream);
 // Whether the separator shape fills the GPU with whole 256-byte row runs.
 bool sep_fills(const sbs_lhs *h, int tc, int64_t m, const SepChoice &c);
 

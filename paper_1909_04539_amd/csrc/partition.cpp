@@ -419,12 +419,12 @@ void sep_plan_solve(const SepHostPlan &hp, int h, bool periodic, int64_t n, Solv
 
 template <typename Row, typename SolveFn>
 double sep_plan_deviation(const SepHostPlan &hp, int kind, bool periodic, int64_t n, const double *bands,
-                          SolveFn solve) {
+                          SolveFn solve, int checks) {
     const int h = kind / 2;
     uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
     double worst = 0.0;
     std::vector<double> d(n), a, b;
-    for (int q = 0; q < kPlanChecks; ++q) {
+    for (int q = 0; q < checks; ++q) {
         for (int64_t i = 0; i < n; ++i) {
             st ^= st << 13;
             st ^= st >> 7;
@@ -447,10 +447,11 @@ double sep_plan_deviation(const SepHostPlan &hp, int kind, bool periodic, int64_
 }
 
 // kind 3 or 5; `periodic` wraps a tridiagonal matrix round (needs n a whole
-// number P >= 2 of blocks; every block then has a separator).
+// number P >= 2 of blocks; every block then has a separator).  checks: seeded
+// right-hand sides of the accuracy gate (0: the caller checks the whole).
 template <typename Row, typename FactorFn, typename SolveFn>
 bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int lb, FactorFn factor, SolveFn solve,
-                    SepHostPlan &hp) {
+                    SepHostPlan &hp, int checks = kPlanChecks) {
     const int h = kind / 2, nb = 2 * h + 1;
     const int P = (int)((n + lb - 1) / lb);
     if (periodic && (n % lb != 0 || P < 2)) return false;
@@ -568,7 +569,7 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
         }
     }
     hp.sinv.swap(S);
-    return sep_plan_deviation<Row>(hp, kind, periodic, n, bands, solve) <= kPlanTolerance;
+    return sep_plan_deviation<Row>(hp, kind, periodic, n, bands, solve, checks) <= kPlanTolerance;
 }
 
 template <typename Row32, typename Row64>
@@ -810,7 +811,7 @@ std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, Fa
         for (int64_t k = 0; k < ns; ++k) {
             HostSeg &s = segs[k];
             if (s.same >= 0) continue;
-            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, s.hp)) return {};
+            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, s.hp, 1)) return {};
             std::vector<unsigned char> b64;
             serialise_sep<Row, Row32>(s.hp, b64, s.b32, s.sp);
             serialise_refine<Row32>(s.hp, s.b32, s.sp, kind, s.hi - s.lo, sub[k].data(), s.rec, s.sp.refine);
@@ -818,6 +819,175 @@ std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, Fa
         return segs;
     }
     return {};
+}
+
+// ---------------------------------------------------------------------------
+// Cut form (CutSeg, CutWin).
+
+struct HostCutSeg {
+    int64_t a = 0, b = 0;  // rows
+    int same = -1;         // an earlier segment that is the same matrix, or -1
+    SepHostPlan hp;
+    SepPlan sp;
+    std::vector<unsigned char> b64, b32;
+};
+struct HostCutWin {
+    int64_t row = 0, first = 0;
+    int same = -1;
+    int len = 0;
+    std::vector<double> w;  // [len][h]
+};
+struct HostCuts {
+    std::vector<HostCutSeg> segs;
+    std::vector<HostCutWin> wins;
+};
+
+// Rows c .. c + h - 1 of A^{-1} near their diagonal entries: the solutions of
+// A^T w = e on the rows within kCutNear of the cut (the matrix beyond changes
+// the entries kept below by the square of the decay over kCutNear rows).
+// On either side entries are dropped while their magnitudes add up to at most
+// 2^-58 of the row's largest, which moves the unknown by at most 2^-57 of
+// (row's largest) x (largest right-hand side), 1/16 of the rounding of one
+// term of its sum; false if more than kMaxCutReach rows on a side are left.
+constexpr int64_t kCutNear = 256;
+
+template <typename Row, typename FactorFn, typename SolveFn>
+bool cut_window(int kind, int64_t n, const double *bands, int64_t row, FactorFn factor, SolveFn solve, HostCutWin &win) {
+    const int h = kind / 2;
+    const int64_t lo = std::max<int64_t>(0, row - kCutNear), hi = std::min<int64_t>(n, row + h + kCutNear), ns = hi - lo;
+    std::vector<Row> rows(ns);
+    int64_t bad = -1;
+    // entry (i, i + k - h) of A^T is A's entry (i + k - h, i): band 2h - k of that row
+    auto tr = [&](int k, int64_t i) -> double {
+        const int64_t j = i + k - h;
+        return j < 0 || j >= ns ? 0.0 : bands[(int64_t)(2 * h - k) * n + lo + j];
+    };
+    if (!factor(ns, tr, rows.data(), &bad)) return false;
+    std::vector<double> v((size_t)h * ns, 0.0);
+    int64_t reach_lo = 0, reach_hi = 0;
+    for (int c = 0; c < h; ++c) {
+        double *w = v.data() + (size_t)c * ns;
+        w[row + c - lo] = 1.0;
+        solve(ns, rows.data(), w);
+        double mx = 0.0;
+        for (int64_t i = 0; i < ns; ++i) mx = std::max(mx, std::fabs(w[i]));
+        if (!std::isfinite(mx)) return false;
+        const double most = std::ldexp(mx, -58);
+        int64_t i = 0, e = ns - 1;
+        for (double s = 0.0; i < row - lo && (s += std::fabs(w[i])) <= most; ++i) {
+        }
+        for (double s = 0.0; e > row + h - 1 - lo && (s += std::fabs(w[e])) <= most; --e) {
+        }
+        reach_lo = std::max(reach_lo, row - lo - i);
+        reach_hi = std::max(reach_hi, lo + e - (row + h - 1));
+    }
+    if (reach_lo > kMaxCutReach || reach_hi > kMaxCutReach) return false;
+    win.row = row;
+    win.first = row - reach_lo;
+    win.len = (int)(reach_lo + h + reach_hi);
+    win.w.resize((size_t)win.len * h);
+    for (int i = 0; i < win.len; ++i)
+        for (int c = 0; c < h; ++c) win.w[(size_t)i * h + c] = v[(size_t)c * ns + (win.first - lo) + i];
+    return true;
+}
+
+// The cut form's own solve of one column, as the kernels run it.
+template <typename Row, typename SolveFn>
+void cut_solve(const HostCuts &hc, int kind, int64_t n, const double *bands, SolveFn solve, std::vector<double> &x) {
+    const int h = kind / 2;
+    for (size_t k = 0; k < hc.wins.size(); ++k) {
+        const HostCutWin &w = hc.wins[k], &src = w.same >= 0 ? hc.wins[w.same] : w;
+        double z[2] = {0.0, 0.0};
+        for (int i = 0; i < src.len; ++i)
+            for (int c = 0; c < h; ++c) z[c] += src.w[(size_t)i * h + c] * x[w.first + i];
+        for (int c = 0; c < h; ++c) x[w.row + c] = z[c];
+    }
+    for (const HostCutSeg &s : hc.segs) {
+        std::vector<double> f(x.begin() + s.a, x.begin() + s.b);
+        const int64_t ns = s.b - s.a;
+        for (int t = 0; t < h; ++t)
+            for (int c = 0; c < h; ++c) {
+                if (s.a > 0 && c >= t && t < ns) f[t] -= bands[(int64_t)(c - t) * n + s.a + t] * x[s.a - h + c];
+                if (s.b < n && c <= t) f[ns - h + t] -= bands[(int64_t)(2 * h + c - t) * n + s.b - h + t] * x[s.b + c];
+            }
+        sep_plan_solve<Row>(s.same >= 0 ? hc.segs[s.same].hp : s.hp, h, false, ns, solve, f);
+        std::copy(f.begin(), f.end(), x.begin() + s.a);
+    }
+}
+
+// Cuts the matrix into Q segments of at most kCutRows rows, all of them a
+// whole number of 32-row blocks but the last; false if a plan is missing, a
+// window too wide, or the result not the recurrences' within kPlanTolerance.
+template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
+bool build_cuts(int kind, int64_t n, const double *bands, FactorFn factor, SolveFn solve, HostCuts &hc) {
+    const int h = kind / 2;
+    const int64_t Q = (n + h + kCutRows + h - 1) / (kCutRows + h);
+    if (Q < 2 || Q > kMaxCutSegs) return false;
+    const int64_t run = ((n - h * (Q - 1) + Q - 1) / Q + kSegLb - 1) / kSegLb * kSegLb;
+    std::vector<std::vector<double>> sub;
+    for (int64_t a = 0; a < n;) {
+        HostCutSeg s;
+        s.a = a;
+        // a remainder of no more than a cut would leave an empty last segment
+        s.b = a + run + h < n ? a + run : n;
+        sub.push_back(sub_bands(kind, n, bands, s.a, s.b));
+        for (size_t q = 0; q < hc.segs.size() && s.same < 0; ++q)
+            if (hc.segs[q].same < 0 && sub[q] == sub.back()) s.same = (int)q;
+        if (s.b - s.a > kCutRows + h) return false;
+        if (s.same < 0 &&
+            !build_sep_plan<Row>(kind, false, s.b - s.a, sub.back().data(), kSegLb, factor, solve, s.hp, 0))
+            return false;
+        hc.segs.push_back(std::move(s));
+        if (hc.segs.back().b < n) {
+            HostCutWin w;
+            const int64_t row = hc.segs.back().b;
+            // an earlier cut whose surroundings are the same has the same window
+            for (size_t q = 0; q < hc.wins.size() && w.same < 0; ++q) {
+                const HostCutWin &o = hc.wins[q];
+                if (o.same >= 0 || o.row < kCutNear + h || row + 2 * h + kCutNear > n) continue;
+                bool alike = true;
+                for (int64_t i = -kCutNear - h; i < kCutNear + 2 * h && alike; ++i)
+                    for (int b = 0; b < kind && alike; ++b) alike = bands[b * n + row + i] == bands[b * n + o.row + i];
+                if (!alike) continue;
+                w.same = (int)q;
+                w.row = row;
+                w.first = row + (o.first - o.row);
+                w.len = o.len;
+            }
+            if (w.same < 0 && !cut_window<Row>(kind, n, bands, row, factor, solve, w)) return false;
+            hc.wins.push_back(std::move(w));
+        }
+        a = hc.segs.back().b + h;
+        if (hc.segs.back().b == n) break;
+    }
+    // a window must not reach another cut: its rows are overwritten
+    for (size_t k = 0; k < hc.wins.size(); ++k) {
+        const HostCutWin &w = hc.wins[k];
+        if (k > 0 && w.first < hc.wins[k - 1].row + h) return false;
+        if (k + 1 < hc.wins.size() && w.first + w.len > hc.wins[k + 1].row) return false;
+    }
+    uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
+    std::vector<double> d(n), x;
+    for (int64_t i = 0; i < n; ++i) {
+        st ^= st << 13;
+        st ^= st >> 7;
+        st ^= st << 17;
+        d[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
+    }
+    x = d;
+    reference_solve(kind, false, n, bands, d);
+    cut_solve<Row>(hc, kind, n, bands, solve, x);
+    double num = 0.0, den = 0.0;
+    bool nan = false;
+    for (int64_t i = 0; i < n; ++i) {
+        nan |= std::isnan(x[i]);
+        num = std::max(num, std::fabs(x[i] - d[i]));
+        den = std::max(den, std::fabs(d[i]));
+    }
+    if (nan || !(num <= kPlanTolerance * den)) return false;
+    for (HostCutSeg &s : hc.segs)
+        if (s.same < 0) serialise_sep<Row, Row32>(s.hp, s.b64, s.b32, s.sp);
+    return true;
 }
 
 // The device's view of a segment: plan blob (FP32) and the kernel's copy.
@@ -915,6 +1085,17 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
         if (s.same < 0) total += align256(s.b32.size()) + align256(s.rec.size());
     const size_t nseg = whole ? 1 : segs.size();
     total += align256(nseg * sizeof(RefSeg));
+    HostCuts hc;
+    if (!periodic && h->n > kCutRows) {
+        const bool ok = tri ? build_cuts<TriRow<double>, TriRow<float>>(SBS_TRI, h->n, bands, FactorTri{},
+                                                                        solve_tri_rows, hc)
+                            : build_cuts<PentaRow<double>, PentaRow<float>>(SBS_PENTA, h->n, bands, FactorPenta{},
+                                                                            solve_penta_rows, hc);
+        if (!ok) hc = HostCuts();
+    }
+    for (const HostCutSeg &s : hc.segs) total += align256(s.b64.size()) + align256(s.b32.size());
+    for (const HostCutWin &w : hc.wins) total += align256(w.w.size() * 8);
+    total += align256(hc.segs.size() * sizeof(CutSeg)) + align256(hc.wins.size() * sizeof(CutWin));
     if (total == 0) return SBS_OK;
     void *dev = nullptr;
     if (hipMalloc(&dev, total) != hipSuccess) return SBS_ERR_NO_MEMORY;
@@ -969,6 +1150,57 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
             h->segP = std::max(h->segP, (int)s.P);
             h->segNr = std::max(h->segNr, (int)s.Nr);
         }
+    }
+    if (!hc.segs.empty()) {
+        const int bw = h->kind / 2;
+        const int64_t n = h->n;
+        std::vector<CutSeg> cs;
+        std::vector<CutWin> cw;
+        for (const HostCutSeg &s : hc.segs) {
+            CutSeg t{};
+            if (s.same >= 0) {
+                t = cs[s.same];
+            } else {
+                t.blob[0] = put(s.b64.data(), s.b64.size());
+                t.blob[1] = put(s.b32.data(), s.b32.size());
+                t.fac[0] = (int32_t)s.sp.fac_bytes64, t.fac[1] = (int32_t)s.sp.fac_bytes32;
+                t.spk[0] = (int32_t)s.sp.spk_bytes64, t.spk[1] = (int32_t)s.sp.spk_bytes32;
+                t.scf[0] = (int32_t)s.sp.scf_bytes64, t.scf[1] = (int32_t)s.sp.scf_bytes32;
+                t.sinv[0] = (int32_t)s.sp.sinv_bytes64, t.sinv[1] = (int32_t)s.sp.sinv_bytes32;
+                t.map = (int32_t)s.sp.map_bytes;
+                t.P = s.sp.P;
+                t.Nr = s.sp.Nr;
+                t.kofs = s.sp.kofs;
+                t.kw = s.sp.kw;
+                h->cut.P = std::max(h->cut.P, s.sp.P);
+                h->cut.Nr = std::max(h->cut.Nr, s.sp.Nr);
+                for (int tc = 0; tc < 2; ++tc)
+                    h->cut.blob_bytes[tc] = std::max(h->cut.blob_bytes[tc], s.sp.blob_bytes(tc));
+            }
+            t.row0 = (int32_t)s.a;
+            t.rows = (int32_t)(s.b - s.a);
+            t.has_lo = s.a > 0;
+            t.has_hi = s.b < n;
+            for (int r = 0; r < 2; ++r)
+                for (int c = 0; c < 2; ++c) {
+                    t.lo[r][c] = t.hi[r][c] = 0.0;
+                    if (r >= bw || c >= bw) continue;
+                    if (t.has_lo && c >= r && r < t.rows) t.lo[r][c] = bands[(int64_t)(c - r) * n + s.a + r];
+                    if (t.has_hi && c <= r) t.hi[r][c] = bands[(int64_t)(2 * bw + c - r) * n + s.b - bw + r];
+                }
+            cs.push_back(t);
+        }
+        for (const HostCutWin &w : hc.wins) {
+            CutWin t{};
+            t.w = w.same >= 0 ? cw[w.same].w : reinterpret_cast<const double *>(put(w.w.data(), w.w.size() * 8));
+            t.row = (int32_t)w.row;
+            t.first = (int32_t)w.first;
+            t.len = w.len;
+            cw.push_back(t);
+        }
+        h->cut.segs = reinterpret_cast<const CutSeg *>(put(cs.data(), cs.size() * sizeof(CutSeg)));
+        h->cut.wins = reinterpret_cast<const CutWin *>(put(cw.data(), cw.size() * sizeof(CutWin)));
+        h->cut.Q = (int)cs.size();
     }
     if (hipMemcpy(dev, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) return SBS_ERR_DEVICE;
     h->device_bytes += (int64_t)total;

@@ -33,8 +33,11 @@
 namespace sbs {
 namespace {
 
-typedef double D2 __attribute__((ext_vector_type(2)));
-typedef float F2 __attribute__((ext_vector_type(2)));
+// (a pair is one 16- or 8-byte access wherever it starts: rows of an odd
+// number of systems start at odd elements, and global accesses of gfx950 need
+// the alignment of a 4-byte word only)
+typedef double D2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef float F2 __attribute__((ext_vector_type(2), aligned(4)));
 typedef double D4 __attribute__((ext_vector_type(4)));
 
 template <int KIND, typename T>
@@ -110,7 +113,14 @@ struct SepArgs {
     int steps;     // Crank-Nicolson steps to run (1 for a solve)
     int64_t m;
     BandCoef coef;  // Crank-Nicolson steps: the matrix's constant band values
+    const CutSeg *segs;  // the cut form: Q segments
+    int Q;
 };
+
+// Device memory that does not change while a kernel runs: uniform reads
+// become scalar loads.
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T *;
 
 // Z = S^{-1} Yhat for the group on the matrix cores (Yhat = redl + redr, the
 // two parts of the separator right-hand sides): 16 x 16 output tiles of
@@ -364,13 +374,50 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // call asks for, and a step costs its arithmetic and barriers only.
 // (Hyperdiffusion n = 1024, m = 65536, 8 steps per call: 686 us, with one
 // launch and one pass over HBM per step 1827 us.)
-template <int KIND, typename T, int LB, int VEC, int MAXT, bool GF, bool CN = false>
+//
+// SEG: the cut form.  Workgroup b solves segment b % Q of the matrix as one of
+// its own (its plan, its rows), after k_cut_rows has put the unknowns of the
+// cut rows into the array: the segment's first and last H right-hand sides
+// lose their couplings to them.  A segment of 256 rows leaves room for 128
+// systems per workgroup, whatever n is.  Segments with fewer blocks than the launch has lanes for
+// run their last block more than once (the same values to the same places).
+// m may be odd: a lane at or past the last system takes the last two and
+// stores the last one only, since the other may be another workgroup's.
+template <int KIND, typename T, int LB, int VEC, int MAXT, bool GF, bool CN = false, bool SEG = false>
 __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ blob, SepArgs a, const T *in,
                                               T *out) {
     using Row = typename RowOf<KIND, T>::type;
     constexpr int H = KIND / 2, NB = 2 * H + 1, NI = LB - H;
     constexpr bool MMA = sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char lds[];
+    bool cut_lo = false, cut_hi = false;
+    T clo[H][H], chi[H][H];
+    if constexpr (SEG) {
+        constexpr int tc = sizeof(T) == 8 ? 0 : 1;
+        const cptr<CutSeg> s = (cptr<CutSeg>)(a.segs + blockIdx.x % a.Q);
+        blob = s->blob[tc];
+        a.fac_bytes = s->fac[tc];
+        a.spk_bytes = s->spk[tc];
+        a.scf_bytes = s->scf[tc];
+        a.sinv_bytes = s->sinv[tc];
+        a.map_bytes = s->map;
+        a.n = s->rows;
+        a.P = s->P;
+        a.Nr = s->Nr;
+        a.kofs = s->kofs;
+        a.kw = s->kw;
+        in += (int64_t)s->row0 * a.m;
+        out += (int64_t)s->row0 * a.m;
+        cut_lo = s->has_lo != 0;
+        cut_hi = s->has_hi != 0;
+#pragma unroll
+        for (int t = 0; t < H; ++t)
+#pragma unroll
+            for (int c = 0; c < H; ++c) {
+                clo[t][c] = (T)s->lo[t][c];
+                chi[t][c] = (T)s->hi[t][c];
+            }
+    }
     const int P = a.P, Nr = a.Nr, S = a.S, n = a.n;
     const int blob_bytes = a.fac_bytes + a.spk_bytes + a.scf_bytes + a.sinv_bytes + a.map_bytes;
     const int sinv_at = a.fac_bytes + a.spk_bytes + a.scf_bytes;
@@ -403,23 +450,36 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 
 
     const int Ls = S / VEC;  // lanes per block row
-    const int l = threadIdx.x, p = l / Ls, sl = l - p * Ls;
+    const int l = threadIdx.x, p0 = l / Ls, sl = l - p0 * Ls;
+    const int p = SEG ? min(p0, P - 1) : p0;
     const int r0 = p * LB;
     const bool has_sep = a.periodic || p < P - 1, has_prev = a.periodic || p > 0;
     const int pp = p == 0 ? P - 1 : p - 1;
     const int s0 = sl * VEC;  // the lane's first system within the group
     const int64_t m = a.m;
     const bool full = r0 + LB <= n;
-    const int grid = gridDim.x;
-    int b = blockIdx.x;
+    const int grid = SEG ? gridDim.x / a.Q : gridDim.x;
+    int b = SEG ? blockIdx.x / a.Q : blockIdx.x;
     if ((a.flags & 1) && grid % 8 == 0) b = (b % 8) * (grid / 8) + b / 8;
 
     T x[LB][VEC];
     // lanes past the last system take the last VEC systems: same values, same
     // addresses, so their duplicate stores are harmless
     auto col = [&](int g) { return min((int64_t)g * S + s0, m - VEC); };
+    auto last_only = [&](int g) { return SEG && VEC == 2 && (int64_t)g * S + s0 > m - VEC; };
+    // SEG: the unknowns of the cut rows beside the lane's block (only a last
+    // segment may be a single block, and it has none after it)
+    const bool at_lo = SEG && cut_lo && p == 0, at_hi = SEG && cut_hi && p == P - 1;
+    T beside[H][VEC];
     auto load_group = [&](int g) {
         const T *src = in + (int64_t)r0 * m + col(g);
+        if constexpr (SEG) {
+            if (at_lo || at_hi) {
+                const T *q = at_lo ? src - (int64_t)H * m : src + (int64_t)LB * m;
+#pragma unroll
+                for (int c = 0; c < H; ++c) load_vec<T, VEC>(q + (int64_t)c * m, beside[c]);
+            }
+        }
         if (full) {
 #pragma unroll
             for (int t = 0; t < LB; ++t) load_vec<T, VEC>(src + (int64_t)t * m, x[t]);
@@ -480,6 +540,24 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             const Row *fr = fr0;
             const T *sp = sp0;
             if constexpr (GF) asm volatile("" : "+v"(fr), "+v"(sp));
+
+            if constexpr (SEG) {
+                if (at_lo) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v)
+#pragma unroll
+                        for (int t = 0; t < H; ++t)
+#pragma unroll
+                            for (int c = t; c < H; ++c) x[t][v] = fma(-clo[t][c], beside[c][v], x[t][v]);
+                } else if (at_hi) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v)
+#pragma unroll
+                        for (int t = 0; t < H; ++t)
+#pragma unroll
+                            for (int c = 0; c <= t; ++c) x[NI + t][v] = fma(-chi[t][c], beside[c][v], x[NI + t][v]);
+                }
+            }
 
             // 1. block sweeps (Section 3.1 / 4.1 recurrences, block factor);
             // each group of G rows reads its coefficients while the previous
@@ -582,6 +660,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             }
             // 4. correction and stores
             T *dst = out + (int64_t)r0 * m + col(g);
+            const bool one = last_only(g);
             // the spikes of GC rows per round trip; from global memory (GF) the
             // next rows' spikes are loaded before the current rows are stored,
             // since a load issued after a store waits for that store
@@ -627,7 +706,10 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                             asm volatile("" : "+v"(x[t][v]));
                         }
                     } else if (full || r0 + t < n) {
-                        store_vec_nt<T, VEC>(dst + (int64_t)t * m, v2);
+                        if (SEG && one)
+                            __builtin_nontemporal_store(v2[VEC - 1], dst + (int64_t)t * m + VEC - 1);
+                        else
+                            store_vec_nt<T, VEC>(dst + (int64_t)t * m, v2);
                     }
                 }
                 pin(zr[0][0]);
@@ -693,6 +775,76 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     }
 }
 
+// The unknowns of the cut rows (the cut form's first kernel): for every cut and
+// system, H rows of A^{-1} near the cut times the right-hand sides there, into
+// the cut's rows.  A workgroup takes one cut and 64 * VEC systems; its four
+// waves take a quarter of the window's rows each and add up in LDS (fixed
+// order), so that the loads of a system, all independent, are in flight over
+// four waves.  Reads what it needs of the right-hand sides once more than the
+// solve does: 2 * 37 rows in 258 for the s = 0.5 hyperdiffusion matrix.  The
+// sums are FP64 whatever T is; the window of a cut holds no other cut's rows.
+constexpr int kCutWaves = 4;
+
+template <int H, typename T, int VEC>
+__global__ __launch_bounds__(64 * kCutWaves) void k_cut_rows(const CutWin *__restrict__ wins, int ncuts, T *x,
+                                                             int64_t m) {
+    const int lane = threadIdx.x % kWave, part = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const cptr<CutWin> win = (cptr<CutWin>)(wins + blockIdx.x % ncuts);
+    const int64_t j0 = ((int64_t)(blockIdx.x / ncuts) * kWave + lane) * VEC, j = min(j0, m - VEC);
+    const int per = (win->len + kCutWaves - 1) / kCutWaves;
+    const int i0 = part * per, i1 = min(i0 + per, win->len);
+    const cptr<double> w = (cptr<double>)win->w;
+    const T *src = x + (int64_t)win->first * m + j;
+    double z[H][VEC];
+#pragma unroll
+    for (int c = 0; c < H; ++c)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) z[c][v] = 0.0;
+    constexpr int U = 8;
+    int i = i0;
+    for (; i + U <= i1; i += U) {
+        T f[U][VEC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_vec<T, VEC>(src + (int64_t)(i + u) * m, f[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < H; ++c)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) z[c][v] = fma(w[(i + u) * H + c], (double)f[u][v], z[c][v]);
+    }
+    for (; i < i1; ++i) {
+        T f[VEC];
+        load_vec<T, VEC>(src + (int64_t)i * m, f);
+#pragma unroll
+        for (int c = 0; c < H; ++c)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) z[c][v] = fma(w[i * H + c], (double)f[v], z[c][v]);
+    }
+    // every wave has read its rows (the cut's own among them) before any is written
+    __shared__ double sum[kCutWaves][H][VEC][kWave];
+#pragma unroll
+    for (int c = 0; c < H; ++c)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) sum[part][c][v][lane] = z[c][v];
+    __syncthreads();
+    if (part >= H) return;
+    T r[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        double t = sum[0][part][v][lane];
+#pragma unroll
+        for (int q = 1; q < kCutWaves; ++q) t += sum[q][part][v][lane];
+        r[v] = (T)t;
+    }
+    T *dst = x + (int64_t)(win->row + part) * m + j;
+    // past the last pair: the last system only (see k_sep)
+    if (VEC == 1 || j0 > m - VEC)
+        dst[VEC - 1] = r[VEC - 1];
+    else
+        *reinterpret_cast<typename Pair<T>::type *>(dst) = typename Pair<T>::type{r[0], r[VEC - 1]};
+}
+
 // ---------------------------------------------------------------------------
 // Launch side.
 
@@ -704,9 +856,9 @@ constexpr int sep_maxt() {
     return LB * VEC * (int)sizeof(T) / 4 <= 64 ? 1024 : 512;
 }
 
-template <int KIND, typename T, int LB, int VEC, bool GF, bool CN = false>
+template <int KIND, typename T, int LB, int VEC, bool GF, bool CN = false, bool SEG = false>
 hipError_t sep_kernel(const void **fn) {
-    auto kern = k_sep<KIND, T, LB, VEC, sep_maxt<T, LB, VEC>(), GF, CN>;
+    auto kern = k_sep<KIND, T, LB, VEC, sep_maxt<T, LB, VEC>(), GF, CN, SEG>;
     // once per instantiation; thread-safe static initialisation, so that
     // concurrent first launches from several host threads do not race
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -856,6 +1008,97 @@ bool sep_shape(const sbs_lhs *h, int tc, int64_t m, const void *x, int lb, int v
     for (int q = 0; q < 3; ++q)
         if (kPartLbs[q] == lb) return sep_fit(h, tc, m, x, q, vec, S, flags, out);
     return false;
+}
+
+namespace {
+
+// The cut form's kernel: 32-row blocks, two systems per lane.
+constexpr int kCutVec = 2;
+
+template <int KIND, typename T>
+hipError_t cut_kernel(const void **fn, int *maxt) {
+    *maxt = sep_maxt<T, kSegLb, kCutVec>();
+    return sep_kernel<KIND, T, kSegLb, kCutVec, false, false, true>(fn);
+}
+
+hipError_t cut_fn(int kind, int tc, const void **fn, int *maxt) {
+    if (kind == SBS_TRI) return tc == 0 ? cut_kernel<SBS_TRI, double>(fn, maxt) : cut_kernel<SBS_TRI, float>(fn, maxt);
+    return tc == 0 ? cut_kernel<SBS_PENTA, double>(fn, maxt) : cut_kernel<SBS_PENTA, float>(fn, maxt);
+}
+
+template <int H, typename T>
+hipError_t go_cut_rows(const CutPlan &cp, T *x, int64_t m, hipStream_t s) {
+    const int64_t groups = (m + kWave * kCutVec - 1) / (kWave * kCutVec);
+    if (groups * (cp.Q - 1) > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_cut_rows<H, T, kCutVec>), dim3((unsigned)(groups * (cp.Q - 1))), dim3(kWave * kCutWaves), 0,
+                       s, cp.wins, cp.Q - 1, x, m);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t cut_rows(const sbs_lhs *h, T *x, int64_t m, hipStream_t s) {
+    return h->kind == SBS_TRI ? go_cut_rows<1, T>(h->cut, x, m, s) : go_cut_rows<2, T>(h->cut, x, m, s);
+}
+
+}  // namespace
+
+// 128 systems per workgroup, one block per wave, so that every access of a wave
+// is one run (1 KiB in FP64), if every CU then has a workgroup; else fewer
+// (down to 64 bytes a run) until it has, or the workgroup is no longer whole
+// waves.  Long runs are worth more than less reading by the windows or a
+// second workgroup per CU: penta n = 1024, m = 65536 with segments of 256 rows
+// and 128 systems 232 us, 256 rows and 64 systems (two workgroups) 255 us, 512
+// rows and 64 systems 235 us, 32 systems 257 us; tri n = 1024 226, 249, 235
+// and 257 us; FP32 tri n = 2000, m = 50001 218, 234, 311 us.
+bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out) {
+    const CutPlan &cp = h->cut;
+    if (cp.Q < 2 || m < kCutVec) return false;
+    const size_t elem = tc == 0 ? 8 : 4;
+    const void *fn = nullptr;
+    int maxt = 0;
+    if (cut_fn(h->kind, tc, &fn, &maxt) != hipSuccess) return false;
+    const int cus = cu_count(h->device);
+    CutChoice best;
+    for (int S = kWave * kCutVec; S * (int)elem >= 64; S /= 2) {
+        CutChoice c;
+        c.S = S;
+        c.threads = S / kCutVec * cp.P;
+        const size_t red = tc == 0 ? sep_red_bytes<double>(S, cp.Nr) : sep_red_bytes<float>(S, cp.Nr);
+        c.lds = cp.blob_bytes[tc] + red * (tc == 0 ? 3 : 2);
+        if (c.threads > maxt || c.lds > kMaxPartLdsBytes) continue;
+        if (best.S && c.threads % kWave) break;
+        if ((c.wgs = occupancy(fn, c.threads, c.lds)) < 1) continue;
+        best = c;
+        if ((m + S - 1) / S * cp.Q >= cus) break;
+    }
+    if (!best.S) return false;
+    *out = best;
+    return true;
+}
+
+hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, hipStream_t s) {
+    if (m <= 0) return hipSuccess;
+    const CutPlan &cp = h->cut;
+    const void *fn = nullptr;
+    int maxt = 0;
+    if (hipError_t e = cut_fn(h->kind, tc, &fn, &maxt); e != hipSuccess) return e;
+    const int64_t ngroups = (m + c.S - 1) / c.S;
+    if (c.threads > maxt || ngroups * cp.Q > 0x7fffffff) return hipErrorInvalidValue;
+    const hipError_t e =
+        tc == 0 ? cut_rows(h, static_cast<double *>(x), m, s) : cut_rows(h, static_cast<float *>(x), m, s);
+    if (e != hipSuccess) return e;
+    SepArgs a{};
+    a.S = c.S;
+    a.ngroups = (int)ngroups;
+    a.steps = 1;
+    a.m = m;
+    a.segs = cp.segs;
+    a.Q = cp.Q;
+    const int64_t per_seg =
+        std::max<int64_t>(1, std::min<int64_t>(ngroups, (int64_t)cu_count(h->device) * c.wgs / cp.Q));
+    const unsigned char *blob = nullptr;
+    void *args[] = {&blob, &a, &x, &x};
+    return hipLaunchKernel(fn, dim3((unsigned)(per_seg * cp.Q)), dim3(c.threads), args, c.lds, s);
 }
 
 hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t s, int steps) {
