@@ -507,21 +507,26 @@ sbs_status sbs_cn_step(sbs_handle h, void *c, int64_t m, int32_t dtype, int32_t 
     if (m > (int64_t)0x7fffffff * kWave) return SBS_ERR_INVALID_ARG;
     const int t = dtype == SBS_F64 ? 0 : 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // pentadiagonal, constant bands and a separator shape that fills every CU
-    // with whole row runs: the separator kernel's step (coefficients by
-    // value).  Hyperdiffusion n = 1024, m = 65536: 234.4 us against 246.2 us
+    const int cn = h->constant_bands ? 2 : 1;  // constant bands: coefficients by value, no band rows in LDS
+    SepChoice sc;
+    if (steps > 1 && choose_sep_steps(h, t, m, c, cn, &sc))
+        return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    // One step: pentadiagonal, constant bands and a separator shape that fills
+    // every CU with whole row runs: the separator kernel's step (coefficients
+    // by value).  Hyperdiffusion n = 1024, m = 65536: 234.4 us against 246.2 us
     // in the pair form; for tridiagonal matrices the pair form's step is the
     // faster (periodic diffusion, same size: 221.6 us against 233.5 us).
     if (h->constant_bands && h->kind == SBS_PENTA) {
-        SepChoice sc;
-        if (choose_sep(h, t, m, c, &sc, true) && sep_fills(h, t, m, sc)) {
+        if (choose_sep(h, t, m, c, &sc, 2) && sep_fills(h, t, m, sc))
             return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
-        }
     }
     PartChoice pc;
-    const int cn = h->constant_bands ? 2 : 1;  // constant bands: coefficients by value, no band rows in LDS
     if (choose_partition(h, t, m, &pc, cn))
         return launch_partition(h, pc, t, t, t, c, c, m, s, cn, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    // no pair plan that fits: the separator form (pentadiagonal n = 1000 with
+    // varying bands, m = 3000: 14 us a step against 128 us), else the sweeps
+    if (choose_sep_steps(h, t, m, c, cn, &sc))
+        return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     for (int k = 0; k < steps; ++k)
         if (launch_cn(h, t, c, m, s) != hipSuccess) return SBS_ERR_DEVICE;
     return SBS_OK;

@@ -113,6 +113,7 @@ struct SepArgs {
     int steps;     // Crank-Nicolson steps to run (1 for a solve)
     int64_t m;
     BandCoef coef;  // Crank-Nicolson steps: the matrix's constant band values
+    const BandRow *bands;  // or its band rows
     const CutSeg *segs;  // the cut form: Q segments
     int Q;
 };
@@ -361,10 +362,11 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // are stored after all of them are computed (a spike load issued after a
 // store would wait for that store).
 //
-// CN: a.steps Crank-Nicolson steps c <- A^{-1} (2I - A) c (Sections 3.2, 4.2)
-// of a matrix whose bands are constant (the values in a.coef): with
-// u = A^{-1} c in registers, row t of the output is
-// 2 u_t - sum_e coef_e u_{t-H+e}.  The rows
+// CN: a.steps Crank-Nicolson steps c <- A^{-1} (2I - A) c (Sections 3.2, 4.2):
+// with u = A^{-1} c in registers, row t of the output is
+// 2 u_t - sum_e coef_e u_{t-H+e}, with the row's own coefficients (CN 1: the
+// band rows a.bands, staged in LDS) or those of a matrix whose bands are
+// constant (CN 2: the values in a.coef).  The rows
 // above the block are the previous block's separators (known to the lane);
 // the first H rows of the next block come through LDS, one more barrier.
 // Values outside the matrix are 0, so the constant coefficients also give
@@ -372,18 +374,20 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // workgroup, so every step but the last leaves its rows in the registers
 // for the next one: HBM is crossed once in and once out however many steps a
 // call asks for, and a step costs its arithmetic and barriers only.
-// (Hyperdiffusion n = 1024, m = 65536, 8 steps per call: 686 us, with one
-// launch and one pass over HBM per step 1827 us.)
+// (Hyperdiffusion n = 1024, m = 65536, 8 steps per call: 597 us, with one
+// launch and one pass over HBM per step 1827 us; periodic diffusion n = 512,
+// m = 6000, 20 steps: 89 us against 332 us.)  The rows are stored after the
+// last step, not as they are formed: with the pairs of an odd batch as a
+// branch in the output loop 66 registers spilled.
 //
 // SEG: the cut form.  Workgroup b solves segment b % Q of the matrix as one of
 // its own (its plan, its rows), after k_cut_rows has put the unknowns of the
 // cut rows into the array: the segment's first and last H right-hand sides
 // lose their couplings to them.  A segment of 256 rows leaves room for 128
-// systems per workgroup, whatever n is.  Segments with fewer blocks than the launch has lanes for
-// run their last block more than once (the same values to the same places).
+// systems per workgroup, whatever n is.
 // m may be odd: a lane at or past the last system takes the last two and
 // stores the last one only, since the other may be another workgroup's.
-template <int KIND, typename T, int LB, int VEC, int MAXT, bool GF, bool CN = false, bool SEG = false>
+template <int KIND, typename T, int LB, int VEC, int MAXT, bool GF, int CN = 0, bool SEG = false>
 __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ blob, SepArgs a, const T *in,
                                               T *out) {
     using Row = typename RowOf<KIND, T>::type;
@@ -447,11 +451,21 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     T *lz = alias ? lredl : reinterpret_cast<T *>(lds + plan_lds + 2 * sep_red_bytes<T>(S, Nr));
     // CN: the first H rows of every block of the group, [S][P][H]
     T *ltop = reinterpret_cast<T *>(lds + plan_lds + (alias ? 2 : 3) * sep_red_bytes<T>(S, Nr));
+    // CN 1: the band rows, [P * LB][NB], 0 outside the matrix
+    T *lband = reinterpret_cast<T *>(reinterpret_cast<unsigned char *>(ltop) + align16(S * P * H * (int)sizeof(T)));
+    if constexpr (CN == 1) {
+        for (int i = threadIdx.x; i < P * LB; i += blockDim.x)
+#pragma unroll
+            for (int e = 0; e < NB; ++e) lband[i * NB + e] = i < n ? (T)a.bands[i].c[e] : T(0);
+    }
 
 
     const int Ls = S / VEC;  // lanes per block row
     const int l = threadIdx.x, p0 = l / Ls, sl = l - p0 * Ls;
-    const int p = SEG ? min(p0, P - 1) : p0;
+    // lanes past the last block (the workgroup is whole waves, and a segment of
+    // the cut form may have fewer blocks than the launch has lanes for) run it
+    // once more: the same values to the same places
+    const int p = min(p0, P - 1);
     const int r0 = p * LB;
     const bool has_sep = a.periodic || p < P - 1, has_prev = a.periodic || p > 0;
     const int pp = p == 0 ? P - 1 : p - 1;
@@ -466,7 +480,9 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     // lanes past the last system take the last VEC systems: same values, same
     // addresses, so their duplicate stores are harmless
     auto col = [&](int g) { return min((int64_t)g * S + s0, m - VEC); };
-    auto last_only = [&](int g) { return SEG && VEC == 2 && (int64_t)g * S + s0 > m - VEC; };
+    // (an odd batch: the cut form and Crank-Nicolson steps take pairs all the same)
+    constexpr bool ANYM = (SEG || CN) && VEC == 2;
+    auto last_only = [&](int g) { return ANYM && (int64_t)g * S + s0 > m - VEC; };
     // SEG: the unknowns of the cut rows beside the lane's block (only a last
     // segment may be a single block, and it has none after it)
     const bool at_lo = SEG && cut_lo && p == 0, at_hi = SEG && cut_hi && p == P - 1;
@@ -706,7 +722,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                             asm volatile("" : "+v"(x[t][v]));
                         }
                     } else if (full || r0 + t < n) {
-                        if (SEG && one)
+                        if (ANYM && one)
                             __builtin_nontemporal_store(v2[VEC - 1], dst + (int64_t)t * m + VEC - 1);
                         else
                             store_vec_nt<T, VEC>(dst + (int64_t)t * m, v2);
@@ -733,10 +749,6 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                     }
                 // rows above the block: the previous block's separators (0 above
                 // the first block of a matrix that does not wrap round)
-                const T c0 = (T)a.coef.c[0];
-                // one store pointer stepped row by row (opaque, so that the
-                // rows' addresses are not all formed up front and kept live)
-                T *q = dst;
                 T up[H][VEC];  // the H rows above row t, before their own update
 #pragma unroll
                 for (int c = 0; c < H; ++c)
@@ -744,6 +756,9 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                     for (int v = 0; v < VEC; ++v) up[c][v] = zl[c][v];
 #pragma unroll
                 for (int t = 0; t < LB; ++t) {
+                    T cb[NB];
+#pragma unroll
+                    for (int e = 0; e < NB; ++e) cb[e] = CN == 1 ? lband[(r0 + t) * NB + e] : (T)a.coef.c[e];
                     T v2[VEC];
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) {
@@ -752,23 +767,34 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                         for (int e = 0; e < NB; ++e) {
                             const int i = t - H + e;
                             const T u = e < H ? up[e][v] : (i >= LB ? dn[i - LB][v] : x[i][v]);
-                            ax = e == 0 ? c0 * u : fma((T)a.coef.c[e], u, ax);
+                            ax = e == 0 ? cb[0] * u : fma(cb[e], u, ax);
                         }
                         v2[v] = T(2) * x[t][v] - ax;
 #pragma unroll
                         for (int c = 0; c < H; ++c) up[c][v] = c + 1 < H ? up[c + 1][v] : x[t][v];
                     }
-                    if (step > 1) {
-                        // rows past the matrix stay 0
+                    // rows past the matrix stay 0
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < n ? v2[v] : T(0);
-                    } else {
-                        if (full || r0 + t < n) store_vec_nt<T, VEC>(q, v2);
-                        q += m;
-                        asm volatile("" : "+v"(q));
-                    }
+                    for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < n ? v2[v] : T(0);
                     if (t % G == G - 1) pin(v2[0]);
                 }
+            }
+        }
+        if constexpr (CN) {
+            // one store pointer stepped row by row (opaque, so that the rows'
+            // addresses are not all formed up front and kept live)
+            T *q = out + (int64_t)r0 * m + col(g);
+            const bool one = last_only(g);
+#pragma unroll
+            for (int t = 0; t < LB; ++t) {
+                if (full || r0 + t < n) {
+                    if (ANYM && one)
+                        __builtin_nontemporal_store(x[t][VEC - 1], q + VEC - 1);
+                    else
+                        store_vec_nt<T, VEC>(q, x[t]);
+                }
+                q += m;
+                asm volatile("" : "+v"(q));
             }
         }
         if (g + grid < a.ngroups) load_group(g + grid);
@@ -856,7 +882,7 @@ constexpr int sep_maxt() {
     return LB * VEC * (int)sizeof(T) / 4 <= 64 ? 1024 : 512;
 }
 
-template <int KIND, typename T, int LB, int VEC, bool GF, bool CN = false, bool SEG = false>
+template <int KIND, typename T, int LB, int VEC, bool GF, int CN = 0, bool SEG = false>
 hipError_t sep_kernel(const void **fn) {
     auto kern = k_sep<KIND, T, LB, VEC, sep_maxt<T, LB, VEC>(), GF, CN, SEG>;
     // once per instantiation; thread-safe static initialisation, so that
@@ -871,19 +897,21 @@ hipError_t sep_kernel(const void **fn) {
 
 // The shapes built: (LB, VEC) with at most 128 registers of values per lane;
 // with the plan in global memory (GF) the two longest, (32, 2) and (64, 1);
-// Crank-Nicolson steps of pentadiagonal matrices (plan in LDS) (32, 1),
-// (32, 2) and (64, 1).
+// Crank-Nicolson steps (plan in LDS) (16, 1), (32, 1), (32, 2) and (64, 1).
+template <int KIND, typename T, int CN>
+hipError_t sep_kernel_cn(int lb, int vec, const void **fn, int *maxt) {
+    if (lb == 16 && vec == 1) return *maxt = sep_maxt<T, 16, 1>(), sep_kernel<KIND, T, 16, 1, false, CN>(fn);
+    if (lb == 32 && vec == 1) return *maxt = sep_maxt<T, 32, 1>(), sep_kernel<KIND, T, 32, 1, false, CN>(fn);
+    if (lb == 32 && vec == 2) return *maxt = sep_maxt<T, 32, 2>(), sep_kernel<KIND, T, 32, 2, false, CN>(fn);
+    if (lb == 64 && vec == 1) return *maxt = sep_maxt<T, 64, 1>(), sep_kernel<KIND, T, 64, 1, false, CN>(fn);
+    return hipErrorInvalidValue;
+}
+
 template <int KIND, typename T>
-hipError_t sep_kernel_of(int lb, int vec, bool gf, bool cn, const void **fn, int *maxt) {
-    if (cn) {
-        if constexpr (KIND == SBS_PENTA) {
-            if (gf) return hipErrorInvalidValue;
-            if (lb == 32 && vec == 1) return *maxt = sep_maxt<T, 32, 1>(), sep_kernel<KIND, T, 32, 1, false, true>(fn);
-            if (lb == 32 && vec == 2) return *maxt = sep_maxt<T, 32, 2>(), sep_kernel<KIND, T, 32, 2, false, true>(fn);
-            if (lb == 64 && vec == 1) return *maxt = sep_maxt<T, 64, 1>(), sep_kernel<KIND, T, 64, 1, false, true>(fn);
-        }
-        return hipErrorInvalidValue;
-    }
+hipError_t sep_kernel_of(int lb, int vec, bool gf, int cn, const void **fn, int *maxt) {
+    if (cn && gf) return hipErrorInvalidValue;
+    if (cn == 1) return sep_kernel_cn<KIND, T, 1>(lb, vec, fn, maxt);
+    if (cn == 2) return sep_kernel_cn<KIND, T, 2>(lb, vec, fn, maxt);
     if (gf) {
         if (lb == 32 && vec == 2) return *maxt = sep_maxt<T, 32, 2>(), sep_kernel<KIND, T, 32, 2, true>(fn);
         if (lb == 64 && vec == 1) return *maxt = sep_maxt<T, 64, 1>(), sep_kernel<KIND, T, 64, 1, true>(fn);
@@ -899,7 +927,7 @@ hipError_t sep_kernel_of(int lb, int vec, bool gf, bool cn, const void **fn, int
     return hipErrorInvalidValue;
 }
 
-hipError_t sep_fn(int kind, int tc, int lb, int vec, bool gf, bool cn, const void **fn, int *maxt) {
+hipError_t sep_fn(int kind, int tc, int lb, int vec, bool gf, int cn, const void **fn, int *maxt) {
     const int k = kind == SBS_PENTA ? SBS_PENTA : SBS_TRI;  // periodic blocks are plain tridiagonal
     if (k == SBS_TRI)
         return tc == 0 ? sep_kernel_of<SBS_TRI, double>(lb, vec, gf, cn, fn, maxt)
@@ -911,13 +939,15 @@ hipError_t sep_fn(int kind, int tc, int lb, int vec, bool gf, bool cn, const voi
 // LDS of one workgroup: the plan (GF: S^{-1} only), the two parts of the
 // separator right-hand sides and (FP64: the matrix-core product's output)
 // the separators, unless `alias` puts them in redL's storage; Crank-Nicolson
-// steps add the blocks' first rows after a third buffer.
-// (cn_h: the half band width H of a Crank-Nicolson step, 0 for a solve)
-size_t sep_lds(const SepPlan &sp, int tc, int S, bool gf, bool alias, int cn_h = 0) {
+// steps add the blocks' first rows after a third buffer, and the band rows
+// (cn 1).  H: the half band width, for those.
+size_t sep_lds(const SepPlan &sp, int tc, int S, bool gf, bool alias, int cn = 0, int H = 0) {
     const size_t elem = tc == 0 ? 8 : 4;
     const size_t red = tc == 0 ? sep_red_bytes<double>(S, sp.Nr) : sep_red_bytes<float>(S, sp.Nr);
     const size_t plan = gf ? (tc == 0 ? sp.sinv_bytes64 : sp.sinv_bytes32) : sp.blob_bytes(tc);
-    if (cn_h) return plan + 3 * red + ((size_t)S * sp.P * cn_h * elem + 15) / 16 * 16;
+    if (cn)
+        return plan + 3 * red + ((size_t)S * sp.P * H * elem + 15) / 16 * 16 +
+               (cn == 1 ? (size_t)sp.P * sp.lb * (2 * H + 1) * elem : 0);
     return plan + red * (tc == 0 && !alias ? 3 : 2);
 }
 
@@ -929,27 +959,30 @@ int cu_count(int device) { return device_cus(device); }
 // room for a third FP64 buffer the separators overwrite redL (flags bit 5,
 // which only this function sets).
 //
-// cn: a Crank-Nicolson step of a matrix with constant bands (plan in LDS only).
+// cn: Crank-Nicolson steps with band rows (1) or constant bands (2); plan in
+// LDS only.
 bool sep_fit(const sbs_lhs *h, int tc, int64_t m, const void *x, int q, int vec, int S, int flags, SepChoice *c,
-             bool cn = false) {
+             int cn = 0) {
     const SepPlan &sp = h->sep[q];
     const size_t elem = tc == 0 ? 8 : 4;
     if (!sp.ok || m < vec || S < vec || S % vec) return false;
-    if (vec == 2 && (m % 2 || reinterpret_cast<uintptr_t>(x) % (2 * elem))) return false;
+    if (vec == 2 && !cn && (m % 2 || reinterpret_cast<uintptr_t>(x) % (2 * elem))) return false;
     flags &= ~32;
     bool gf = (flags & 16) != 0, alias = false;
     if (cn && gf) return false;
     if (!cn && !gf && sep_lds(sp, tc, S, false, false) > kMaxPartLdsBytes) gf = true;
     if (!cn && gf && sep_lds(sp, tc, S, true, false) > kMaxPartLdsBytes) alias = tc == 0;
-    const size_t lds = sep_lds(sp, tc, S, gf, alias, cn ? h->kind / 2 : 0);
+    const size_t lds = sep_lds(sp, tc, S, gf, alias, cn, h->kind == SBS_PENTA ? 2 : 1);
     if (lds > kMaxPartLdsBytes) return false;
     const void *fn = nullptr;
     int maxt = 0;
     if (sep_fn(h->kind, tc, sp.lb, vec, gf, cn, &fn, &maxt) != hipSuccess) return false;
-    const int threads = (S / vec) * sp.P;
+    // whole waves, so that the matrix cores can form the separators (pentadiagonal
+    // n = 544, m = 16384, 272 lanes: per-lane dot products took 63 us)
+    const int lanes = (S / vec) * sp.P, threads = (lanes + kWave - 1) / kWave * kWave;
     if (threads > maxt) return false;
     // the separators in redL: one matrix-core tile per wave
-    if (alias && (threads % kWave || ((sp.Nr + 15) / 16) * ((S + 15) / 16) > threads / kWave)) return false;
+    if (alias && (lanes % kWave || ((sp.Nr + 15) / 16) * ((S + 15) / 16) > threads / kWave)) return false;
     int wgs = 0;
     if ((wgs = occupancy(fn, threads, lds)) < 1) return false;
     c->plan = q;
@@ -969,7 +1002,7 @@ bool sep_fit(const sbs_lhs *h, int tc, int64_t m, const void *x, int q, int vec,
 // Default launch options: groups in launch order.
 constexpr int kSepDefaultFlags = 0;
 
-bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *out, bool cn) {
+bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *out, int cn) {
     const size_t elem = tc == 0 ? 8 : 4;
     const int cus = cu_count(h->device);
     SepChoice best;
@@ -986,7 +1019,7 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
                 // 8 waves per CU)
                 const int64_t run = std::min<int64_t>((int64_t)S * elem, 256);
                 const int64_t acc = (int64_t)vec * elem;
-                const int64_t lanes = std::min<int64_t>(engaged * c.threads, (int64_t)cus * 8 * kWave);
+                const int64_t lanes = std::min<int64_t>(engaged * (S / vec * h->sep[q].P), (int64_t)cus * 8 * kWave);
                 const int64_t key[5] = {std::min<int64_t>(engaged, cus), c.gf ? 0 : 1, run, acc, lanes};
                 if (std::lexicographical_compare(best_key, best_key + 5, key, key + 5)) {
                     std::copy(key, key + 5, best_key);
@@ -996,6 +1029,57 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
     if (best.plan < 0) return false;
     *out = best;
     return true;
+}
+
+// Several Crank-Nicolson steps run from registers, so the arithmetic, LDS reads
+// and barriers of a step decide, not the row runs.  FP64, up to 4M unknowns:
+// the shortest blocks (the serial chain of a step is two passes over a block),
+// 8 systems per workgroup, 16 where that makes fewer than four waves (8 steps,
+// tridiagonal n = 512, m = 2000: 30 us, 32-row blocks 38 to 42 us, the pair
+// form 50 us; pentadiagonal 36, 49 and 69 us).  More than that: 32-row blocks
+// with two systems per lane, which read each coefficient once for both, in the
+// shape with the most waves resident per CU, 16 systems per workgroup on a tie
+// (two workgroups then hide each other's barriers; tridiagonal n = 1000,
+// m = 60000: 428 us, 32 systems 581 us, 16-row blocks 603 us, the pair form
+// 774 us; pentadiagonal 540, 666, - and 672 us; with band rows in LDS n = 512
+// 401 us at 64 systems, 883 us at 16).  64-row blocks where the separators of
+// shorter ones leave too little LDS (pentadiagonal n = 2000, m = 10000: 298 us,
+// 32-row blocks 700 us, one launch of the sweeps per step 2007 us).  FP32: one
+// system per lane, 32-row blocks up to 8M unknowns, else 64-row ones.
+bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn, SepChoice *out) {
+    const int cus = cu_count(h->device);
+    const int64_t unknowns = h->n * m;
+    auto waves = [](const SepChoice &c) { return c.wgs * (c.threads / kWave); };
+    auto try_shape = [&](int q, int vec, int S, SepChoice *c) { return sep_fit(h, tc, m, x, q, vec, S, 0, c, cn); };
+    // the shape of block length q with the most waves per CU, earlier S on a tie
+    auto most = [&](int q, int vec, std::initializer_list<int> Ss, SepChoice *best) {
+        bool any = false;
+        for (int S : Ss) {
+            SepChoice c;
+            if (!try_shape(q, vec, S, &c) || (any && std::min(waves(c), 8) <= std::min(waves(*best), 8))) continue;
+            *best = c;
+            any = true;
+        }
+        return any;
+    };
+    SepChoice c, d;
+    if (tc == 1) {
+        if (unknowns > (int64_t(1) << 23) && most(2, 1, {16, 32, 64, 8}, &c)) return *out = c, true;
+        if (most(1, 1, {h->n >= 512 ? 16 : 32, 16, 8}, &c) || most(2, 1, {16, 8, 4}, &c)) return *out = c, true;
+        return false;
+    }
+    if (unknowns <= (int64_t(1) << 22)) {
+        const int S = h->sep[0].P >= 32 ? 8 : 16;
+        if (try_shape(0, 1, S, &c) || try_shape(0, 1, 8, &c)) return *out = c, true;
+    }
+    const bool few = (m + 15) / 16 < cus;  // too few groups of 16 to go round
+    const bool pairs = m >= 2 && most(1, 2, few ? std::initializer_list<int>{8, 4, 16, 32, 64}
+                                                : std::initializer_list<int>{16, 32, 64, 8, 4}, &c);
+    const bool longer = most(2, 1, few ? std::initializer_list<int>{8, 4, 16} : std::initializer_list<int>{16, 8, 32, 4},
+                             &d);
+    if (longer && (!pairs || std::min(waves(d), 8) > std::min(waves(c), 8))) return *out = d, true;
+    if (pairs) return *out = c, true;
+    return (try_shape(0, 1, 8, &c) || try_shape(1, 1, 8, &c)) && (*out = c, true);
 }
 
 bool sep_fills(const sbs_lhs *h, int tc, int64_t m, const SepChoice &c) {
@@ -1018,7 +1102,7 @@ constexpr int kCutVec = 2;
 template <int KIND, typename T>
 hipError_t cut_kernel(const void **fn, int *maxt) {
     *maxt = sep_maxt<T, kSegLb, kCutVec>();
-    return sep_kernel<KIND, T, kSegLb, kCutVec, false, false, true>(fn);
+    return sep_kernel<KIND, T, kSegLb, kCutVec, false, 0, true>(fn);
 }
 
 hipError_t cut_fn(int kind, int tc, const void **fn, int *maxt) {
@@ -1129,6 +1213,7 @@ hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int
     a.steps = steps;
     a.m = m;
     a.coef = h->coef;
+    a.bands = h->bands;
     const int grid = (int)std::min<int64_t>(ngroups, (int64_t)cu_count(h->device) * std::max(1, c.wgs));
     const unsigned char *blob = static_cast<const unsigned char *>(f64 ? sp.blob64 : sp.blob32);
     void *args[] = {&blob, &a, &x, &x};
