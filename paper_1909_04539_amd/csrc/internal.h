@@ -168,7 +168,8 @@ struct SepPlan {
 };
 
 // Cut form of a plain solve (systems too long for one workgroup).  The matrix
-// is cut at Q - 1 places, h rows each; the rows between two cuts are a segment.
+// is cut at Q - 1 places, h rows each (Q places if it is periodic, the last
+// cut its last row); the rows between two cuts are a segment.
 // With the unknowns of the cut rows known the segments decouple.  Those
 // unknowns come first: row c of A^{-1} times the right-hand side, of which only
 // the entries near the diagonal matter where the inverse decays (CutWin), and
@@ -179,13 +180,14 @@ struct alignas(16) CutSeg {
     const unsigned char *blob[2];          // the segment's separator plan, FP64 and FP32
     int32_t fac[2], spk[2], scf[2], sinv[2], map;  // its parts' bytes
     int32_t row0, rows, P, Nr, kofs, kw;
-    int32_t has_lo, has_hi, pad;           // whether a cut lies before / after the segment
+    int32_t has_lo, has_hi;                // whether a cut lies before / after the segment
+    int32_t lo_at;                         // first row of the cut before it, relative to row0
     double lo[2][2];  // coefficient of the segment's row t on unknown c of the cut before it
     double hi[2][2];  // of its row rows - h + t on unknown c of the cut after it
 };
 struct alignas(16) CutWin {
     const double *w;      // [len][h]: entries first .. first + len - 1 of the h rows of A^{-1}
-    int32_t row, first, len, pad;  // the cut's first row
+    int32_t row, first, len, pad;  // row: the cut's first row; rows past the last wrap round (periodic)
 };
 constexpr int kCutRows = 256;      // rows of a segment, at most
 constexpr int kMaxCutSegs = 512;   // segments of one matrix (n up to about 130 000)
@@ -194,7 +196,7 @@ constexpr int kMaxCutReach = 192;  // rows of A^{-1} kept on either side of a cu
 struct CutPlan {
     const CutSeg *segs = nullptr;  // device arrays
     const CutWin *wins = nullptr;
-    int Q = 0;                     // segments (0: the matrix has no cut form)
+    int Q = 0, cuts = 0;           // segments (0: the matrix has no cut form) and cuts
     int P = 0, Nr = 0;             // the largest of them
     size_t blob_bytes[2] = {0, 0};
 };

@@ -826,6 +826,7 @@ std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, Fa
 
 struct HostCutSeg {
     int64_t a = 0, b = 0;  // rows
+    bool has_lo = false, has_hi = false;  // a cut before / after it
     int same = -1;         // an earlier segment that is the same matrix, or -1
     SepHostPlan hp;
     SepPlan sp;
@@ -849,18 +850,21 @@ struct HostCuts {
 // 2^-58 of the row's largest, which moves the unknown by at most 2^-57 of
 // (row's largest) x (largest right-hand side), 1/16 of the rounding of one
 // term of its sum; false if more than kMaxCutReach rows on a side are left.
+// Rows of a periodic matrix are counted round (n > 2 kCutNear + 1).
 constexpr int64_t kCutNear = 256;
 
 template <typename Row, typename FactorFn, typename SolveFn>
-bool cut_window(int kind, int64_t n, const double *bands, int64_t row, FactorFn factor, SolveFn solve, HostCutWin &win) {
+bool cut_window(int kind, bool periodic, int64_t n, const double *bands, int64_t row, FactorFn factor, SolveFn solve,
+                HostCutWin &win) {
     const int h = kind / 2;
-    const int64_t lo = std::max<int64_t>(0, row - kCutNear), hi = std::min<int64_t>(n, row + h + kCutNear), ns = hi - lo;
+    const int64_t lo = periodic ? row - kCutNear : std::max<int64_t>(0, row - kCutNear);
+    const int64_t hi = periodic ? row + h + kCutNear : std::min<int64_t>(n, row + h + kCutNear), ns = hi - lo;
     std::vector<Row> rows(ns);
     int64_t bad = -1;
     // entry (i, i + k - h) of A^T is A's entry (i + k - h, i): band 2h - k of that row
     auto tr = [&](int k, int64_t i) -> double {
         const int64_t j = i + k - h;
-        return j < 0 || j >= ns ? 0.0 : bands[(int64_t)(2 * h - k) * n + lo + j];
+        return j < 0 || j >= ns ? 0.0 : bands[(int64_t)(2 * h - k) * n + (lo + j + n) % n];
     };
     if (!factor(ns, tr, rows.data(), &bad)) return false;
     std::vector<double> v((size_t)h * ns, 0.0);
@@ -899,7 +903,7 @@ void cut_solve(const HostCuts &hc, int kind, int64_t n, const double *bands, Sol
         const HostCutWin &w = hc.wins[k], &src = w.same >= 0 ? hc.wins[w.same] : w;
         double z[2] = {0.0, 0.0};
         for (int i = 0; i < src.len; ++i)
-            for (int c = 0; c < h; ++c) z[c] += src.w[(size_t)i * h + c] * x[w.first + i];
+            for (int c = 0; c < h; ++c) z[c] += src.w[(size_t)i * h + c] * x[(w.first + i + n) % n];
         for (int c = 0; c < h; ++c) x[w.row + c] = z[c];
     }
     for (const HostCutSeg &s : hc.segs) {
@@ -907,40 +911,56 @@ void cut_solve(const HostCuts &hc, int kind, int64_t n, const double *bands, Sol
         const int64_t ns = s.b - s.a;
         for (int t = 0; t < h; ++t)
             for (int c = 0; c < h; ++c) {
-                if (s.a > 0 && c >= t && t < ns) f[t] -= bands[(int64_t)(c - t) * n + s.a + t] * x[s.a - h + c];
-                if (s.b < n && c <= t) f[ns - h + t] -= bands[(int64_t)(2 * h + c - t) * n + s.b - h + t] * x[s.b + c];
+                if (s.has_lo && c >= t && t < ns)
+                    f[t] -= bands[(int64_t)(c - t) * n + s.a + t] * x[(s.a - h + c + n) % n];
+                if (s.has_hi && c <= t) f[ns - h + t] -= bands[(int64_t)(2 * h + c - t) * n + s.b - h + t] * x[s.b + c];
             }
         sep_plan_solve<Row>(s.same >= 0 ? hc.segs[s.same].hp : s.hp, h, false, ns, solve, f);
         std::copy(f.begin(), f.end(), x.begin() + s.a);
     }
 }
 
-// Cuts the matrix into Q segments of at most kCutRows rows, all of them a
-// whole number of 32-row blocks but the last; false if a plan is missing, a
-// window too wide, or the result not the recurrences' within kPlanTolerance.
-template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
-bool build_cuts(int kind, int64_t n, const double *bands, FactorFn factor, SolveFn solve, HostCuts &hc) {
-    const int h = kind / 2;
-    const int64_t Q = (n + h + kCutRows + h - 1) / (kCutRows + h);
-    if (Q < 2 || Q > kMaxCutSegs) return false;
-    const int64_t run = ((n - h * (Q - 1) + Q - 1) / Q + kSegLb - 1) / kSegLb * kSegLb;
-    std::vector<std::vector<double>> sub;
-    for (int64_t a = 0; a < n;) {
+// Segments of `run` rows and cuts; the last segment takes what is left.  For a
+// periodic matrix the last cut is its last row.
+std::vector<HostCutSeg> lay_cuts(int h, bool periodic, int64_t n, int64_t run) {
+    std::vector<HostCutSeg> segs;
+    const int64_t end = periodic ? n - h : n;
+    for (int64_t a = 0; a < end;) {
         HostCutSeg s;
         s.a = a;
-        // a remainder of no more than a cut would leave an empty last segment
-        s.b = a + run + h < n ? a + run : n;
-        sub.push_back(sub_bands(kind, n, bands, s.a, s.b));
-        for (size_t q = 0; q < hc.segs.size() && s.same < 0; ++q)
-            if (hc.segs[q].same < 0 && sub[q] == sub.back()) s.same = (int)q;
-        if (s.b - s.a > kCutRows + h) return false;
-        if (s.same < 0 &&
-            !build_sep_plan<Row>(kind, false, s.b - s.a, sub.back().data(), kSegLb, factor, solve, s.hp, 0))
-            return false;
-        hc.segs.push_back(std::move(s));
-        if (hc.segs.back().b < n) {
+        s.b = std::min(end, a + run);
+        s.has_lo = a > 0 || periodic;
+        s.has_hi = s.b < n;
+        a = s.b + h;
+        // what is left after a cut has to be a segment: a last cut with none
+        // after it leaves no rows to be solved by it
+        if (s.b < end && a >= end) s.b = end, s.has_hi = s.b < n, a = end;
+        segs.push_back(std::move(s));
+    }
+    return segs;
+}
+
+// Cuts the matrix into segments of at most kCutRows rows, all of them a whole
+// number of 32-row blocks but the last: about equal ones, or shorter ones where
+// the last would be longer or (periodic) too short for the windows of the cuts
+// on either side.  False if a window is too wide, a plan is missing, or the
+// result is not the recurrences' within kPlanTolerance.
+template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
+bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorFn factor, SolveFn solve, HostCuts &hc) {
+    const int h = kind / 2;
+    const int64_t Q = (n + h + kCutRows + h - 1) / (kCutRows + h);
+    if (Q < 2 || Q > kMaxCutSegs || (periodic && n < 2 * kCutNear + 2)) return false;
+    const int64_t even = ((n - h * (Q - 1) + Q - 1) / Q + kSegLb - 1) / kSegLb * kSegLb;
+    for (int64_t run = even; run >= kCutRows / 2 || run == even; run -= kSegLb) {
+        hc.segs = lay_cuts(h, periodic, n, run);
+        hc.wins.clear();
+        if ((int64_t)hc.segs.size() > kMaxCutSegs) return false;
+        if (hc.segs.size() < 2 || hc.segs.back().b - hc.segs.back().a > kCutRows) continue;
+        bool ok = true;
+        for (const HostCutSeg &s : hc.segs) {
+            if (!s.has_hi) continue;
             HostCutWin w;
-            const int64_t row = hc.segs.back().b;
+            const int64_t row = s.b;
             // an earlier cut whose surroundings are the same has the same window
             for (size_t q = 0; q < hc.wins.size() && w.same < 0; ++q) {
                 const HostCutWin &o = hc.wins[q];
@@ -954,17 +974,30 @@ bool build_cuts(int kind, int64_t n, const double *bands, FactorFn factor, Solve
                 w.first = row + (o.first - o.row);
                 w.len = o.len;
             }
-            if (w.same < 0 && !cut_window<Row>(kind, n, bands, row, factor, solve, w)) return false;
+            if (w.same < 0 && !cut_window<Row>(kind, periodic, n, bands, row, factor, solve, w)) return false;
             hc.wins.push_back(std::move(w));
         }
-        a = hc.segs.back().b + h;
-        if (hc.segs.back().b == n) break;
+        // a window must not reach another cut: its rows are overwritten
+        const size_t nw = hc.wins.size();
+        for (size_t k = 0; k < nw && ok; ++k) {
+            const HostCutWin &w = hc.wins[k];
+            if (k > 0) ok = ok && w.first >= hc.wins[k - 1].row + h;
+            if (k + 1 < nw) ok = ok && w.first + w.len <= hc.wins[k + 1].row;
+            if (periodic && k == 0) ok = ok && w.first + n >= hc.wins[nw - 1].row + h;
+            if (periodic && k + 1 == nw) ok = ok && w.first + w.len - n <= hc.wins[0].row;
+        }
+        if (ok) break;
+        hc.segs.clear();
     }
-    // a window must not reach another cut: its rows are overwritten
-    for (size_t k = 0; k < hc.wins.size(); ++k) {
-        const HostCutWin &w = hc.wins[k];
-        if (k > 0 && w.first < hc.wins[k - 1].row + h) return false;
-        if (k + 1 < hc.wins.size() && w.first + w.len > hc.wins[k + 1].row) return false;
+    if (hc.segs.size() < 2) return false;
+    std::vector<std::vector<double>> sub;
+    for (HostCutSeg &s : hc.segs) {
+        sub.push_back(sub_bands(kind, n, bands, s.a, s.b));
+        for (size_t q = 0; q + 1 < sub.size() && s.same < 0; ++q)
+            if (hc.segs[q].same < 0 && sub[q] == sub.back()) s.same = (int)q;
+        if (s.same < 0 &&
+            !build_sep_plan<Row>(kind, false, s.b - s.a, sub.back().data(), kSegLb, factor, solve, s.hp, 0))
+            return false;
     }
     uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
     std::vector<double> d(n), x;
@@ -975,7 +1008,7 @@ bool build_cuts(int kind, int64_t n, const double *bands, FactorFn factor, Solve
         d[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
     }
     x = d;
-    reference_solve(kind, false, n, bands, d);
+    reference_solve(kind, periodic, n, bands, d);
     cut_solve<Row>(hc, kind, n, bands, solve, x);
     double num = 0.0, den = 0.0;
     bool nan = false;
@@ -1086,11 +1119,11 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     const size_t nseg = whole ? 1 : segs.size();
     total += align256(nseg * sizeof(RefSeg));
     HostCuts hc;
-    if (!periodic && h->n > kCutRows) {
-        const bool ok = tri ? build_cuts<TriRow<double>, TriRow<float>>(SBS_TRI, h->n, bands, FactorTri{},
+    if (h->n > kCutRows) {
+        const bool ok = tri ? build_cuts<TriRow<double>, TriRow<float>>(SBS_TRI, periodic, h->n, bands, FactorTri{},
                                                                         solve_tri_rows, hc)
-                            : build_cuts<PentaRow<double>, PentaRow<float>>(SBS_PENTA, h->n, bands, FactorPenta{},
-                                                                            solve_penta_rows, hc);
+                            : build_cuts<PentaRow<double>, PentaRow<float>>(SBS_PENTA, false, h->n, bands,
+                                                                            FactorPenta{}, solve_penta_rows, hc);
         if (!ok) hc = HostCuts();
     }
     for (const HostCutSeg &s : hc.segs) total += align256(s.b64.size()) + align256(s.b32.size());
@@ -1152,7 +1185,7 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
         }
     }
     if (!hc.segs.empty()) {
-        const int bw = h->kind / 2;
+        const int bw = tri ? 1 : 2;
         const int64_t n = h->n;
         std::vector<CutSeg> cs;
         std::vector<CutWin> cw;
@@ -1179,8 +1212,9 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
             }
             t.row0 = (int32_t)s.a;
             t.rows = (int32_t)(s.b - s.a);
-            t.has_lo = s.a > 0;
-            t.has_hi = s.b < n;
+            t.has_lo = s.has_lo;
+            t.has_hi = s.has_hi;
+            t.lo_at = s.a > 0 ? -bw : (int32_t)(n - bw);
             for (int r = 0; r < 2; ++r)
                 for (int c = 0; c < 2; ++c) {
                     t.lo[r][c] = t.hi[r][c] = 0.0;
@@ -1194,13 +1228,14 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
             CutWin t{};
             t.w = w.same >= 0 ? cw[w.same].w : reinterpret_cast<const double *>(put(w.w.data(), w.w.size() * 8));
             t.row = (int32_t)w.row;
-            t.first = (int32_t)w.first;
+            t.first = (int32_t)((w.first + n) % n);
             t.len = w.len;
             cw.push_back(t);
         }
         h->cut.segs = reinterpret_cast<const CutSeg *>(put(cs.data(), cs.size() * sizeof(CutSeg)));
         h->cut.wins = reinterpret_cast<const CutWin *>(put(cw.data(), cw.size() * sizeof(CutWin)));
         h->cut.Q = (int)cs.size();
+        h->cut.cuts = (int)cw.size();
     }
     if (hipMemcpy(dev, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) return SBS_ERR_DEVICE;
     h->device_bytes += (int64_t)total;

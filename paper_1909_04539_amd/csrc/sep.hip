@@ -395,6 +395,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     constexpr bool MMA = sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char lds[];
     bool cut_lo = false, cut_hi = false;
+    int lo_at = 0;
     T clo[H][H], chi[H][H];
     if constexpr (SEG) {
         constexpr int tc = sizeof(T) == 8 ? 0 : 1;
@@ -414,6 +415,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
         out += (int64_t)s->row0 * a.m;
         cut_lo = s->has_lo != 0;
         cut_hi = s->has_hi != 0;
+        lo_at = s->lo_at;
 #pragma unroll
         for (int t = 0; t < H; ++t)
 #pragma unroll
@@ -483,18 +485,21 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     // (an odd batch: the cut form and Crank-Nicolson steps take pairs all the same)
     constexpr bool ANYM = (SEG || CN) && VEC == 2;
     auto last_only = [&](int g) { return ANYM && (int64_t)g * S + s0 > m - VEC; };
-    // SEG: the unknowns of the cut rows beside the lane's block (only a last
-    // segment may be a single block, and it has none after it)
+    // SEG: the unknowns of the cut rows before the lane's block and after it (a
+    // single block has both only if the matrix is periodic, so tridiagonal:
+    // pentadiagonal lanes need one of the two and keep it in `before`)
     const bool at_lo = SEG && cut_lo && p == 0, at_hi = SEG && cut_hi && p == P - 1;
-    T beside[H][VEC];
+    T before[H][VEC], after[H][VEC];
     auto load_group = [&](int g) {
         const T *src = in + (int64_t)r0 * m + col(g);
         if constexpr (SEG) {
-            if (at_lo || at_hi) {
-                const T *q = at_lo ? src - (int64_t)H * m : src + (int64_t)LB * m;
+            if (H == 1 ? at_lo : at_lo || at_hi) {
+                const T *q = src + (int64_t)(at_lo ? lo_at : n - r0) * m;
 #pragma unroll
-                for (int c = 0; c < H; ++c) load_vec<T, VEC>(q + (int64_t)c * m, beside[c]);
+                for (int c = 0; c < H; ++c) load_vec<T, VEC>(q + (int64_t)c * m, before[c]);
             }
+            if constexpr (H == 1)
+                if (at_hi) load_vec<T, VEC>(src + (int64_t)(n - r0) * m, after[0]);
         }
         if (full) {
 #pragma unroll
@@ -564,14 +569,24 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 #pragma unroll
                         for (int t = 0; t < H; ++t)
 #pragma unroll
-                            for (int c = t; c < H; ++c) x[t][v] = fma(-clo[t][c], beside[c][v], x[t][v]);
-                } else if (at_hi) {
+                            for (int c = t; c < H; ++c) x[t][v] = fma(-clo[t][c], before[c][v], x[t][v]);
+                }
+                if (at_hi && full) {
 #pragma unroll
                     for (int v = 0; v < VEC; ++v)
 #pragma unroll
                         for (int t = 0; t < H; ++t)
 #pragma unroll
-                            for (int c = 0; c <= t; ++c) x[NI + t][v] = fma(-chi[t][c], beside[c][v], x[NI + t][v]);
+                            for (int c = 0; c <= t; ++c)
+                                x[NI + t][v] = fma(-chi[t][c], H == 1 ? after[c][v] : before[c][v], x[NI + t][v]);
+                } else if (H == 1 && at_hi) {
+                    // a ragged last segment of a periodic matrix
+#pragma unroll
+                    for (int t = 0; t < LB; ++t)
+                        if (r0 + t == n - 1) {
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) x[t][v] = fma(-chi[0][0], after[0][v], x[t][v]);
+                        }
                 }
             }
 
@@ -813,14 +828,16 @@ constexpr int kCutWaves = 4;
 
 template <int H, typename T, int VEC>
 __global__ __launch_bounds__(64 * kCutWaves) void k_cut_rows(const CutWin *__restrict__ wins, int ncuts, T *x,
-                                                             int64_t m) {
+                                                             int64_t m, int n) {
     const int lane = threadIdx.x % kWave, part = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const cptr<CutWin> win = (cptr<CutWin>)(wins + blockIdx.x % ncuts);
     const int64_t j0 = ((int64_t)(blockIdx.x / ncuts) * kWave + lane) * VEC, j = min(j0, m - VEC);
     const int per = (win->len + kCutWaves - 1) / kCutWaves;
     const int i0 = part * per, i1 = min(i0 + per, win->len);
     const cptr<double> w = (cptr<double>)win->w;
-    const T *src = x + (int64_t)win->first * m + j;
+    const T *src = x + j;
+    const int first = win->first;
+    auto row = [&](int i) { return (int64_t)(first + i < n ? first + i : first + i - n) * m; };
     double z[H][VEC];
 #pragma unroll
     for (int c = 0; c < H; ++c)
@@ -831,7 +848,7 @@ __global__ __launch_bounds__(64 * kCutWaves) void k_cut_rows(const CutWin *__res
     for (; i + U <= i1; i += U) {
         T f[U][VEC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) load_vec<T, VEC>(src + (int64_t)(i + u) * m, f[u]);
+        for (int u = 0; u < U; ++u) load_vec<T, VEC>(src + row(i + u), f[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -841,7 +858,7 @@ __global__ __launch_bounds__(64 * kCutWaves) void k_cut_rows(const CutWin *__res
     }
     for (; i < i1; ++i) {
         T f[VEC];
-        load_vec<T, VEC>(src + (int64_t)i * m, f);
+        load_vec<T, VEC>(src + row(i), f);
 #pragma unroll
         for (int c = 0; c < H; ++c)
 #pragma unroll
@@ -1106,22 +1123,22 @@ hipError_t cut_kernel(const void **fn, int *maxt) {
 }
 
 hipError_t cut_fn(int kind, int tc, const void **fn, int *maxt) {
-    if (kind == SBS_TRI) return tc == 0 ? cut_kernel<SBS_TRI, double>(fn, maxt) : cut_kernel<SBS_TRI, float>(fn, maxt);
+    if (kind != SBS_PENTA) return tc == 0 ? cut_kernel<SBS_TRI, double>(fn, maxt) : cut_kernel<SBS_TRI, float>(fn, maxt);
     return tc == 0 ? cut_kernel<SBS_PENTA, double>(fn, maxt) : cut_kernel<SBS_PENTA, float>(fn, maxt);
 }
 
 template <int H, typename T>
-hipError_t go_cut_rows(const CutPlan &cp, T *x, int64_t m, hipStream_t s) {
+hipError_t go_cut_rows(const CutPlan &cp, T *x, int64_t m, int64_t n, hipStream_t s) {
     const int64_t groups = (m + kWave * kCutVec - 1) / (kWave * kCutVec);
-    if (groups * (cp.Q - 1) > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_cut_rows<H, T, kCutVec>), dim3((unsigned)(groups * (cp.Q - 1))), dim3(kWave * kCutWaves), 0,
-                       s, cp.wins, cp.Q - 1, x, m);
+    if (groups * cp.cuts > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_cut_rows<H, T, kCutVec>), dim3((unsigned)(groups * cp.cuts)), dim3(kWave * kCutWaves), 0, s,
+                       cp.wins, cp.cuts, x, m, (int)n);
     return hipGetLastError();
 }
 
 template <typename T>
 hipError_t cut_rows(const sbs_lhs *h, T *x, int64_t m, hipStream_t s) {
-    return h->kind == SBS_TRI ? go_cut_rows<1, T>(h->cut, x, m, s) : go_cut_rows<2, T>(h->cut, x, m, s);
+    return h->kind != SBS_PENTA ? go_cut_rows<1, T>(h->cut, x, m, h->n, s) : go_cut_rows<2, T>(h->cut, x, m, h->n, s);
 }
 
 }  // namespace

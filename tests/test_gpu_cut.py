@@ -1,8 +1,9 @@
 """Plain solves of systems too long for one workgroup: the cut form (the
 unknowns of a few rows first, from the rows of the inverse around them, then
 the segments between them on their own) against the oracle, at ragged lengths
-and last segments, odd batches, partial groups and unaligned rows; nothing
-outside the right-hand sides is written."""
+and last segments, odd batches, partial groups and unaligned rows, and for
+periodic matrices of any length; nothing outside the right-hand sides is
+written."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +18,12 @@ TOL = {torch.float64: 1e-12, torch.float32: 2e-5}
 
 def matrix(kind, n, which):
     rng = np.random.default_rng(n)
+    if kind == 13:
+        s = {"constant": 0.5, "stiff": 20.0, "slow": 200.0}.get(which)
+        if s is not None:
+            return np.stack([np.full(n, -s), np.full(n, 1 + 2 * s), np.full(n, -s)])
+        a, c = rng.uniform(-1, 1, n), rng.uniform(-1, 1, n)
+        return np.stack([a, np.abs(a) + np.abs(c) + rng.uniform(1, 2, n), c])
     if which == "constant":
         return W.diffusion_bands(n, 0.5) if kind == 3 else W.hyperdiffusion_bands(n, 0.9)
     if which == "stiff":  # rows of the inverse 150 rows wide on either side
@@ -37,7 +44,8 @@ def colrel(x, ref):
 @pytest.mark.parametrize("kind,n,which", [
     (3, 3001, "random"), (3, 5141, "random"), (3, 8192, "constant"), (3, 5000, "stiff"), (3, 5000, "slow"),
     (5, 1541, "random"), (5, 2001, "random"), (5, 5140, "constant"), (5, 5143, "random"), (5, 5000, "stiff"),
-    (5, 5000, "slow")])
+    (5, 5000, "slow"), (13, 513, "random"), (13, 514, "random"), (13, 1000, "constant"), (13, 1027, "random"),
+    (13, 2600, "random"), (13, 2001, "stiff"), (13, 4999, "random"), (13, 3001, "slow")])
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("m", [1, 2, 3, 33, 64, 513])
 def test_cut_solves_match_oracle(kind, n, which, dtype, m):
