@@ -148,27 +148,35 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 }
 
 // Whether AUTO takes the cut form (two kernels, segments of 256 rows in runs of
-// up to 1 KiB) instead of `form`.  Always where a workgroup cannot hold a whole
-// system with its plan in LDS: the sweeps run one lane per system
-// (pentadiagonal n = 5000, m = 500: 25 against 427 us; tridiagonal n = 8192,
-// m = 4096: 122 against 618 us) and a plan in memory costs a trip per block
-// (pentadiagonal n = 1500 random, m = 2048: 24 against 127 us).  Else where the
-// right-hand sides no longer stay in the 256 MB memory-side cache from one
-// launch to the next, so that the length of the runs decides (pentadiagonal
-// n = 1024, m = 65536: 230 against 253 us; tridiagonal n = 2000, m = 16384:
-// 110 against 153 us; FP32 n = 2000, m = 50001: 216 against 343 us); below,
-// the second kernel costs more than the runs gain (n = 1000, m = 8192:
-// tridiagonal 31 against 24, pentadiagonal 34 against 26 us).  The line lies
-// between 131 MB (n = 1000, m = 16384: tridiagonal 54 against 56,
-// pentadiagonal 59 against 57 us) and 262 MB (m = 32769: 121 against 148, 127
-// against 149 us), and where the whole-system form has runs under 256 bytes
-// between 66 MB (n = 2000, m = 4096: 31 against 30 us) and 98 MB (n = 1500,
-// m = 8192: 46 against 50, 49 against 68 us).
-bool takes_cut(const sbs_lhs *h, int t, int64_t m, int form, const sbs::SepChoice &sc, const sbs::PartChoice &pc) {
+// up to 1 KiB) instead of `form`.  Times are whole form against cut form.
+//  - Always where a workgroup cannot hold a whole system with its plan in LDS:
+//    the sweeps run one lane per system (pentadiagonal n = 5000, m = 500: 427
+//    against 25 us; tridiagonal n = 8192, m = 4096: 618 against 116 us) and a
+//    plan in memory costs a trip per block (pentadiagonal n = 1500 with random
+//    bands, m = 2048: 127 against 24 us).
+//  - Never for what stays in the 256 MB memory-side cache from one launch to
+//    the next (n = 1000, m = 8192: 24 against 31 us; n = 2000, m = 4096: 30
+//    against 31 us; from 98 MB on, n = 1500, m = 8192: 50 against 46 us).
+//  - From 1025 rows on the whole form has runs under 256 bytes or few workgroups
+//    (n = 1100, m = 50000: 223 against 203, 234 against 210 us; n = 2048,
+//    m = 65536 pentadiagonal: 609 against 506 us); in FP32 from 601 rows on
+//    (tridiagonal n = 768, m = 160000: 322 against 226 us; n = 512: 176 against
+//    187 us).
+//  - Odd batches the whole form reads 8 (4) bytes per lane (n = 700, m = 99999:
+//    338 against 281, 362 against 288 us).
+//  - FP64 up to 1024 rows the whole form reads everything once (n = 768,
+//    m = 60000: 149 against 154 us), but with rows a multiple of 128 KiB apart its
+//    256-byte runs of some 30 blocks meet in few memory channels (n = 1024:
+//    m = 65536 253 against 229 us, m = 49152 179 against 167 us, m = 60000 212
+//    against 221 us; n = 896, m = 65536: 198 against 203 us).
+bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, const sbs::SepChoice &sc) {
     if (form == 0 || (form == 1 && sc.gf)) return true;
     const int64_t elem = t == 0 ? 8 : 4, bytes = h->n * m * elem;
-    const int64_t run = (form == 1 ? sc.S : pc.S) * elem;
-    return bytes >= (run < 256 ? 90000000 : int64_t(1) << 27);
+    if (bytes < 90000000) return false;
+    if (h->n > 1024) return true;
+    if (bytes < int64_t(1) << 27) return false;
+    if (m % 2 || !aligned(rhs, 2 * elem)) return true;
+    return t == 0 ? h->n > 960 && m * elem % (128 * 1024) == 0 : h->n > 600;
 }
 
 // The choice depends on the handle, the dtype, m, whether rhs is aligned for
@@ -201,7 +209,7 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
     }
     const int form = pick_uncached(h, t, m, rhs, for_auto, sc, pc);
     sbs::CutChoice cc;
-    if (for_auto && takes_cut(h, t, m, form, *sc, *pc)) sbs::choose_cut(h, t, m, &cc);
+    if (for_auto && takes_cut(h, t, m, rhs, form, *sc)) sbs::choose_cut(h, t, m, &cc);
     if (cut) *cut = cc;
     std::lock_guard<std::mutex> g(mu);
     if (known.size() >= 4096) known.clear();  // bounded: many batch sizes only cost a new choice

@@ -198,6 +198,7 @@ struct CutPlan {
     const CutWin *wins = nullptr;
     int Q = 0, cuts = 0;           // segments (0: the matrix has no cut form) and cuts
     int P = 0, Nr = 0;             // the largest of them
+    int64_t rows = 0, last = 0;    // rows of every segment but the last, and of the last
     size_t blob_bytes[2] = {0, 0};
 };
 

@@ -920,15 +920,15 @@ void cut_solve(const HostCuts &hc, int kind, int64_t n, const double *bands, Sol
     }
 }
 
-// Segments of `run` rows and cuts; the last segment takes what is left.  For a
-// periodic matrix the last cut is its last row.
+// Segments of `run` rows and cuts; the last segment takes what is left once that
+// is no more than kCutRows.  For a periodic matrix the last cut is its last row.
 std::vector<HostCutSeg> lay_cuts(int h, bool periodic, int64_t n, int64_t run) {
     std::vector<HostCutSeg> segs;
     const int64_t end = periodic ? n - h : n;
     for (int64_t a = 0; a < end;) {
         HostCutSeg s;
         s.a = a;
-        s.b = std::min(end, a + run);
+        s.b = end - a <= kCutRows ? end : a + run;
         s.has_lo = a > 0 || periodic;
         s.has_hi = s.b < n;
         a = s.b + h;
@@ -950,12 +950,17 @@ bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorF
     const int h = kind / 2;
     const int64_t Q = (n + h + kCutRows + h - 1) / (kCutRows + h);
     if (Q < 2 || Q > kMaxCutSegs || (periodic && n < 2 * kCutNear + 2)) return false;
-    const int64_t even = ((n - h * (Q - 1) + Q - 1) / Q + kSegLb - 1) / kSegLb * kSegLb;
-    for (int64_t run = even; run >= kCutRows / 2 || run == even; run -= kSegLb) {
+    // the whole blocks nearest to an equal share from below, from above, then less
+    const int64_t below = (n - h * (Q - 1)) / Q / kSegLb * kSegLb;
+    std::vector<int64_t> runs = {below, below + kSegLb};
+    for (int64_t run = below - kSegLb; run >= kCutRows / 2; run -= kSegLb) runs.push_back(run);
+    for (int64_t run : runs) {
+        if (run < kSegLb || run > kCutRows) continue;
         hc.segs = lay_cuts(h, periodic, n, run);
         hc.wins.clear();
         if ((int64_t)hc.segs.size() > kMaxCutSegs) return false;
         if (hc.segs.size() < 2 || hc.segs.back().b - hc.segs.back().a > kCutRows) continue;
+        if (run == below && (int64_t)hc.segs.size() > Q) continue;  // one segment more than the fewest
         bool ok = true;
         for (const HostCutSeg &s : hc.segs) {
             if (!s.has_hi) continue;
@@ -1234,6 +1239,8 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
         }
         h->cut.segs = reinterpret_cast<const CutSeg *>(put(cs.data(), cs.size() * sizeof(CutSeg)));
         h->cut.wins = reinterpret_cast<const CutWin *>(put(cw.data(), cw.size() * sizeof(CutWin)));
+        h->cut.rows = cs.front().rows;
+        h->cut.last = cs.back().rows;
         h->cut.Q = (int)cs.size();
         h->cut.cuts = (int)cw.size();
     }

@@ -115,7 +115,7 @@ struct SepArgs {
     BandCoef coef;  // Crank-Nicolson steps: the matrix's constant band values
     const BandRow *bands;  // or its band rows
     const CutSeg *segs;  // the cut form: Q segments
-    int Q;
+    int Q, per, per_last;  // and the workgroups of each, and of the last
 };
 
 // Device memory that does not change while a kernel runs: uniform reads
@@ -380,7 +380,7 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // last step, not as they are formed: with the pairs of an odd batch as a
 // branch in the output loop 66 registers spilled.
 //
-// SEG: the cut form.  Workgroup b solves segment b % Q of the matrix as one of
+// SEG: the cut form.  A workgroup solves one segment of the matrix as one of
 // its own (its plan, its rows), after k_cut_rows has put the unknowns of the
 // cut rows into the array: the segment's first and last H right-hand sides
 // lose their couplings to them.  A segment of 256 rows leaves room for 128
@@ -395,11 +395,25 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     constexpr bool MMA = sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char lds[];
     bool cut_lo = false, cut_hi = false;
-    int lo_at = 0;
+    int lo_at = 0, seg_b = 0, seg_grid = 1;
     T clo[H][H], chi[H][H];
     if constexpr (SEG) {
         constexpr int tc = sizeof(T) == 8 ? 0 : 1;
-        const cptr<CutSeg> s = (cptr<CutSeg>)(a.segs + blockIdx.x % a.Q);
+        // the segments in turn, then what the last one has fewer or more
+        const int each = min(a.per, a.per_last), rest = (int)blockIdx.x - a.Q * each;
+        int k;
+        if (rest < 0) {
+            k = blockIdx.x % a.Q;
+            seg_b = blockIdx.x / a.Q;
+        } else if (a.per > each) {
+            k = rest % (a.Q - 1);
+            seg_b = each + rest / (a.Q - 1);
+        } else {
+            k = a.Q - 1;
+            seg_b = each + rest;
+        }
+        seg_grid = k == a.Q - 1 ? a.per_last : a.per;
+        const cptr<CutSeg> s = (cptr<CutSeg>)(a.segs + k);
         blob = s->blob[tc];
         a.fac_bytes = s->fac[tc];
         a.spk_bytes = s->spk[tc];
@@ -464,18 +478,19 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 
     const int Ls = S / VEC;  // lanes per block row
     const int l = threadIdx.x, p0 = l / Ls, sl = l - p0 * Ls;
-    // lanes past the last block (the workgroup is whole waves, and a segment of
-    // the cut form may have fewer blocks than the launch has lanes for) run it
-    // once more: the same values to the same places
+    // lanes past the last block (the workgroup is whole waves) run it once more:
+    // the same values to the same places.  In the cut form, where a short last
+    // segment may leave whole waves over, they write nothing.
     const int p = min(p0, P - 1);
+    const bool active = !SEG || p0 < P;
     const int r0 = p * LB;
     const bool has_sep = a.periodic || p < P - 1, has_prev = a.periodic || p > 0;
     const int pp = p == 0 ? P - 1 : p - 1;
     const int s0 = sl * VEC;  // the lane's first system within the group
     const int64_t m = a.m;
     const bool full = r0 + LB <= n;
-    const int grid = SEG ? gridDim.x / a.Q : gridDim.x;
-    int b = SEG ? blockIdx.x / a.Q : blockIdx.x;
+    const int grid = SEG ? seg_grid : gridDim.x;
+    int b = SEG ? seg_b : blockIdx.x;
     if ((a.flags & 1) && grid % 8 == 0) b = (b % 8) * (grid / 8) + b / 8;
 
     T x[LB][VEC];
@@ -600,7 +615,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             // this block's last interior rows (redl); one barrier.  (In this order
             // the first rows' values are dropped before the last rows' are used,
             // which keeps the FP64 pentadiagonal kernel within its registers.)
-            if (has_prev) {
+            if (has_prev && active) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
 #pragma unroll
@@ -612,7 +627,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                         lredr[o_prev + v * ldr + c] = yh;
                     }
             }
-            if (has_sep) {
+            if (has_sep && active) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
 #pragma unroll
@@ -736,7 +751,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                             x[t][v] = v2[v];
                             asm volatile("" : "+v"(x[t][v]));
                         }
-                    } else if (full || r0 + t < n) {
+                    } else if (active && (full || r0 + t < n)) {
                         if (ANYM && one)
                             __builtin_nontemporal_store(v2[VEC - 1], dst + (int64_t)t * m + VEC - 1);
                         else
@@ -750,7 +765,8 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
 #pragma unroll
-                    for (int c = 0; c < H; ++c) ltop[((s0 + v) * P + p) * H + c] = x[c][v];
+                    for (int c = 0; c < H; ++c)
+                        if (active) ltop[((s0 + v) * P + p) * H + c] = x[c][v];
                 __syncthreads();
                 const bool has_next = a.periodic || p < P - 1;
                 const int pn = p == P - 1 ? 0 : p + 1;
@@ -802,7 +818,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             const bool one = last_only(g);
 #pragma unroll
             for (int t = 0; t < LB; ++t) {
-                if (full || r0 + t < n) {
+                if (active && (full || r0 + t < n)) {
                     if (ANYM && one)
                         __builtin_nontemporal_store(x[t][VEC - 1], q + VEC - 1);
                     else
@@ -1028,6 +1044,10 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
         for (int vec = 2; vec >= 1; --vec)
             for (int S = 64; S >= 1; S /= 2) {
                 SepChoice c;
+                // two pentadiagonal FP64 systems per lane of 16 rows spill 40
+                // registers: 32-row blocks instead (n = 300, m = 60000: 60 against
+                // 93 us; n = 384, m = 120000: 161 against 166 us)
+                if (tc == 0 && h->kind == SBS_PENTA && vec == 2 && h->sep[q].lb == 16 && h->n > 32) continue;
                 if (!sep_fit(h, tc, m, x, q, vec, S, kSepDefaultFlags, &c, cn)) continue;
                 const int64_t groups = (m + S - 1) / S;
                 const int64_t engaged = std::min<int64_t>(groups, (int64_t)cus * c.wgs);
@@ -1195,11 +1215,14 @@ hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int
     a.m = m;
     a.segs = cp.segs;
     a.Q = cp.Q;
-    const int64_t per_seg =
-        std::max<int64_t>(1, std::min<int64_t>(ngroups, (int64_t)cu_count(h->device) * c.wgs / cp.Q));
+    // the GPU's workgroups shared out by the segments' rows (all but the last
+    // have the same number)
+    const int64_t all = (int64_t)cu_count(h->device) * c.wgs, rest = cp.rows * (cp.Q - 1);
+    a.per = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, all * cp.rows / (rest + cp.last)));
+    a.per_last = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, all - (int64_t)a.per * (cp.Q - 1)));
     const unsigned char *blob = nullptr;
     void *args[] = {&blob, &a, &x, &x};
-    return hipLaunchKernel(fn, dim3((unsigned)(per_seg * cp.Q)), dim3(c.threads), args, c.lds, s);
+    return hipLaunchKernel(fn, dim3((unsigned)((int64_t)a.per * (cp.Q - 1) + a.per_last)), dim3(c.threads), args, c.lds, s);
 }
 
 hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t s, int steps) {
