@@ -284,7 +284,11 @@ size_t sbs_refined_static_scratch_bytes(void);
  * their matrices A), with the explicit half taken from the handle's own rows,
  * periodic rows wrapping round.  The explicit half is fused into the solve.
  * Where the matrix has a partition plan all steps of a call run on chip: every
- * unknown is read and written once per call; otherwise once per step.
+ * unknown is read and written once per call; otherwise once per step.  Long
+ * systems of decaying inverse run segment by segment, with the unknowns
+ * between the segments (under 1/100 of the array) in memory from the device's
+ * stream-ordered pool for the length of the call; while a graph is captured,
+ * or without that memory, they run as one sweep per step.
  *  c      device, interleaved (n, m), dtype SBS_F64 or SBS_F32; overwritten.
  *  steps  >= 0 (0 and m == 0 do nothing).
  * Any kind of handle.  Asynchronous on `stream`.

@@ -217,6 +217,42 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
     return form;
 }
 
+// Whether a Crank-Nicolson call takes the cut form although other forms fit.
+// It crosses HBM once per step, the others once per call, so only for one step
+// (several are then the same arithmetic however a caller groups them): past
+// 2048 rows, where the pair form (constant bands) has short row runs and few
+// waves (diffusion n = 2500, m = 8192: 85 against 293 us, four steps 321 and
+// 187 us; n = 4000, m = 2000: 39 and 44 us, 145 and 64 us), and with band rows
+// where those fill LDS (tridiagonal n = 2000, m = 10000: 89 against 234 us;
+// n = 600, m = 100000: 254 and 327 us; n = 1000, m = 8192: 41 and 42 us,
+// m = 1000: 30 and 20 us; constant bands n = 1000, m = 60000: 236 and 222 us).
+bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, int steps) {
+    if (steps > 1) return false;
+    const int64_t bytes = h->n * m * (t == 0 ? 8 : 4);
+    return h->n > 2048 || (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27));
+}
+
+// Steps in the cut form, with the unknowns of the cut rows in memory from the
+// device's stream-ordered pool for the length of the call.
+// False: the matrix has no cut form, a graph is being captured (no allocation
+// belongs into it), or there is no memory; other forms then run.
+bool cut_cn(const sbs_lhs *h, int t, void *c, int64_t m, int cn, int steps, hipStream_t s, sbs_status *st) {
+    CutChoice cut;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!choose_cut_cn(h, t, m, cn, &cut) || hipStreamIsCapturing(s, &cap) != hipSuccess ||
+        cap != hipStreamCaptureStatusNone)
+        return false;
+    void *work = nullptr;
+    if (hipMallocAsync(&work, cut_cn_bytes(h, t, m), s) != hipSuccess) {
+        (void)hipGetLastError();  // not this call's error
+        return false;
+    }
+    const hipError_t e = launch_cut_cn(h, cut, t, c, m, cn, steps, work, s);
+    const hipError_t f = hipFreeAsync(work, s);
+    *st = e == hipSuccess && f == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    return true;
+}
+
 }  // namespace
 
 namespace sbs {
@@ -516,27 +552,37 @@ sbs_status sbs_cn_step(sbs_handle h, void *c, int64_t m, int32_t dtype, int32_t 
     const int t = dtype == SBS_F64 ? 0 : 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int cn = h->constant_bands ? 2 : 1;  // constant bands: coefficients by value, no band rows in LDS
+    sbs_status st = SBS_OK;
+    if (takes_cut_cn(h, t, m, steps) && cut_cn(h, t, c, m, cn, steps, s, &st)) return st;
     SepChoice sc;
-    if (steps > 1 && choose_sep_steps(h, t, m, c, cn, &sc))
-        return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    PartChoice pc;
+    if (steps > 1) {
+        if (choose_sep_steps(h, t, m, c, cn, &sc))
+            return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+        // no separator plan that fits: the pair form's steps, if the bands are
+        // constant (n = 4000, m = 2000, 8 steps: 89 us; cut form 285, sweeps 3499)
+        if (h->constant_bands && choose_partition(h, t, m, &pc, 3))
+            return launch_partition(h, pc, t, t, t, c, c, m, s, 3, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    }
     // One step: pentadiagonal, constant bands and a separator shape that fills
     // every CU with whole row runs: the separator kernel's step (coefficients
     // by value).  Hyperdiffusion n = 1024, m = 65536: 234.4 us against 246.2 us
     // in the pair form; for tridiagonal matrices the pair form's step is the
     // faster (periodic diffusion, same size: 221.6 us against 233.5 us).
-    if (h->constant_bands && h->kind == SBS_PENTA) {
-        if (choose_sep(h, t, m, c, &sc, 2) && sep_fills(h, t, m, sc))
-            return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    if (steps == 1 && h->constant_bands && h->kind == SBS_PENTA) {
+        if (choose_sep(h, t, m, c, &sc, 3) && sep_fills(h, t, m, sc))
+            return launch_sep(h, sc, t, c, m, s, 1) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     }
-    PartChoice pc;
-    if (choose_partition(h, t, m, &pc, cn))
-        return launch_partition(h, pc, t, t, t, c, c, m, s, cn, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    const bool pairs = choose_partition(h, t, m, &pc, cn);
     // no pair plan that fits: the separator form (pentadiagonal n = 1000 with
-    // varying bands, m = 3000: 14 us a step against 128 us), else the sweeps
-    if (choose_sep_steps(h, t, m, c, cn, &sc))
+    // varying bands, m = 3000: 14 us a step against 128 us), the cut form, or
+    // the sweeps
+    if (!pairs && choose_sep_steps(h, t, m, c, cn, &sc))
         return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    if (!pairs && cut_cn(h, t, c, m, cn, steps, s, &st)) return st;
     for (int k = 0; k < steps; ++k)
-        if (launch_cn(h, t, c, m, s) != hipSuccess) return SBS_ERR_DEVICE;
+        if ((pairs ? launch_partition(h, pc, t, t, t, c, c, m, s, cn) : launch_cn(h, t, c, m, s)) != hipSuccess)
+            return SBS_ERR_DEVICE;
     return SBS_OK;
 }
 

@@ -182,6 +182,7 @@ struct alignas(16) CutSeg {
     int32_t row0, rows, P, Nr, kofs, kw;
     int32_t has_lo, has_hi;                // whether a cut lies before / after the segment
     int32_t lo_at;                         // first row of the cut before it, relative to row0
+    int32_t lo_cut, hi_cut, pad[2];        // the cuts' numbers
     double lo[2][2];  // coefficient of the segment's row t on unknown c of the cut before it
     double hi[2][2];  // of its row rows - h + t on unknown c of the cut after it
 };
@@ -339,6 +340,12 @@ struct CutChoice {
 };
 bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out);
 hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, hipStream_t stream);
+// Crank-Nicolson steps on the cut form (cn: 1 band rows, 2 constant bands).
+// work: device scratch for the unknowns of the cut rows, cut_cn_bytes(h, tc, m).
+size_t cut_cn_bytes(const sbs_lhs *h, int tc, int64_t m);
+bool choose_cut_cn(const sbs_lhs *h, int tc, int64_t m, int cn, CutChoice *out);
+hipError_t launch_cut_cn(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, int cn, int steps, void *work,
+                         hipStream_t stream);
 // Whether the separator shape fills the GPU with whole 256-byte row runs.
 bool sep_fills(const sbs_lhs *h, int tc, int64_t m, const SepChoice &c);
 

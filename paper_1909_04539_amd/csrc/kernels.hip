@@ -824,16 +824,16 @@ __device__ __forceinline__ void stage_blob(unsigned char *lds, const unsigned ch
     for (; i < total; i += step) dst[i] = src[i];
 }
 
-// CN: `steps` Crank-Nicolson steps (in == out) instead of a solve: after the
+// CN: a Crank-Nicolson step (in == out) instead of a solve: after the
 // correction each lane holds its block of u = A^{-1} c, swaps its first and
 // last H values with the neighbouring blocks through LDS, and writes
 // 2 u - A u with the band rows (CN 1: compact, NB = 2H + 1 per row, in LDS;
-// CN 2: constant bands, the NB coefficients in `coef`).  The group's systems
-// are whole in the workgroup, so every step but the last leaves its rows in
-// the registers for the next one: HBM is crossed once in and once out however
-// many steps a call asks for.
-// (Periodic diffusion n = 512, m = 6000, 20 steps per call: 182 us, with one
-// launch per step 333 us.)
+// CN 2 and 3: constant bands, the NB coefficients in `coef`).  CN 3: `steps`
+// of them.  The group's systems are whole in the workgroup, so every step but
+// the last leaves its rows in the registers for the next one: HBM is crossed
+// once in and once out however many steps a call asks for.  One step has a
+// kernel of its own since the choice between register and store at each row
+// costs it a fifth (diffusion n = 1000, m = 60000: 221 us, with it 289 us).
 // `periodic`: block 0 and block P-1 are neighbours (one more interface pair).
 // ROWS: the systems are stored one after another (system j at j*n .. j*n+n-1,
 // the rows of a row-major grid) instead of interleaved; each lane then reads
@@ -909,7 +909,7 @@ __global__ __launch_bounds__(MAXT) void k_part(const unsigned char *__restrict__
 #pragma unroll
             for (int t = 0; t < LB; ++t) x[t] = (r0 + t < n) ? static_cast<T>(src[(int64_t)t * rs]) : T(0);
         }
-        for (int step = CN ? steps : 1; step > 0; --step) {
+        for (int step = CN == 3 ? steps : 1; step > 0; --step) {
             typename R::Fwd st;
             fwd_chunk<KIND, T, LB>(fr, x, st);
             typename R::Bwd bs;
@@ -972,14 +972,14 @@ __global__ __launch_bounds__(MAXT) void k_part(const unsigned char *__restrict__
                     win[NB - 1] = t + H < LB ? corr(t + H) : rgt[t + H - LB];
                     // constant bands: the coefficients are kernel arguments (the
                     // values they meet outside the matrix are 0 in the window)
-                    const double *b = CN == 2 ? coef.c : lband + (r0 + t) * NB;
+                    const double *b = CN >= 2 ? coef.c : lband + (r0 + t) * NB;
                     T ax = T(b[0]) * win[0];
 #pragma unroll
                     for (int k = 1; k < NB; ++k) ax = fma(T(b[k]), win[k], ax);
                     const T v = T(2) * win[H] - ax;
                     // one store pointer stepped row by row (pinned, so that the
                     // addresses of all rows are not formed up front and kept live)
-                    if (step > 1) {
+                    if (CN == 3 && step > 1) {
                         // read by no later row of this step; rows past the matrix stay 0
                         x[t] = r0 + t < n ? v : T(0);
                     } else {
@@ -1604,8 +1604,10 @@ int part_kind(int kind) { return kind == SBS_PENTA ? SBS_PENTA : SBS_TRI; }
 // waves and LDS together).
 template <int KIND, typename T>
 int part_wgs_cn(int cn, int lb, int threads, size_t lds) {
-    return cn == 2 ? part_wgs_lb<KIND, T, 2>(lb, threads, lds)
-                   : cn == 1 ? part_wgs_lb<KIND, T, 1>(lb, threads, lds) : part_wgs_lb<KIND, T, 0>(lb, threads, lds);
+    return cn == 3   ? part_wgs_lb<KIND, T, 3>(lb, threads, lds)
+           : cn == 2 ? part_wgs_lb<KIND, T, 2>(lb, threads, lds)
+           : cn == 1 ? part_wgs_lb<KIND, T, 1>(lb, threads, lds)
+                     : part_wgs_lb<KIND, T, 0>(lb, threads, lds);
 }
 
 int part_wgs_per_cu(int kind, int tc, int lb, int threads, size_t lds, int cn) {
@@ -1880,16 +1882,17 @@ bool part_shape(const sbs_lhs *h, int tc, int64_t m, int lb, int S, PartChoice *
 template <int KIND, typename T>
 hipError_t go_part_cn(const sbs_lhs *h, const PartChoice &c, const void *in, void *out, int64_t m, hipStream_t s,
                       int cn, int steps) {
-    return cn == 2 ? go_part_lb<KIND, T, 2>(h, c, in, out, m, steps, s)
-                   : cn == 1 ? go_part_lb<KIND, T, 1>(h, c, in, out, m, steps, s)
-                             : go_part_lb<KIND, T, 0>(h, c, in, out, m, 1, s);
+    return cn == 3   ? go_part_lb<KIND, T, 3>(h, c, in, out, m, steps, s)
+           : cn == 2 ? go_part_lb<KIND, T, 2>(h, c, in, out, m, 1, s)
+           : cn == 1 ? go_part_lb<KIND, T, 1>(h, c, in, out, m, 1, s)
+                     : go_part_lb<KIND, T, 0>(h, c, in, out, m, 1, s);
 }
 
 hipError_t launch_partition(const sbs_lhs *h, const PartChoice &c, int tc, int tin, int tout, const void *in, void *out,
                             int64_t m, hipStream_t stream, int cn, int steps) {
     if (m <= 0) return hipSuccess;
-    if (steps < 1) return hipErrorInvalidValue;
-    if (tc != tin || tc != tout || cn < 0 || cn > 2 || (cn == 2 && !h->constant_bands)) return hipErrorInvalidValue;
+    if (steps < 1 || (steps > 1 && cn != 3)) return hipErrorInvalidValue;
+    if (tc != tin || tc != tout || cn < 0 || cn > 3 || (cn >= 2 && !h->constant_bands)) return hipErrorInvalidValue;
     if (part_kind(h->kind) == SBS_TRI)
         return tc == 0 ? go_part_cn<SBS_TRI, double>(h, c, in, out, m, stream, cn, steps)
                        : go_part_cn<SBS_TRI, float>(h, c, in, out, m, stream, cn, steps);

@@ -1220,6 +1220,8 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
             t.has_lo = s.has_lo;
             t.has_hi = s.has_hi;
             t.lo_at = s.a > 0 ? -bw : (int32_t)(n - bw);
+            t.hi_cut = (int32_t)cs.size();
+            t.lo_cut = s.a > 0 ? t.hi_cut - 1 : (int32_t)hc.wins.size() - 1;
             for (int r = 0; r < 2; ++r)
                 for (int c = 0; c < 2; ++c) {
                     t.lo[r][c] = t.hi[r][c] = 0.0;

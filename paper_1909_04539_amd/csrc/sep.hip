@@ -116,6 +116,7 @@ struct SepArgs {
     const BandRow *bands;  // or its band rows
     const CutSeg *segs;  // the cut form: Q segments
     int Q, per, per_last;  // and the workgroups of each, and of the last
+    const void *ucut;      // its Crank-Nicolson steps: the unknowns of the cut rows, [cut][H][m]
 };
 
 // Device memory that does not change while a kernel runs: uniform reads
@@ -366,19 +367,24 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // with u = A^{-1} c in registers, row t of the output is
 // 2 u_t - sum_e coef_e u_{t-H+e}, with the row's own coefficients (CN 1: the
 // band rows a.bands, staged in LDS) or those of a matrix whose bands are
-// constant (CN 2: the values in a.coef).  The rows
+// constant (CN 2 and 3: the values in a.coef).  The rows
 // above the block are the previous block's separators (known to the lane);
 // the first H rows of the next block come through LDS, one more barrier.
 // Values outside the matrix are 0, so the constant coefficients also give
 // the truncated rows at its ends.  The group's systems are whole in the
 // workgroup, so every step but the last leaves its rows in the registers
 // for the next one: HBM is crossed once in and once out however many steps a
-// call asks for, and a step costs its arithmetic and barriers only.
+// call asks for, and a step costs its arithmetic and barriers only.  CN 3 is
+// one step, with each row stored as it is formed: fewer values live, and the
+// stores spread out (hyperdiffusion n = 600, m = 100000: 234 us, through the
+// several steps' kernel 277 us).
 // (Hyperdiffusion n = 1024, m = 65536, 8 steps per call: 597 us, with one
 // launch and one pass over HBM per step 1827 us; periodic diffusion n = 512,
 // m = 6000, 20 steps: 89 us against 332 us.)  The rows are stored after the
 // last step, not as they are formed: with the pairs of an odd batch as a
 // branch in the output loop 66 registers spilled.
+// With SEG one step per launch; the unknowns of the cut rows are in ucut, and
+// the workgroup before a cut also steps its rows.
 //
 // SEG: the cut form.  A workgroup solves one segment of the matrix as one of
 // its own (its plan, its rows), after k_cut_rows has put the unknowns of the
@@ -395,7 +401,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     constexpr bool MMA = sizeof(T) == 8;
     extern __shared__ __align__(16) unsigned char lds[];
     bool cut_lo = false, cut_hi = false;
-    int lo_at = 0, seg_b = 0, seg_grid = 1;
+    int lo_at = 0, lo_cut = 0, hi_cut = 0, seg_b = 0, seg_grid = 1;
     T clo[H][H], chi[H][H];
     if constexpr (SEG) {
         constexpr int tc = sizeof(T) == 8 ? 0 : 1;
@@ -430,6 +436,9 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
         cut_lo = s->has_lo != 0;
         cut_hi = s->has_hi != 0;
         lo_at = s->lo_at;
+        lo_cut = s->lo_cut;
+        hi_cut = s->hi_cut;
+        if constexpr (CN == 1) a.bands += s->row0;
 #pragma unroll
         for (int t = 0; t < H; ++t)
 #pragma unroll
@@ -498,7 +507,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     // addresses, so their duplicate stores are harmless
     auto col = [&](int g) { return min((int64_t)g * S + s0, m - VEC); };
     // (an odd batch: the cut form and Crank-Nicolson steps take pairs all the same)
-    constexpr bool ANYM = (SEG || CN) && VEC == 2;
+    constexpr bool ANYM = (SEG || (CN && CN != 3)) && VEC == 2;
     auto last_only = [&](int g) { return ANYM && (int64_t)g * S + s0 > m - VEC; };
     // SEG: the unknowns of the cut rows before the lane's block and after it (a
     // single block has both only if the matrix is periodic, so tridiagonal:
@@ -508,13 +517,19 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     auto load_group = [&](int g) {
         const T *src = in + (int64_t)r0 * m + col(g);
         if constexpr (SEG) {
+            // (Crank-Nicolson steps leave the cut rows' own values where they are)
+            const T *qlo = src + (int64_t)lo_at * m, *qhi = src + (int64_t)(n - r0) * m;
+            if constexpr (CN) {
+                qlo = static_cast<const T *>(a.ucut) + (int64_t)lo_cut * H * m + col(g);
+                qhi = static_cast<const T *>(a.ucut) + (int64_t)hi_cut * H * m + col(g);
+            }
             if (H == 1 ? at_lo : at_lo || at_hi) {
-                const T *q = src + (int64_t)(at_lo ? lo_at : n - r0) * m;
+                const T *q = at_lo ? qlo : qhi;
 #pragma unroll
                 for (int c = 0; c < H; ++c) load_vec<T, VEC>(q + (int64_t)c * m, before[c]);
             }
             if constexpr (H == 1)
-                if (at_hi) load_vec<T, VEC>(src + (int64_t)(n - r0) * m, after[0]);
+                if (at_hi) load_vec<T, VEC>(qhi, after[0]);
         }
         if (full) {
 #pragma unroll
@@ -564,7 +579,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             cr[c][d] = (2 * H - c + d < NB) ? cfp[c * NB + 2 * H - c + d] : T(0);
         }
     for (; g < a.ngroups; g += grid) {
-        for (int step = CN ? a.steps : 1; step > 0; --step) {
+        for (int step = CN && CN != 3 ? a.steps : 1; step > 0; --step) {
             // the lane's offsets into the separator buffers, made opaque each
             // group so that the addresses derived from them are formed where they
             // are used instead of being kept live (and spilled) across the loop
@@ -778,13 +793,31 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                         const T t0 = ltop[((s0 + v) * P + pn) * H + c];
                         dn[c][v] = has_next ? t0 : T(0);
                     }
+                if constexpr (SEG) {
+                    if (at_hi) {
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v)
+#pragma unroll
+                            for (int c = 0; c < H; ++c) dn[c][v] = H == 1 ? after[c][v] : before[c][v];
+                        // the row after a ragged last segment (periodic)
+                        if (H == 1 && !full) {
+#pragma unroll
+                            for (int t = 0; t < LB; ++t)
+                                if (r0 + t == n) {
+#pragma unroll
+                                    for (int v = 0; v < VEC; ++v) x[t][v] = after[0][v];
+                                }
+                        }
+                    }
+                }
                 // rows above the block: the previous block's separators (0 above
                 // the first block of a matrix that does not wrap round)
                 T up[H][VEC];  // the H rows above row t, before their own update
+                T *q = dst;    // CN 3: stepped row by row, as below
 #pragma unroll
                 for (int c = 0; c < H; ++c)
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) up[c][v] = zl[c][v];
+                    for (int v = 0; v < VEC; ++v) up[c][v] = SEG && at_lo ? before[c][v] : zl[c][v];
 #pragma unroll
                 for (int t = 0; t < LB; ++t) {
                     T cb[NB];
@@ -804,14 +837,20 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 #pragma unroll
                         for (int c = 0; c < H; ++c) up[c][v] = c + 1 < H ? up[c + 1][v] : x[t][v];
                     }
-                    // rows past the matrix stay 0
+                    if constexpr (CN == 3) {
+                        if (full || r0 + t < n) store_vec_nt<T, VEC>(q, v2);
+                        q += m;
+                        asm volatile("" : "+v"(q));
+                    } else {
+                        // rows past the matrix stay 0
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < n ? v2[v] : T(0);
+                        for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < n ? v2[v] : T(0);
+                    }
                     if (t % G == G - 1) pin(v2[0]);
                 }
             }
         }
-        if constexpr (CN) {
+        if constexpr (CN && CN != 3) {
             // one store pointer stepped row by row (opaque, so that the rows'
             // addresses are not all formed up front and kept live)
             T *q = out + (int64_t)r0 * m + col(g);
@@ -827,6 +866,23 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                 q += m;
                 asm volatile("" : "+v"(q));
             }
+            if constexpr (SEG) {
+                // the cut after the segment: c' = 2 u - A u = 2 u - c
+                if (at_hi && active) {
+                    T *qc = out + (int64_t)n * m + col(g);
+#pragma unroll
+                    for (int c = 0; c < H; ++c) {
+                        T w[VEC];
+                        load_vec<T, VEC>(qc + (int64_t)c * m, w);
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) w[v] = T(2) * (H == 1 ? after[c][v] : before[c][v]) - w[v];
+                        if (ANYM && one)
+                            __builtin_nontemporal_store(w[VEC - 1], qc + (int64_t)c * m + VEC - 1);
+                        else
+                            store_vec_nt<T, VEC>(qc + (int64_t)c * m, w);
+                    }
+                }
+            }
         }
         if (g + grid < a.ngroups) load_group(g + grid);
     }
@@ -838,13 +894,14 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 // waves take a quarter of the window's rows each and add up in LDS (fixed
 // order), so that the loads of a system, all independent, are in flight over
 // four waves.  Reads what it needs of the right-hand sides once more than the
-// solve does: 2 * 37 rows in 258 for the s = 0.5 hyperdiffusion matrix.  The
+// solve does: 2 * 37 rows in 258 for the s = 0.5 hyperdiffusion matrix.  With
+// ucut they go there, [cut][H][m], and the right-hand sides stay as they are.  The
 // sums are FP64 whatever T is; the window of a cut holds no other cut's rows.
 constexpr int kCutWaves = 4;
 
 template <int H, typename T, int VEC>
 __global__ __launch_bounds__(64 * kCutWaves) void k_cut_rows(const CutWin *__restrict__ wins, int ncuts, T *x,
-                                                             int64_t m, int n) {
+                                                             int64_t m, int n, T *ucut) {
     const int lane = threadIdx.x % kWave, part = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const cptr<CutWin> win = (cptr<CutWin>)(wins + blockIdx.x % ncuts);
     const int64_t j0 = ((int64_t)(blockIdx.x / ncuts) * kWave + lane) * VEC, j = min(j0, m - VEC);
@@ -896,7 +953,7 @@ __global__ __launch_bounds__(64 * kCutWaves) void k_cut_rows(const CutWin *__res
         for (int q = 1; q < kCutWaves; ++q) t += sum[q][part][v][lane];
         r[v] = (T)t;
     }
-    T *dst = x + (int64_t)(win->row + part) * m + j;
+    T *dst = ucut ? ucut + ((int64_t)(blockIdx.x % ncuts) * H + part) * m + j : x + (int64_t)(win->row + part) * m + j;
     // past the last pair: the last system only (see k_sep)
     if (VEC == 1 || j0 > m - VEC)
         dst[VEC - 1] = r[VEC - 1];
@@ -945,6 +1002,9 @@ hipError_t sep_kernel_of(int lb, int vec, bool gf, int cn, const void **fn, int 
     if (cn && gf) return hipErrorInvalidValue;
     if (cn == 1) return sep_kernel_cn<KIND, T, 1>(lb, vec, fn, maxt);
     if (cn == 2) return sep_kernel_cn<KIND, T, 2>(lb, vec, fn, maxt);
+    if constexpr (KIND == SBS_PENTA)
+        if (cn == 3) return sep_kernel_cn<KIND, T, 3>(lb, vec, fn, maxt);
+    if (cn) return hipErrorInvalidValue;
     if (gf) {
         if (lb == 32 && vec == 2) return *maxt = sep_maxt<T, 32, 2>(), sep_kernel<KIND, T, 32, 2, true>(fn);
         if (lb == 64 && vec == 1) return *maxt = sep_maxt<T, 64, 1>(), sep_kernel<KIND, T, 64, 1, true>(fn);
@@ -992,8 +1052,8 @@ int cu_count(int device) { return device_cus(device); }
 // room for a third FP64 buffer the separators overwrite redL (flags bit 5,
 // which only this function sets).
 //
-// cn: Crank-Nicolson steps with band rows (1) or constant bands (2); plan in
-// LDS only.
+// cn: Crank-Nicolson steps with band rows (1) or constant bands (2), or one
+// step with constant bands (3, pentadiagonal only); plan in LDS only.
 bool sep_fit(const sbs_lhs *h, int tc, int64_t m, const void *x, int q, int vec, int S, int flags, SepChoice *c,
              int cn = 0) {
     const SepPlan &sp = h->sep[q];
@@ -1048,6 +1108,7 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
                 // registers: 32-row blocks instead (n = 300, m = 60000: 60 against
                 // 93 us; n = 384, m = 120000: 161 against 166 us)
                 if (tc == 0 && h->kind == SBS_PENTA && vec == 2 && h->sep[q].lb == 16 && h->n > 32) continue;
+                if (vec == 2 && (m % 2 || reinterpret_cast<uintptr_t>(x) % (2 * elem))) continue;  // pairs aligned
                 if (!sep_fit(h, tc, m, x, q, vec, S, kSepDefaultFlags, &c, cn)) continue;
                 const int64_t groups = (m + S - 1) / S;
                 const int64_t engaged = std::min<int64_t>(groups, (int64_t)cus * c.wgs);
@@ -1079,12 +1140,17 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
 // (two workgroups then hide each other's barriers; tridiagonal n = 1000,
 // m = 60000: 428 us, 32 systems 581 us, 16-row blocks 603 us, the pair form
 // 774 us; pentadiagonal 540, 666, - and 672 us; with band rows in LDS n = 512
-// 401 us at 64 systems, 883 us at 16).  64-row blocks where the separators of
-// shorter ones leave too little LDS (pentadiagonal n = 2000, m = 10000: 298 us,
-// 32-row blocks 700 us, one launch of the sweeps per step 2007 us).  FP32: one
-// system per lane, 32-row blocks up to 8M unknowns, else 64-row ones.
+// 401 us at 64 systems, 883 us at 16; n = 1400, m = 20000, pentadiagonal: 347
+// us at 16 systems, 556 us at 8, 64-row blocks 426 us).  64-row blocks where
+// the separators of shorter ones leave too little LDS (pentadiagonal n = 2000,
+// m = 10000: 254 us, the cut form 703, one launch of the sweeps per step 2007
+// us).  Four systems per workgroup, 32-byte row runs, only for batches of up to
+// 4M unknowns or without a cut form (n = 2000 with band rows, m = 10000: 851
+// us, the cut form 660; m = 1000: 100 and 200 us).  FP32: one system per lane,
+// 32-row blocks up to 8M unknowns, else 64-row ones in the widest workgroup of
+// up to 12 waves (n = 1400, m = 40000: 32 systems 392 us, 16 517 us, 32-row
+// blocks 746 us; n = 2000, m = 20000: 16 systems 685 us, 32 (16 waves) 939 us).
 bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn, SepChoice *out) {
-    const int cus = cu_count(h->device);
     const int64_t unknowns = h->n * m;
     auto waves = [](const SepChoice &c) { return c.wgs * (c.threads / kWave); };
     auto try_shape = [&](int q, int vec, int S, SepChoice *c) { return sep_fit(h, tc, m, x, q, vec, S, 0, c, cn); };
@@ -1099,24 +1165,26 @@ bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn
         }
         return any;
     };
-    SepChoice c, d;
+    SepChoice c;
+    const bool cut = h->cut.P > 0;
     if (tc == 1) {
-        if (unknowns > (int64_t(1) << 23) && most(2, 1, {16, 32, 64, 8}, &c)) return *out = c, true;
-        if (most(1, 1, {h->n >= 512 ? 16 : 32, 16, 8}, &c) || most(2, 1, {16, 8, 4}, &c)) return *out = c, true;
-        return false;
+        if (unknowns > (int64_t(1) << 23)) {
+            for (int S : {64, 32, 16})
+                if (try_shape(2, 1, S, &c) && c.threads <= 768) return *out = c, true;
+        }
+        return (most(1, 1, {h->n >= 512 ? 16 : 32, 16, 8}, &c) || most(2, 1, {16, 8}, &c) ||
+                (!cut && most(2, 1, {4}, &c))) &&
+               (*out = c, true);
     }
-    if (unknowns <= (int64_t(1) << 22)) {
+    const bool few = unknowns <= (int64_t(1) << 22);
+    if (few) {
         const int S = h->sep[0].P >= 32 ? 8 : 16;
         if (try_shape(0, 1, S, &c) || try_shape(0, 1, 8, &c)) return *out = c, true;
     }
-    const bool few = (m + 15) / 16 < cus;  // too few groups of 16 to go round
-    const bool pairs = m >= 2 && most(1, 2, few ? std::initializer_list<int>{8, 4, 16, 32, 64}
-                                                : std::initializer_list<int>{16, 32, 64, 8, 4}, &c);
-    const bool longer = most(2, 1, few ? std::initializer_list<int>{8, 4, 16} : std::initializer_list<int>{16, 8, 32, 4},
-                             &d);
-    if (longer && (!pairs || std::min(waves(d), 8) > std::min(waves(c), 8))) return *out = d, true;
-    if (pairs) return *out = c, true;
-    return (try_shape(0, 1, 8, &c) || try_shape(1, 1, 8, &c)) && (*out = c, true);
+    return ((m >= 2 && most(1, 2, {16, 32, 64}, &c)) || most(2, 1, {8, 16}, &c) || (m >= 2 && try_shape(1, 2, 8, &c)) ||
+            ((few || !cut) && (most(2, 1, {4}, &c) || (m >= 2 && try_shape(1, 2, 4, &c)))) || try_shape(0, 1, 8, &c) ||
+            try_shape(1, 1, 8, &c)) &&
+           (*out = c, true);
 }
 
 bool sep_fills(const sbs_lhs *h, int tc, int64_t m, const SepChoice &c) {
@@ -1137,29 +1205,36 @@ namespace {
 constexpr int kCutVec = 2;
 
 template <int KIND, typename T>
-hipError_t cut_kernel(const void **fn, int *maxt) {
+hipError_t cut_kernel(int cn, const void **fn, int *maxt) {
     *maxt = sep_maxt<T, kSegLb, kCutVec>();
-    return sep_kernel<KIND, T, kSegLb, kCutVec, false, 0, true>(fn);
+    return cn == 0   ? sep_kernel<KIND, T, kSegLb, kCutVec, false, 0, true>(fn)
+           : cn == 1 ? sep_kernel<KIND, T, kSegLb, kCutVec, false, 1, true>(fn)
+                     : sep_kernel<KIND, T, kSegLb, kCutVec, false, 2, true>(fn);
 }
 
-hipError_t cut_fn(int kind, int tc, const void **fn, int *maxt) {
-    if (kind != SBS_PENTA) return tc == 0 ? cut_kernel<SBS_TRI, double>(fn, maxt) : cut_kernel<SBS_TRI, float>(fn, maxt);
-    return tc == 0 ? cut_kernel<SBS_PENTA, double>(fn, maxt) : cut_kernel<SBS_PENTA, float>(fn, maxt);
+hipError_t cut_fn(int kind, int tc, int cn, const void **fn, int *maxt) {
+    if (kind != SBS_PENTA)
+        return tc == 0 ? cut_kernel<SBS_TRI, double>(cn, fn, maxt) : cut_kernel<SBS_TRI, float>(cn, fn, maxt);
+    return tc == 0 ? cut_kernel<SBS_PENTA, double>(cn, fn, maxt) : cut_kernel<SBS_PENTA, float>(cn, fn, maxt);
 }
 
 template <int H, typename T>
-hipError_t go_cut_rows(const CutPlan &cp, T *x, int64_t m, int64_t n, hipStream_t s) {
+hipError_t go_cut_rows(const CutPlan &cp, T *x, int64_t m, int64_t n, T *ucut, hipStream_t s) {
     const int64_t groups = (m + kWave * kCutVec - 1) / (kWave * kCutVec);
     if (groups * cp.cuts > 0x7fffffff) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_cut_rows<H, T, kCutVec>), dim3((unsigned)(groups * cp.cuts)), dim3(kWave * kCutWaves), 0, s,
-                       cp.wins, cp.cuts, x, m, (int)n);
+                       cp.wins, cp.cuts, x, m, (int)n, ucut);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t cut_rows(const sbs_lhs *h, T *x, int64_t m, hipStream_t s) {
-    return h->kind != SBS_PENTA ? go_cut_rows<1, T>(h->cut, x, m, h->n, s) : go_cut_rows<2, T>(h->cut, x, m, h->n, s);
+hipError_t cut_rows(const sbs_lhs *h, void *x, int64_t m, void *ucut, hipStream_t s) {
+    T *xt = static_cast<T *>(x), *ut = static_cast<T *>(ucut);
+    return h->kind != SBS_PENTA ? go_cut_rows<1, T>(h->cut, xt, m, h->n, ut, s)
+                                : go_cut_rows<2, T>(h->cut, xt, m, h->n, ut, s);
 }
+
+bool fit_cut(const sbs_lhs *h, int tc, int64_t m, int cn, CutChoice *out);
 
 }  // namespace
 
@@ -1171,13 +1246,20 @@ hipError_t cut_rows(const sbs_lhs *h, T *x, int64_t m, hipStream_t s) {
 // and 128 systems 232 us, 256 rows and 64 systems (two workgroups) 255 us, 512
 // rows and 64 systems 235 us, 32 systems 257 us; tri n = 1024 226, 249, 235
 // and 257 us; FP32 tri n = 2000, m = 50001 218, 234, 311 us.
-bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out) {
+bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out) { return fit_cut(h, tc, m, 0, out); }
+
+bool choose_cut_cn(const sbs_lhs *h, int tc, int64_t m, int cn, CutChoice *out) { return fit_cut(h, tc, m, cn, out); }
+
+namespace {
+
+bool fit_cut(const sbs_lhs *h, int tc, int64_t m, int cn, CutChoice *out) {
     const CutPlan &cp = h->cut;
+    const int H = h->kind == SBS_PENTA ? 2 : 1;
     if (cp.Q < 2 || m < kCutVec) return false;
     const size_t elem = tc == 0 ? 8 : 4;
     const void *fn = nullptr;
     int maxt = 0;
-    if (cut_fn(h->kind, tc, &fn, &maxt) != hipSuccess) return false;
+    if (cut_fn(h->kind, tc, cn, &fn, &maxt) != hipSuccess) return false;
     const int cus = cu_count(h->device);
     CutChoice best;
     for (int S = kWave * kCutVec; S * (int)elem >= 64; S /= 2) {
@@ -1185,7 +1267,10 @@ bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out) {
         c.S = S;
         c.threads = S / kCutVec * cp.P;
         const size_t red = tc == 0 ? sep_red_bytes<double>(S, cp.Nr) : sep_red_bytes<float>(S, cp.Nr);
-        c.lds = cp.blob_bytes[tc] + red * (tc == 0 ? 3 : 2);
+        c.lds = cp.blob_bytes[tc] + red * (tc == 0 || cn ? 3 : 2);
+        if (cn)
+            c.lds += ((size_t)S * cp.P * H * elem + 15) / 16 * 16 +
+                     (cn == 1 ? (size_t)cp.P * kSegLb * (2 * H + 1) * elem : 0);
         if (c.threads > maxt || c.lds > kMaxPartLdsBytes) continue;
         if (best.S && c.threads % kWave) break;
         if ((c.wgs = occupancy(fn, c.threads, c.lds)) < 1) continue;
@@ -1197,18 +1282,22 @@ bool choose_cut(const sbs_lhs *h, int tc, int64_t m, CutChoice *out) {
     return true;
 }
 
-hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, hipStream_t s) {
+// One solve or Crank-Nicolson step (cn, with ucut): the cut rows, then the segments.
+hipError_t run_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, int cn, void *ucut,
+                   hipStream_t s) {
     if (m <= 0) return hipSuccess;
     const CutPlan &cp = h->cut;
     const void *fn = nullptr;
     int maxt = 0;
-    if (hipError_t e = cut_fn(h->kind, tc, &fn, &maxt); e != hipSuccess) return e;
+    if (hipError_t e = cut_fn(h->kind, tc, cn, &fn, &maxt); e != hipSuccess) return e;
     const int64_t ngroups = (m + c.S - 1) / c.S;
     if (c.threads > maxt || ngroups * cp.Q > 0x7fffffff) return hipErrorInvalidValue;
-    const hipError_t e =
-        tc == 0 ? cut_rows(h, static_cast<double *>(x), m, s) : cut_rows(h, static_cast<float *>(x), m, s);
+    const hipError_t e = tc == 0 ? cut_rows<double>(h, x, m, ucut, s) : cut_rows<float>(h, x, m, ucut, s);
     if (e != hipSuccess) return e;
     SepArgs a{};
+    a.coef = h->coef;
+    a.bands = h->bands;
+    a.ucut = ucut;
     a.S = c.S;
     a.ngroups = (int)ngroups;
     a.steps = 1;
@@ -1223,6 +1312,23 @@ hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int
     const unsigned char *blob = nullptr;
     void *args[] = {&blob, &a, &x, &x};
     return hipLaunchKernel(fn, dim3((unsigned)((int64_t)a.per * (cp.Q - 1) + a.per_last)), dim3(c.threads), args, c.lds, s);
+}
+
+}  // namespace
+
+hipError_t launch_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, hipStream_t s) {
+    return run_cut(h, c, tc, x, m, 0, nullptr, s);
+}
+
+size_t cut_cn_bytes(const sbs_lhs *h, int tc, int64_t m) {
+    return (size_t)h->cut.cuts * (h->kind == SBS_PENTA ? 2 : 1) * (size_t)m * (tc == 0 ? 8 : 4);
+}
+
+hipError_t launch_cut_cn(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_t m, int cn, int steps, void *work,
+                         hipStream_t s) {
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < steps && e == hipSuccess; ++k) e = run_cut(h, c, tc, x, m, cn, work, s);
+    return e;
 }
 
 hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int64_t m, hipStream_t s, int steps) {
