@@ -570,7 +570,11 @@ hipError_t go_refw(const sbs_lhs *h, const RefwChoice &c, const float *b, double
     sg.Nr = sp.Nr;
     sg.ldsinv = sp.refine.ldsinv;
     const int ngroups = (int)((m + kWave - 1) / kWave);
-    const int grid = std::min(ngroups, device_cus(h->device));
+    // as many workgroups as fit side by side (waves and LDS): while one waits
+    // for its barriers or for HBM the others compute (tridiagonal, 256M
+    // unknowns: n = 256 879 -> 686 us, n = 128 1067 -> 671, n = 48 2133 -> 690)
+    const int wgs = std::max(1, std::min((LB <= 32 ? 16 : 8) / sp.P, (int)(kMaxPartLdsBytes / c.lds)));
+    const int grid = std::min(ngroups, device_cus(h->device) * wgs);
     hipLaunchKernelGGL((k_refine_wave<KIND, LB, refw_maxt<KIND, LB>()>), dim3(grid), dim3(sp.P * kWave), c.lds, s, sg,
                        ngroups, sweeps, b, x, m);
     return hipGetLastError();
