@@ -308,10 +308,13 @@ sbs_status refined_run(const sbs_lhs *h, const float *b, double *x, int64_t m, i
                        hipStream_t s) {
     // Fused paths: one kernel keeps each block of b and x on chip through all
     // passes (needs a partition plan); r is not touched.  First the
-    // one-wave-per-block kernel on the separator plan, then the same on
-    // overlapping segments of the matrix, then the pair form.
+    // one-wave-per-block kernel, on overlapping segments of the matrix where two
+    // workgroups of it fit on a CU, else on the separator plan, else on longer
+    // segments; then the pair form.
     RefwChoice rc;
-    if (choose_refine_wave(h, m, &rc))
+    const bool halves = h->nseg > 1 && h->segP <= seg_half(h->kind) &&
+                        (!h->seg_small || m <= (int64_t)64 * device_cus(h->device));
+    if (!halves && choose_refine_wave(h, m, &rc))
         return launch_refine_wave(h, rc, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     if (h->nseg > 0) return launch_refine_segs(h, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     PartChoice pc;

@@ -133,6 +133,7 @@ struct alignas(16) RefSeg {
 constexpr int kSegLb = 32;       // rows per block of a segment's plan
 constexpr int kMaxSegs = 64;     // segments of one matrix (n up to about 20 000)
 constexpr int kMaxHalo = 64;     // rows of a halo
+constexpr int kMaxWhole = 512;   // rows that one workgroup can solve whole
 constexpr double kSegDrop = 0x1p-60;
 // Blocks of a segment: one wave each (1024 threads), and the workgroup's
 // right-hand sides and exchange buffers within the LDS.
@@ -216,6 +217,7 @@ struct sbs_lhs {
     void *pdev = nullptr;       // partition data (one allocation for all plans)
     const sbs::RefSeg *segs = nullptr;  // device array, nseg segments (0: the matrix has none)
     int nseg = 0, segP = 0, segNr = 0;  // segP, segNr: the largest P and Nr among them
+    bool seg_small = false;     // they pay only for batches that do not fill the GPU otherwise
     sbs::CutPlan cut;
     sbs::PartPlan part[3];      // block lengths 16, 32, 64
     sbs::SepPlan sep[3];        // block lengths 16, 32, 64
@@ -370,13 +372,15 @@ struct Tile {
     // corrections, one wave per tile; 2: FP32 request, one FP64 sweep of its
     // stored values; 3, 4: FP32 request, mixed precision with two corrections
     // on one segment of the matrix, a workgroup with one wave per block (3: at
-    // most kSegHalf blocks in every segment, 4: more)
+    // most seg_half blocks in every segment, 4: more)
     int32_t kind, prec;
     int32_t req;                // the request's slot in the launch's completion arrays
     int32_t pad;
 };
 
-constexpr int kSegHalf = 8;  // blocks of the segments that run two workgroups per CU
+// Blocks of the segments that run two workgroups per CU: 8 waves of 128
+// registers each, and the pentadiagonal kernel's LDS (90 KB at 8 blocks).
+constexpr int seg_half(int kind) { return kind == SBS_PENTA ? 7 : 8; }
 // Runs tiles [0, ntiles), all of one kind and prec, with `grid`
 // persistent waves (prec 3 and 4: workgroups that fill the GPU instead);
 // *dev_counter must be 0 when the kernel starts.

@@ -771,15 +771,52 @@ bool seg_independent(int kind, int64_t n, const double *bands, const HostSeg &s,
     return true;
 }
 
-// Cuts the matrix into the fewest equal segments that fit with the shortest
-// halo whose segments are independent; empty if there is none.
+bool pays(int kind, int64_t shorter, int64_t longer, bool small) {
+    return longer > 9 && shorter * 100 <= longer * (small ? 175 : kind == SBS_PENTA ? 140 : 145);
+}
+
+// The fewest equal runs of rows that fit blocks of `cap` rows with `halo` rows
+// on either side: their number, and the 32-row blocks of all of them.
+struct SegLayout {
+    int64_t ns = 0, blocks = 0;
+};
+SegLayout seg_layout(int64_t n, int64_t cap, int64_t halo) {
+    SegLayout l;
+    if (n <= cap) return {1, (n + kSegLb - 1) / kSegLb};
+    const int64_t core = cap - 2 * halo;
+    l.ns = n <= 2 * (cap - halo) ? 2 : (n + core - 1) / core;
+    const int64_t run = (n + l.ns - 1) / l.ns;
+    for (int64_t k = 0; k < l.ns; ++k) {
+        const int64_t lo = std::max<int64_t>(0, run * k - halo), hi = std::min(n, run * (k + 1) + halo);
+        l.blocks += (std::max<int64_t>(hi - lo, 0) + kSegLb - 1) / kSegLb;
+    }
+    return l;
+}
+
+// Cuts the matrix into overlapping segments with the shortest halo that makes
+// them independent; empty if there is none, or if the matrix is better solved
+// whole.  Segments of seg_half blocks run two workgroups per CU, one of which
+// computes while the other loads and stores, at about 36 us a block and 512K
+// systems (pentadiagonal 49), one workgroup of twice the blocks at 55 (70 to
+// 80): short ones unless their halos make 1.45 (1.4) times the blocks.  Batches
+// that do not fill the GPU (16384 systems) take them up to 1.75 times, since
+// they spread the rows over more CUs (n = 512, m = 1000: tridiagonal 19 -> 11
+// us, pentadiagonal 27 -> 14; m = 64000 115 and 122, 160 and 170).
+// (256M unknowns, tridiagonal with 32-row halos n = 512 869 -> 805 us, n = 600
+// 916 -> 827, n = 1500 951 -> 772; with 48-row ones n = 400 927 -> 711, n = 512
+// would go from 869 to 909; pentadiagonal n = 300 1223 -> 1130, n = 1500
+// 1436 -> 1352, n = 600 would go from 1295 to 1402, and nine whole blocks,
+// n = 257, from 1123 to 1261.)
 template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
 std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, FactorFn factor, SolveFn solve) {
-    const int64_t cap = (int64_t)seg_max_blocks(kind) * kSegLb;
-    for (int halo = 16; halo <= kMaxHalo; halo += 16) {
-        const int64_t core = cap - 2 * halo;
-        const int64_t ns = n <= 2 * (cap - halo) ? 2 : (n + core - 1) / core;
-        if (ns > kMaxSegs) return {};
+    const int64_t most = (int64_t)seg_max_blocks(kind) * kSegLb, least = (int64_t)seg_half(kind) * kSegLb;
+    // blocks of the whole matrix where one workgroup can hold it
+    const int64_t whole = n <= kMaxWhole ? (n + kSegLb - 1) / kSegLb : 0;
+    for (int halo = 8; halo <= kMaxHalo; halo += 8) {
+        const SegLayout shorter = seg_layout(n, least, halo), longer = seg_layout(n, most, halo);
+        const bool halves = shorter.ns <= kMaxSegs && pays(kind, shorter.blocks, whole ? whole : longer.blocks, whole > 0);
+        const int64_t ns = halves ? shorter.ns : longer.ns;
+        if (ns == 1 || ns > kMaxSegs) return {};
         std::vector<HostSeg> segs((size_t)ns);
         std::vector<std::vector<double>> sub((size_t)ns);
         bool ok = true;
@@ -811,11 +848,15 @@ std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, Fa
         for (int64_t k = 0; k < ns; ++k) {
             HostSeg &s = segs[k];
             if (s.same >= 0) continue;
-            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, s.hp, 1)) return {};
+            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, s.hp, 1)) {
+                ok = false;
+                break;
+            }
             std::vector<unsigned char> b64;
             serialise_sep<Row, Row32>(s.hp, b64, s.b32, s.sp);
             serialise_refine<Row32>(s.hp, s.b32, s.sp, kind, s.hi - s.lo, sub[k].data(), s.rec, s.sp.refine);
         }
+        if (!ok) continue;
         return segs;
     }
     return {};
@@ -1108,11 +1149,10 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
             total += r32[q].size();
         }
     }
-    // Segments for the mixed-precision kernels: the 32-row separator plan
-    // itself where the whole matrix is one, else overlapping runs of rows.
+    // Segments for the mixed-precision kernels: overlapping runs of rows, or the
+    // 32-row separator plan itself where the whole matrix is one.
     std::vector<HostSeg> segs;
-    const bool whole = !periodic && h->sep[1].ok && h->sep[1].P <= seg_max_blocks(h->kind);
-    if (!periodic && h->n > (int64_t)seg_max_blocks(h->kind) * kSegLb) {
+    if (!periodic && h->n > (int64_t)seg_half(h->kind) * kSegLb) {
         if (tri)
             segs = build_segments<TriRow<double>, TriRow<float>>(SBS_TRI, h->n, bands, FactorTri{}, solve_tri_rows);
         else
@@ -1121,6 +1161,12 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     }
     for (const HostSeg &s : segs)
         if (s.same < 0) total += align256(s.b32.size()) + align256(s.rec.size());
+    if (!segs.empty() && h->n <= kMaxWhole) {
+        int64_t blocks = 0;
+        for (const HostSeg &s : segs) blocks += (s.hi - s.lo + kSegLb - 1) / kSegLb;
+        h->seg_small = !pays(h->kind, blocks, (h->n + kSegLb - 1) / kSegLb, false);
+    }
+    const bool whole = segs.empty() && !periodic && h->sep[1].ok && h->sep[1].P <= seg_max_blocks(h->kind);
     const size_t nseg = whole ? 1 : segs.size();
     total += align256(nseg * sizeof(RefSeg));
     HostCuts hc;

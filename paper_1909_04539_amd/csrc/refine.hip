@@ -595,7 +595,7 @@ hipError_t go_segs(const sbs_lhs *h, const float *b, double *x, int64_t m, int s
     static const hipError_t attr = seg_kernel(k_refine_segs<KIND>);
     if (attr != hipSuccess) return attr;
     const int64_t ntasks = (m + kWave - 1) / kWave * h->nseg;
-    const int64_t wgs = (int64_t)device_cus(h->device) * (h->segP <= kSegHalf ? 2 : 1);
+    const int64_t wgs = (int64_t)device_cus(h->device) * (h->segP <= seg_half(h->kind) ? 2 : 1);
     hipLaunchKernelGGL(k_refine_segs<KIND>, dim3((unsigned)std::min(ntasks, wgs)), dim3(h->segP * kWave),
                        seg_lds(KIND, h->segP), s, h->segs, h->nseg, ntasks, sweeps, b, x, m);
     return hipGetLastError();
@@ -608,7 +608,7 @@ hipError_t go_refine_tiles(bool half, const Tile *tiles, int ntiles, int *counte
     if (attr != hipSuccess) return attr;
     int dev = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
-    const int blocks = half ? kSegHalf : seg_max_blocks(KIND);
+    const int blocks = half ? seg_half(KIND) : seg_max_blocks(KIND);
     const int grid = std::min(ntiles, device_cus(dev) * (half ? 2 : 1));
     hipLaunchKernelGGL(k_refine_tiles<KIND>, dim3(grid), dim3(blocks * kWave), seg_lds(KIND, blocks), s, tiles, ntiles,
                        counter, left, done);

@@ -426,7 +426,7 @@ sbs_status sbs_server_submit(sbs_server *srv, int32_t lhs_id, const void *rhs, i
     // and by segments where the matrix has them (no scratch is touched then,
     // but the request's size stays what the header states)
     if (prec == 1 && h->nseg > 0 && h->segP > 2 && m <= kSegMaxSystems) {
-        const int32_t by_seg = h->segP <= kSegHalf ? 3 : 4;
+        const int32_t by_seg = h->segP <= seg_half(h->kind) ? 3 : 4;
         if (tile_count(h, by_seg, m) <= kMaxTilesPerLaunch) prec = by_seg;
     }
     if (r->bytes > srv->budget) {
