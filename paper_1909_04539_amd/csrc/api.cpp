@@ -154,7 +154,17 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 //    against 25 us; tridiagonal n = 8192, m = 4096: 618 against 116 us) and a
 //    plan in memory costs a trip per block (pentadiagonal n = 1500 with random
 //    bands, m = 2048: 127 against 24 us).
-//  - Never for what stays in the 256 MB memory-side cache from one launch to
+//  - Past 2048 rows always: pair and separator forms have runs of a few systems
+//    and 30 to 500 us of latency (m = 500, tridiagonal n = 3000 64 against 21
+//    us, pentadiagonal 73 and 23; n = 4096, m = 2048 40 and 33, 96 and 36 us).
+//    From 1025 rows on where the separator form's runs are under 128 bytes and
+//    there are systems enough for the cut form's (pentadiagonal n = 1600,
+//    m = 1500: 40 against 26 us, n = 1300 with varying bands 42 and 24 us), or
+//    its last round of workgroups is nearly empty (tridiagonal n = 1800,
+//    m = 4500: 49 against 39 us), and for the pair form from 1729 on
+//    (tridiagonal FP32 n = 1950, m = 777: 21 against 14 us; n = 1600: 17
+//    and 19 us).
+//  - Else never for what stays in the 256 MB memory-side cache from one launch to
 //    the next (n = 1000, m = 8192: 24 against 31 us; n = 2000, m = 4096: 30
 //    against 31 us; from 98 MB on, n = 1500, m = 8192: 50 against 46 us).
 //  - From 1025 rows on the whole form has runs under 256 bytes or few workgroups
@@ -170,8 +180,14 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 //    m = 65536 253 against 229 us, m = 49152 179 against 167 us, m = 60000 212
 //    against 221 us; n = 896, m = 65536: 198 against 203 us).
 bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, const sbs::SepChoice &sc) {
-    if (form == 0 || (form == 1 && sc.gf)) return true;
+    if (form == 0 || (form == 1 && sc.gf) || h->n > 2048) return true;
     const int64_t elem = t == 0 ? 8 : 4, bytes = h->n * m * elem;
+    if (h->n > 1024) {
+        if (form == 2 && h->n > 1728) return true;
+        const int64_t at_once = (int64_t)device_cus(h->device) * std::max(1, sc.wgs);
+        const int64_t groups = form == 1 ? (m + sc.S - 1) / sc.S : 0;
+        if (form == 1 && (sc.S * elem < 128 ? m >= 128 : groups > at_once && groups * 4 <= at_once * 5)) return true;
+    }
     if (bytes < 90000000) return false;
     if (h->n > 1024) return true;
     if (bytes < int64_t(1) << 27) return false;
