@@ -322,7 +322,7 @@ def bench_tri256(args, torch, sbs, W):
             "hbm_frac_16B": round(16 * u / dev / 1e9 / HBM_PEAK_GBS, 4),
             "us_kernel_median_warm": warm * 1e6, "us_kernel_median_cold": cold * 1e6,
             "us_per_solve_graph": gdev / per_graph * 1e6,
-            "bound": "latency: back-to-back calls from Python cost about 10 us of host work each; "
+            "bound": "latency: back-to-back calls from Python cost about 5 us of host work each; "
                      "us_per_solve_graph is the device's own time per solve; cold = 1 GiB written "
                      "between the input's restore and the launch (median of 20)"}
 
