@@ -173,7 +173,9 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 //    (tridiagonal n = 768, m = 160000: 322 against 226 us; n = 512: 176 against
 //    187 us).
 //  - Odd batches the whole form reads 8 (4) bytes per lane (n = 700, m = 99999:
-//    338 against 281, 362 against 288 us).
+//    338 against 281, 362 against 288 us); from 449 rows on in FP64 tridiagonal
+//    (260 MB: n = 480 129 against 118 us, n = 400 122 against 127), else from
+//    321 (pentadiagonal FP32 n = 343 151 against 142 us, n = 270 159 and 177).
 //  - FP64 up to 1024 rows the whole form reads everything once (n = 768,
 //    m = 60000: 149 against 154 us), but with rows a multiple of 128 KiB apart its
 //    256-byte runs of some 30 blocks meet in few memory channels (n = 1024:
@@ -191,7 +193,7 @@ bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, co
     if (bytes < 90000000) return false;
     if (h->n > 1024) return true;
     if (bytes < int64_t(1) << 27) return false;
-    if (m % 2 || !aligned(rhs, 2 * elem)) return true;
+    if (m % 2 || !aligned(rhs, 2 * elem)) return h->n > (t == 0 && h->kind != SBS_PENTA ? 448 : 320);
     return t == 0 ? h->n > 960 && m * elem % (128 * 1024) == 0 : h->n > 600;
 }
 
