@@ -161,9 +161,10 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 //    there are systems enough for the cut form's (pentadiagonal n = 1600,
 //    m = 1500: 40 against 26 us, n = 1300 with varying bands 42 and 24 us), or
 //    its last round of workgroups is nearly empty (tridiagonal n = 1800,
-//    m = 4500: 49 against 39 us), and for the pair form from 1729 on
-//    (tridiagonal FP32 n = 1950, m = 777: 21 against 14 us; n = 1600: 17
-//    and 19 us).
+//    m = 4500: 49 against 39 us), and for the pair form, pentadiagonal FP64
+//    (n = 1200 with varying bands, m = 1500: 50 against 25 us, m = 64 22 and
+//    16 us) or from 1729 on (tridiagonal FP32 n = 1950, m = 777: 21 against
+//    14 us; n = 1600: 17 and 19 us).
 //  - Else never for what stays in the 256 MB memory-side cache from one launch to
 //    the next (n = 1000, m = 8192: 24 against 31 us; n = 2000, m = 4096: 30
 //    against 31 us; from 98 MB on, n = 1500, m = 8192: 50 against 46 us).
@@ -185,7 +186,7 @@ bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, co
     if (form == 0 || (form == 1 && sc.gf) || h->n > 2048) return true;
     const int64_t elem = t == 0 ? 8 : 4, bytes = h->n * m * elem;
     if (h->n > 1024) {
-        if (form == 2 && h->n > 1728) return true;
+        if (form == 2 && (h->n > 1728 || (t == 0 && h->kind == SBS_PENTA))) return true;
         const int64_t at_once = (int64_t)device_cus(h->device) * std::max(1, sc.wgs);
         const int64_t groups = form == 1 ? (m + sc.S - 1) / sc.S : 0;
         if (form == 1 && (sc.S * elem < 128 ? m >= 128 : groups > at_once && groups * 4 <= at_once * 5)) return true;
