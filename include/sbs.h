@@ -183,8 +183,9 @@ sbs_status sbs_solve_batch_variant(sbs_handle h, void *rhs, int64_t m,
  *          (64, 1) only).  Bit 5 is ignored.  Bit 6: the FP64 product
  *          with S^{-1} over every column; by default each 16-row tile of
  *          S^{-1} reads only the columns that hold its nonzero entries (the
- *          plan sets entries of at most 2^-60 / Nr of their row's largest to
- *          0), which gives the same result bit for bit.
+ *          plan sets entries of at most 2^-60 / Nr of their row's largest, as
+ *          they are and times the size of the separator row they meet, to 0),
+ *          which gives the same result bit for bit.
  * Same arguments and results as sbs_solve_batch otherwise.  A shape that has
  * no plan, exceeds 1024 threads, the register budget or the LDS returns
  * SBS_ERR_INVALID_ARG.
@@ -200,8 +201,9 @@ sbs_status sbs_solve_batch_partition(sbs_handle h, void *rhs, int64_t m,
  * Long systems and large batches of matrices whose inverse decays within 192
  * rows (diagonally dominant and positive definite ones) AUTO may cut instead:
  * the unknowns of a few rows come first, from the rows of the inverse around
- * them (what is dropped is below 2^-57 of a row's largest entry), and the
- * segments of 256 rows between them are then solved independently.  This
+ * them, and the segments of at most 256 rows between them are then solved
+ * independently.  What is dropped of those rows moves an unknown by less than
+ * 2^-54 of the system's largest, however the matrix's rows are scaled.  This
  * call and sbs_auto_variant report the whole-system form there too. */
 sbs_status sbs_partition_shape(sbs_handle h, int64_t m, int32_t dtype,
                                const void *rhs, int32_t *form, int32_t *lb,

@@ -321,22 +321,31 @@ struct SepHostPlan {
 // dominant or positive definite matrix, so most of S^{-1} is far below its
 // row's largest entry (for the 1024-row hyperdiffusion matrix in 32-row
 // blocks, entries two separators apart are below 1e-24 of it).  An entry
-// whose magnitude is at most 2^-60 / Nr of its row's largest is set to 0:
-// the dropped part of any z_i = sum_j S^{-1}_ij yhat_j is then at most
+// S^{-1}_ij is set to 0 if both its magnitude and |S^{-1}_ij| s_j, with s_j the
+// largest entry of row j of S, are at most 2^-60 / Nr of the largest in its
+// row.  A separator right-hand side yhat = S z is as large as its row of S
+// makes it (|yhat_j| <= Nr s_j max |z|), and S^{-1}_ij as small, so it is the
+// weighted entry that tells whether z_i depends on it; the entry itself bounds
+// the dropped part of any z_i = sum_j S^{-1}_ij yhat_j by
 // 2^-60 max_j |S^{-1}_ij| max |yhat|, below 1 / (128 Nr) of the rounding
 // error bound of the product itself.  The product is done in 16-row tiles of
 // S^{-1}; tile t (rows 16t .. 16t + 15) reads columns k0 .. k0 + kw - 1 with
 // k0 = min(max(16t + kofs, 0), max(Nr4 - kw, 0)), Nr4 = Nr rounded up to 4,
 // which holds every nonzero entry of the tile's rows.  kw = 0: every column.
-void sep_window(std::vector<double> &S, int Nr, int &kofs, int &kw) {
+// scale: the s_j.
+void sep_window(std::vector<double> &S, const std::vector<double> &scale, int Nr, int &kofs, int &kw) {
     kofs = kw = 0;
     if (Nr <= 0) return;
     for (int i = 0; i < Nr; ++i) {
-        double mx = 0.0;
-        for (int j = 0; j < Nr; ++j) mx = std::max(mx, std::fabs(S[(size_t)i * Nr + j]));
-        const double thr = std::ldexp(mx, -60) / Nr;
+        double *row = S.data() + (size_t)i * Nr;
+        double mx = 0.0, mxs = 0.0;
+        for (int j = 0; j < Nr; ++j) {
+            mx = std::max(mx, std::fabs(row[j]));
+            mxs = std::max(mxs, std::fabs(row[j]) * scale[j]);
+        }
+        const double thr = std::ldexp(mx, -60) / Nr, thrs = std::ldexp(mxs, -60) / Nr;
         for (int j = 0; j < Nr; ++j)
-            if (std::fabs(S[(size_t)i * Nr + j]) <= thr) S[(size_t)i * Nr + j] = 0.0;
+            if (std::fabs(row[j]) <= thr && std::fabs(row[j]) * scale[j] <= thrs) row[j] = 0.0;
     }
     const int mt = (Nr + 15) / 16, Nr4 = (Nr + 3) / 4 * 4;
     std::vector<int> lo(mt, Nr), hi(mt, -1);
@@ -542,8 +551,21 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
             }
         }
     }
+    std::vector<double> scale(Nr, 0.0);
+    for (int r = 0; r < Nr; ++r)
+        for (int k = 0; k < Nr; ++k) scale[r] = std::max(scale[r], std::fabs(S[(size_t)r * Nr + k]));
+    // rows of about the same size, by powers of two: the pivots chosen and every
+    // rounding are then the same however the matrix's rows are scaled
+    std::vector<int> two(Nr, 0);
+    for (int r = 0; r < Nr; ++r) {
+        if (!std::isfinite(scale[r]) || scale[r] == 0.0) return false;
+        two[r] = std::ilogb(scale[r]);
+        for (int k = 0; k < Nr; ++k) S[(size_t)r * Nr + k] = std::ldexp(S[(size_t)r * Nr + k], -two[r]);
+    }
     if (Nr > 0 && !invert(S, Nr)) return false;
-    sep_window(S, Nr, hp.kofs, hp.kw);
+    for (int r = 0; r < Nr; ++r)
+        for (int k = 0; k < Nr; ++k) S[(size_t)r * Nr + k] = std::ldexp(S[(size_t)r * Nr + k], -two[k]);
+    sep_window(S, scale, Nr, hp.kofs, hp.kw);
     hp.lb = lb;
     hp.P = P;
     hp.Nr = Nr;
@@ -887,11 +909,17 @@ struct HostCuts {
 // Rows c .. c + h - 1 of A^{-1} near their diagonal entries: the solutions of
 // A^T w = e on the rows within kCutNear of the cut (the matrix beyond changes
 // the entries kept below by the square of the decay over kCutNear rows).
-// On either side entries are dropped while their magnitudes add up to at most
-// 2^-58 of the row's largest, which moves the unknown by at most 2^-57 of
-// (row's largest) x (largest right-hand side), 1/16 of the rounding of one
-// term of its sum; false if more than kMaxCutReach rows on a side are left.
-// Rows of a periodic matrix are counted round (n > 2 kCutNear + 1).
+// On either side entries w_i are dropped while two sums stay at most 2^-58 each:
+// that of |w_i| in units of the row's largest, and that of |w_i| s_i, with s_i
+// the largest coefficient of the matrix's row i, in units of the largest such
+// term (1 if that is more).  The second does not change when a row and its
+// right-hand sides are multiplied by the same factor, as the solution does not:
+// with f = A x a right-hand side is at most (2h + 1) s_i max |x|, so what is
+// dropped moves the unknown by at most (2h + 1) 2^-57 of the system's largest
+// unknown.  (By |w_i| alone a row with a large diagonal entry, or large rows
+// beside small ones, lost digits: diffusion n = 2500 with one entry 1e12 eleven
+// rows before a cut, 4e-7.)  False if more than kMaxCutReach rows on a side are
+// left.  Rows of a periodic matrix are counted round (n > 2 kCutNear + 1).
 constexpr int64_t kCutNear = 256;
 
 template <typename Row, typename FactorFn, typename SolveFn>
@@ -908,21 +936,33 @@ bool cut_window(int kind, bool periodic, int64_t n, const double *bands, int64_t
         return j < 0 || j >= ns ? 0.0 : bands[(int64_t)(2 * h - k) * n + (lo + j + n) % n];
     };
     if (!factor(ns, tr, rows.data(), &bad)) return false;
-    std::vector<double> v((size_t)h * ns, 0.0);
+    std::vector<double> v((size_t)h * ns, 0.0), scale(ns, 0.0);
+    for (int64_t i = 0; i < ns; ++i)
+        for (int k = 0; k < 2 * h + 1; ++k) {
+            const int64_t r = lo + i, col = r + k - h;
+            if (periodic || (col >= 0 && col < n))
+                scale[i] = std::max(scale[i], std::fabs(bands[(int64_t)k * n + (r + n) % n]));
+        }
     int64_t reach_lo = 0, reach_hi = 0;
     for (int c = 0; c < h; ++c) {
         double *w = v.data() + (size_t)c * ns;
         w[row + c - lo] = 1.0;
         solve(ns, rows.data(), w);
-        double mx = 0.0;
-        for (int64_t i = 0; i < ns; ++i) mx = std::max(mx, std::fabs(w[i]));
-        if (!std::isfinite(mx)) return false;
-        const double most = std::ldexp(mx, -58);
+        double mx = 0.0, mxs = 0.0;
+        for (int64_t i = 0; i < ns; ++i) {
+            mx = std::max(mx, std::fabs(w[i]));
+            mxs = std::max(mxs, std::fabs(w[i]) * scale[i]);
+        }
+        if (!std::isfinite(mx) || !std::isfinite(mxs)) return false;
+        const double most = std::ldexp(mx, -58), mosts = std::ldexp(std::min(mxs, 1.0), -58);
+        double s = 0.0, ss = 0.0;
+        auto drops = [&](int64_t i) {
+            return (s += std::fabs(w[i])) <= most && (ss += std::fabs(w[i]) * scale[i]) <= mosts;
+        };
         int64_t i = 0, e = ns - 1;
-        for (double s = 0.0; i < row - lo && (s += std::fabs(w[i])) <= most; ++i) {
-        }
-        for (double s = 0.0; e > row + h - 1 - lo && (s += std::fabs(w[e])) <= most; --e) {
-        }
+        while (i < row - lo && drops(i)) ++i;
+        s = ss = 0.0;
+        while (e > row + h - 1 - lo && drops(e)) --e;
         reach_lo = std::max(reach_lo, row - lo - i);
         reach_hi = std::max(reach_hi, lo + e - (row + h - 1));
     }
