@@ -85,39 +85,56 @@ struct HostPlan {
 // few seeded right-hand sides and compared with the sweep recurrences on the
 // whole matrix; a plan whose result differs by more than kPlanTolerance
 // (relative, per column, infinity norm) is dropped and the sweeps serve that
-// matrix.
+// matrix.  Four right-hand sides are uniform in every row; two are A x of a
+// uniform x, as large in each row as its coefficients: with uniform ones the
+// unknowns of small rows outweigh all others, and a plan that loses the
+// unknowns of large rows would pass.  For those two the plan may be as near to
+// that x instead (the periodic recurrences lose digits of their own where the
+// first row is large).
 constexpr double kPlanTolerance = 1e-13;
-constexpr int kPlanChecks = 4;  // seeded right-hand sides
+constexpr int kUniformChecks = 4, kScaledChecks = 2;
 
 // Reference: the whole matrix through its factor rows, the recurrences the
-// sweep kernels run.  Periodic matrices (Section 3.3): y = A'^{-1} d, then
-// x = y - (wt.d) z.
-void reference_solve(int kind, bool periodic, int64_t n, const double *bands, std::vector<double> &x) {
-    auto cf = [&](int k, int64_t i) -> double {
-        if (periodic) return bands[(int64_t)k * n + i];
-        const int64_t col = i + k - kind / 2;
-        return (col < 0 || col >= n) ? 0.0 : bands[(int64_t)k * n + i];
-    };
-    int64_t bad = -1;
-    if (periodic) {
-        std::vector<PeriodicRow<double>> r(n);
-        std::vector<TriRow<double>> t(n);
-        if (!factor_periodic_rows(n, cf, r.data(), &bad)) return;
-        double acc = 0.0;
-        for (int64_t i = 0; i < n; ++i) {
-            t[i] = {r[i].a_s, r[i].chat, r[i].inv, 0.0};
-            acc += r[i].wt * x[i];
+// sweep kernels run, factored once.  Periodic matrices (Section 3.3):
+// y = A'^{-1} d, then x = y - (wt.d) z.
+struct Reference {
+    bool periodic, ok = false;
+    int64_t n;
+    std::vector<PeriodicRow<double>> per;
+    std::vector<TriRow<double>> tri;
+    std::vector<PentaRow<double>> penta;
+
+    Reference(int kind, bool periodic_, int64_t n_, const double *bands) : periodic(periodic_), n(n_) {
+        auto cf = [&](int k, int64_t i) -> double {
+            if (periodic) return bands[(int64_t)k * n + i];
+            const int64_t col = i + k - kind / 2;
+            return (col < 0 || col >= n) ? 0.0 : bands[(int64_t)k * n + i];
+        };
+        int64_t bad = -1;
+        if (periodic) {
+            per.resize(n);
+            tri.resize(n);
+            ok = factor_periodic_rows(n, cf, per.data(), &bad);
+            for (int64_t i = 0; i < n && ok; ++i) tri[i] = {per[i].a_s, per[i].chat, per[i].inv, 0.0};
+        } else if (kind == SBS_TRI) {
+            tri.resize(n);
+            ok = factor_tri_rows(n, cf, tri.data(), &bad);
+        } else {
+            penta.resize(n);
+            ok = factor_penta_rows(n, cf, penta.data(), &bad);
         }
-        solve_tri_rows(n, t.data(), x.data());
-        for (int64_t i = 0; i < n; ++i) x[i] -= acc * r[i].z;
-    } else if (kind == SBS_TRI) {
-        std::vector<TriRow<double>> r(n);
-        if (factor_tri_rows(n, cf, r.data(), &bad)) solve_tri_rows(n, r.data(), x.data());
-    } else {
-        std::vector<PentaRow<double>> r(n);
-        if (factor_penta_rows(n, cf, r.data(), &bad)) solve_penta_rows(n, r.data(), x.data());
     }
-}
+    void operator()(std::vector<double> &x) const {
+        if (!ok) return;
+        if (!penta.empty()) return solve_penta_rows(n, penta.data(), x.data());
+        double acc = 0.0;
+        if (periodic)
+            for (int64_t i = 0; i < n; ++i) acc += per[i].wt * x[i];
+        solve_tri_rows(n, tri.data(), x.data());
+        if (periodic)
+            for (int64_t i = 0; i < n; ++i) x[i] -= acc * per[i].z;
+    }
+};
 
 // The plan's own solve of one column, as the kernel runs it: block solves,
 // interface unknowns from the stored inverse, correction.
@@ -156,32 +173,68 @@ void plan_solve(const HostPlan &hp, int h, bool periodic, int64_t n, SolveFn sol
     }
 }
 
-template <typename Row, typename SolveFn>
-double plan_deviation(const HostPlan &hp, int kind, bool periodic, int64_t n, const double *bands, SolveFn solve) {
+// The right-hand sides of the gate, their solutions by the recurrences, and
+// the x that a right-hand side was formed from (empty for the uniform ones);
+// one of these serves every plan of a matrix.
+struct Gate {
+    std::vector<std::vector<double>> d, x, from;
+};
+
+Gate make_gate(int kind, bool periodic, int64_t n, const double *bands) {
     const int h = kind / 2;
+    const Reference ref(kind, periodic, n, bands);
     uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
-    double worst = 0.0;
-    std::vector<double> d(n), a, b;
-    for (int q = 0; q < kPlanChecks; ++q) {
+    Gate g;
+    for (int q = 0; q < kUniformChecks + kScaledChecks; ++q) {
+        std::vector<double> v(n);
         for (int64_t i = 0; i < n; ++i) {
             st ^= st << 13;
             st ^= st >> 7;
             st ^= st << 17;
-            d[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
+            v[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
         }
-        a = d;
-        b = d;
-        reference_solve(kind, periodic, n, bands, a);
-        plan_solve<Row>(hp, h, periodic, n, solve, b);
-        double num = 0.0, den = 0.0;
-        for (int64_t i = 0; i < n; ++i) {
-            num = std::max(num, std::fabs(b[i] - a[i]));
-            den = std::max(den, std::fabs(a[i]));
+        if (q >= kUniformChecks) {
+            std::vector<double> ax(n, 0.0);
+            for (int64_t i = 0; i < n; ++i)
+                for (int k = 0; k < 2 * h + 1; ++k) {
+                    const int64_t col = i + k - h;
+                    if (periodic || (col >= 0 && col < n)) ax[i] += bands[(int64_t)k * n + i] * v[(col + n) % n];
+                }
+            g.from.push_back(v);
+            v.swap(ax);
+        } else {
+            g.from.emplace_back();
         }
-        const double e = den > 0.0 ? num / den : num;
-        if (!(e <= worst)) worst = e;  // a NaN stays
+        g.d.push_back(v);
+        ref(v);
+        g.x.push_back(std::move(v));
     }
-    return worst;
+    return g;
+}
+
+// The relative difference of b from a; NaN if any entry's is.
+double relative_difference(const std::vector<double> &b, const std::vector<double> &a) {
+    double num = 0.0, den = 0.0;
+    for (size_t i = 0; i < a.size(); ++i) {
+        const double e = std::fabs(b[i] - a[i]);
+        if (!(e <= num)) num = e;
+        if (std::isnan(num)) break;
+        den = std::max(den, std::fabs(a[i]));
+    }
+    return den > 0.0 ? num / den : num;
+}
+
+// Whether a plan's solutions (`plan`, in place on one column) are the gate's.
+template <typename PlanSolve>
+bool passes(const Gate &g, PlanSolve plan) {
+    std::vector<double> b;
+    for (size_t q = 0; q < g.d.size(); ++q) {
+        b = g.d[q];
+        plan(b);
+        if (relative_difference(b, g.x[q]) <= kPlanTolerance) continue;
+        if (g.from[q].empty() || !(relative_difference(b, g.from[q]) <= kPlanTolerance)) return false;
+    }
+    return true;
 }
 
 // kind is 3 or 5 (the bandwidth); `periodic` wraps a tridiagonal matrix
@@ -190,7 +243,7 @@ double plan_deviation(const HostPlan &hp, int kind, bool periodic, int64_t n, co
 // P-1's right neighbour is block 0, and the interface system gains that pair.
 template <typename Row, typename FactorFn, typename SolveFn>
 bool build_plan(int kind, bool periodic, int64_t n, const double *bands, int lb, FactorFn factor, SolveFn solve,
-                HostPlan &hp) {
+                const Gate &gate, HostPlan &hp) {
     const int h = kind / 2;
     const int P = (int)((n + lb - 1) / lb);
     const int pairs = periodic ? P : P - 1;
@@ -296,8 +349,7 @@ bool build_plan(int kind, bool periodic, int64_t n, const double *bands, int lb,
         }
     }
     hp.rinv.swap(R);
-    const double dev = plan_deviation<Row>(hp, kind, periodic, n, bands, solve);
-    return dev <= kPlanTolerance;
+    return passes(gate, [&](std::vector<double> &x) { plan_solve<Row>(hp, h, periodic, n, solve, x); });
 }
 
 // ---------------------------------------------------------------------------
@@ -426,41 +478,12 @@ void sep_plan_solve(const SepHostPlan &hp, int h, bool periodic, int64_t n, Solv
     }
 }
 
-template <typename Row, typename SolveFn>
-double sep_plan_deviation(const SepHostPlan &hp, int kind, bool periodic, int64_t n, const double *bands,
-                          SolveFn solve, int checks) {
-    const int h = kind / 2;
-    uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
-    double worst = 0.0;
-    std::vector<double> d(n), a, b;
-    for (int q = 0; q < checks; ++q) {
-        for (int64_t i = 0; i < n; ++i) {
-            st ^= st << 13;
-            st ^= st >> 7;
-            st ^= st << 17;
-            d[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
-        }
-        a = d;
-        b = d;
-        reference_solve(kind, periodic, n, bands, a);
-        sep_plan_solve<Row>(hp, h, periodic, n, solve, b);
-        double num = 0.0, den = 0.0;
-        for (int64_t i = 0; i < n; ++i) {
-            num = std::max(num, std::fabs(b[i] - a[i]));
-            den = std::max(den, std::fabs(a[i]));
-        }
-        const double e = den > 0.0 ? num / den : num;
-        if (!(e <= worst)) worst = e;  // a NaN stays
-    }
-    return worst;
-}
-
 // kind 3 or 5; `periodic` wraps a tridiagonal matrix round (needs n a whole
-// number P >= 2 of blocks; every block then has a separator).  checks: seeded
-// right-hand sides of the accuracy gate (0: the caller checks the whole).
+// number P >= 2 of blocks; every block then has a separator).  gate: the
+// accuracy gate (null: the caller checks the whole).
 template <typename Row, typename FactorFn, typename SolveFn>
 bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int lb, FactorFn factor, SolveFn solve,
-                    SepHostPlan &hp, int checks = kPlanChecks) {
+                    const Gate *gate, SepHostPlan &hp) {
     const int h = kind / 2, nb = 2 * h + 1;
     const int P = (int)((n + lb - 1) / lb);
     if (periodic && (n % lb != 0 || P < 2)) return false;
@@ -591,7 +614,7 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
         }
     }
     hp.sinv.swap(S);
-    return sep_plan_deviation<Row>(hp, kind, periodic, n, bands, solve, checks) <= kPlanTolerance;
+    return !gate || passes(*gate, [&](std::vector<double> &x) { sep_plan_solve<Row>(hp, h, periodic, n, solve, x); });
 }
 
 template <typename Row32, typename Row64>
@@ -870,7 +893,8 @@ std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, Fa
         for (int64_t k = 0; k < ns; ++k) {
             HostSeg &s = segs[k];
             if (s.same >= 0) continue;
-            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, s.hp, 1)) {
+            const Gate gate = make_gate(kind, false, s.hi - s.lo, sub[k].data());
+            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, &gate, s.hp)) {
                 ok = false;
                 break;
             }
@@ -1027,7 +1051,8 @@ std::vector<HostCutSeg> lay_cuts(int h, bool periodic, int64_t n, int64_t run) {
 // on either side.  False if a window is too wide, a plan is missing, or the
 // result is not the recurrences' within kPlanTolerance.
 template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
-bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorFn factor, SolveFn solve, HostCuts &hc) {
+bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorFn factor, SolveFn solve,
+                const Gate &gate, HostCuts &hc) {
     const int h = kind / 2;
     const int64_t Q = (n + h + kCutRows + h - 1) / (kCutRows + h);
     if (Q < 2 || Q > kMaxCutSegs || (periodic && n < 2 * kCutNear + 2)) return false;
@@ -1082,28 +1107,10 @@ bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorF
         for (size_t q = 0; q + 1 < sub.size() && s.same < 0; ++q)
             if (hc.segs[q].same < 0 && sub[q] == sub.back()) s.same = (int)q;
         if (s.same < 0 &&
-            !build_sep_plan<Row>(kind, false, s.b - s.a, sub.back().data(), kSegLb, factor, solve, s.hp, 0))
+            !build_sep_plan<Row>(kind, false, s.b - s.a, sub.back().data(), kSegLb, factor, solve, nullptr, s.hp))
             return false;
     }
-    uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
-    std::vector<double> d(n), x;
-    for (int64_t i = 0; i < n; ++i) {
-        st ^= st << 13;
-        st ^= st >> 7;
-        st ^= st << 17;
-        d[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
-    }
-    x = d;
-    reference_solve(kind, periodic, n, bands, d);
-    cut_solve<Row>(hc, kind, n, bands, solve, x);
-    double num = 0.0, den = 0.0;
-    bool nan = false;
-    for (int64_t i = 0; i < n; ++i) {
-        nan |= std::isnan(x[i]);
-        num = std::max(num, std::fabs(x[i] - d[i]));
-        den = std::max(den, std::fabs(d[i]));
-    }
-    if (nan || !(num <= kPlanTolerance * den)) return false;
+    if (!passes(gate, [&](std::vector<double> &x) { cut_solve<Row>(hc, kind, n, bands, solve, x); })) return false;
     for (HostCutSeg &s : hc.segs)
         if (s.same < 0) serialise_sep<Row, Row32>(s.hp, s.b64, s.b32, s.sp);
     return true;
@@ -1142,14 +1149,20 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     // plain tridiagonal; the wrap is one more interface pair).
     const bool periodic = h->kind == SBS_TRI_PERIODIC;
     const bool tri = h->kind == SBS_TRI || periodic;
+    // (longer matrices have no plan of the whole and no cut form)
+    const Gate gate = h->n <= (int64_t)kMaxCutSegs * (kCutRows + 2)
+                          ? make_gate(tri ? SBS_TRI : SBS_PENTA, periodic, h->n, bands)
+                          : Gate();
     for (int q = 0; q < 3; ++q) {
         HostPlan hp;
         const int lb = kPartLbs[q];
         bool ok;
         if (tri)
-            ok = build_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, hp);
+            ok = build_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, gate,
+                                            hp);
         else
-            ok = build_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows, hp);
+            ok = build_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows, gate,
+                                              hp);
         if (!ok) continue;
         PartPlan &pp = h->part[q];
         pp.periodic = periodic;
@@ -1168,10 +1181,11 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
         const int lb = kPartLbs[q];
         bool ok;
         if (tri)
-            ok = build_sep_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, hp);
+            ok = build_sep_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, &gate,
+                                                hp);
         else
             ok = build_sep_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows,
-                                                  hp);
+                                                  &gate, hp);
         if (!ok) continue;
         SepPlan &sp = h->sep[q];
         sp.periodic = periodic;
@@ -1212,9 +1226,9 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     HostCuts hc;
     if (h->n > kCutRows) {
         const bool ok = tri ? build_cuts<TriRow<double>, TriRow<float>>(SBS_TRI, periodic, h->n, bands, FactorTri{},
-                                                                        solve_tri_rows, hc)
-                            : build_cuts<PentaRow<double>, PentaRow<float>>(SBS_PENTA, false, h->n, bands,
-                                                                            FactorPenta{}, solve_penta_rows, hc);
+                                                                        solve_tri_rows, gate, hc)
+                            : build_cuts<PentaRow<double>, PentaRow<float>>(SBS_PENTA, false, h->n, bands, FactorPenta{},
+                                                                            solve_penta_rows, gate, hc);
         if (!ok) hc = HostCuts();
     }
     for (const HostCutSeg &s : hc.segs) total += align256(s.b64.size()) + align256(s.b32.size());

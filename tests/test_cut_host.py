@@ -177,3 +177,27 @@ def test_scaled_rows_in_separator_plans(part_exe, tmp_path, kind, n, which, K):
                 found += 1
                 assert colrel(got, x) <= 2e-14, (lb, r, colrel(got, x))
         assert found >= 2
+
+
+# Tiny pivots at the rows that start a 16-row block: the recurrences on the
+# whole matrix never meet them, a plan cut there loses digits.  Where those rows
+# are large, a right-hand side that is uniform in every row leaves their
+# unknowns too small to tell; A x of a uniform x does not.
+def tiny_pivots_in_large_rows(n, rows, K):
+    B = P.tiny_block_pivot_bands(n)
+    B[1, 16::16] = np.where(np.arange(16, n, 16) < rows, 1e-9, 3.0)
+    B[:, :rows] *= K
+    return B
+
+
+@pytest.mark.parametrize("n", [256, 1000, 2600])
+def test_plans_that_lose_the_unknowns_of_large_rows_are_dropped(exe, part_exe, tmp_path, n):
+    B = tiny_pivots_in_large_rows(n, min(n // 2, 200), 1e14)
+    x = np.random.default_rng(n).uniform(-1, 1, (n, 2))
+    b = matvec(3, B, x)
+    assert colrel(oracle.solve(3, B, b), x) <= 2e-13
+    (Q, _, got), (nseg, y) = run(exe, tmp_path, 3, B, b)
+    plans, seps = P.run_all(part_exe, tmp_path, 3, B, b)
+    for lb, *_, z in [(Q, got)] + plans + seps:
+        if lb:
+            assert colrel(z, x) <= 2e-13, lb
