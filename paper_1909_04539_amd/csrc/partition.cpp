@@ -17,10 +17,13 @@ constexpr int kMaxInterface = 90;  // interface unknowns: the FP64 inverse stays
 size_t align16(size_t v) { return (v + 15) / 16 * 16; }
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }  // each blob starts as a device allocation would
 
-// Gauss-Jordan inverse with partial pivoting, in place (row-major n x n).
+// Gauss-Jordan inverse with partial pivoting, in place (row-major n x n).  Row
+// c of `a` is 0 before column c when it is used, and that of `inv` after the
+// last column that a pivot has reached (`last`).
 bool invert(std::vector<double> &a, int n) {
     std::vector<double> inv((size_t)n * n, 0.0);
     for (int i = 0; i < n; ++i) inv[(size_t)i * n + i] = 1.0;
+    int last = 0;
     for (int c = 0; c < n; ++c) {
         int piv = c;
         for (int r = c + 1; r < n; ++r)
@@ -32,19 +35,18 @@ bool invert(std::vector<double> &a, int n) {
                 std::swap(a[(size_t)piv * n + k], a[(size_t)c * n + k]);
                 std::swap(inv[(size_t)piv * n + k], inv[(size_t)c * n + k]);
             }
+        last = std::max(last, piv);
         const double s = 1.0 / pv;
-        for (int k = 0; k < n; ++k) {
-            a[(size_t)c * n + k] *= s;
-            inv[(size_t)c * n + k] *= s;
-        }
+        double *ac = a.data() + (size_t)c * n, *ic = inv.data() + (size_t)c * n;
+        for (int k = c; k < n; ++k) ac[k] *= s;
+        for (int k = 0; k <= last; ++k) ic[k] *= s;
         for (int r = 0; r < n; ++r) {
             if (r == c) continue;
-            const double f = a[(size_t)r * n + c];
+            double *ar = a.data() + (size_t)r * n, *ir = inv.data() + (size_t)r * n;
+            const double f = ar[c];
             if (f == 0.0) continue;
-            for (int k = 0; k < n; ++k) {
-                a[(size_t)r * n + k] -= f * a[(size_t)c * n + k];
-                inv[(size_t)r * n + k] -= f * inv[(size_t)c * n + k];
-            }
+            for (int k = c; k < n; ++k) ar[k] -= f * ac[k];
+            for (int k = 0; k <= last; ++k) ir[k] -= f * ic[k];
         }
     }
     for (double v : inv)
@@ -53,18 +55,54 @@ bool invert(std::vector<double> &a, int n) {
     return true;
 }
 
-// The factorisations as values, whatever their coefficients come from (their
-// coefficient reads are inlined).
-struct FactorTri {
+// A bandwidth's factorisation and its solve of NC columns at once (x is
+// [n][NC]; each column is solved as solve_tri_rows / solve_penta_rows solve it.
+// One column is a chain of dependent operations, several fill the time between
+// them).
+struct Tri {
+    using Row = TriRow<double>;
+    using Row32 = TriRow<float>;
+    static constexpr int kind = SBS_TRI, h = 1;
     template <class Coef>
-    bool operator()(int64_t n, Coef coef, TriRow<double> *rows, int64_t *bad) const {
+    static bool factor(int64_t n, Coef coef, Row *rows, int64_t *bad) {
         return factor_tri_rows(n, coef, rows, bad);
     }
+    template <int NC>
+    static void solve(int64_t n, const Row *r, double *x) {
+        double y[NC] = {};
+        for (int64_t i = 0; i < n; ++i)
+            for (int c = 0; c < NC; ++c) y[c] = x[i * NC + c] = x[i * NC + c] * r[i].inv - r[i].a_s * y[c];
+        for (int c = 0; c < NC; ++c) y[c] = 0.0;
+        for (int64_t i = n - 1; i >= 0; --i)
+            for (int c = 0; c < NC; ++c) y[c] = x[i * NC + c] = x[i * NC + c] - r[i].chat * y[c];
+    }
 };
-struct FactorPenta {
+struct Penta {
+    using Row = PentaRow<double>;
+    using Row32 = PentaRow<float>;
+    static constexpr int kind = SBS_PENTA, h = 2;
     template <class Coef>
-    bool operator()(int64_t n, Coef coef, PentaRow<double> *rows, int64_t *bad) const {
+    static bool factor(int64_t n, Coef coef, Row *rows, int64_t *bad) {
         return factor_penta_rows(n, coef, rows, bad);
+    }
+    template <int NC>
+    static void solve(int64_t n, const Row *r, double *x) {
+        double y1[NC] = {}, y2[NC] = {};
+        for (int64_t i = 0; i < n; ++i)
+            for (int c = 0; c < NC; ++c) {
+                const double g = x[i * NC + c] * r[i].inv - r[i].eps_s * y2[c] - r[i].beta_s * y1[c];
+                x[i * NC + c] = g;
+                y2[c] = y1[c];
+                y1[c] = g;
+            }
+        for (int c = 0; c < NC; ++c) y1[c] = y2[c] = 0.0;
+        for (int64_t i = n - 1; i >= 0; --i)
+            for (int c = 0; c < NC; ++c) {
+                const double v = x[i * NC + c] - r[i].gamma * y1[c] - r[i].delta * y2[c];
+                x[i * NC + c] = v;
+                y2[c] = y1[c];
+                y1[c] = v;
+            }
     }
 };
 
@@ -92,159 +130,142 @@ struct HostPlan {
 // that x instead (the periodic recurrences lose digits of their own where the
 // first row is large).
 constexpr double kPlanTolerance = 1e-13;
-constexpr int kUniformChecks = 4, kScaledChecks = 2;
+constexpr int kUniformChecks = 4, kChecks = 6;  // right-hand sides: uniform ones, all
 
-// Reference: the whole matrix through its factor rows, the recurrences the
-// sweep kernels run, factored once.  Periodic matrices (Section 3.3):
-// y = A'^{-1} d, then x = y - (wt.d) z.
-struct Reference {
-    bool periodic, ok = false;
-    int64_t n;
-    std::vector<PeriodicRow<double>> per;
-    std::vector<TriRow<double>> tri;
-    std::vector<PentaRow<double>> penta;
+using Columns = std::vector<double>;  // [n][kChecks]
 
-    Reference(int kind, bool periodic_, int64_t n_, const double *bands) : periodic(periodic_), n(n_) {
-        auto cf = [&](int k, int64_t i) -> double {
-            if (periodic) return bands[(int64_t)k * n + i];
-            const int64_t col = i + k - kind / 2;
-            return (col < 0 || col >= n) ? 0.0 : bands[(int64_t)k * n + i];
-        };
-        int64_t bad = -1;
-        if (periodic) {
-            per.resize(n);
-            tri.resize(n);
-            ok = factor_periodic_rows(n, cf, per.data(), &bad);
-            for (int64_t i = 0; i < n && ok; ++i) tri[i] = {per[i].a_s, per[i].chat, per[i].inv, 0.0};
-        } else if (kind == SBS_TRI) {
-            tri.resize(n);
-            ok = factor_tri_rows(n, cf, tri.data(), &bad);
-        } else {
-            penta.resize(n);
-            ok = factor_penta_rows(n, cf, penta.data(), &bad);
-        }
-    }
-    void operator()(std::vector<double> &x) const {
-        if (!ok) return;
-        if (!penta.empty()) return solve_penta_rows(n, penta.data(), x.data());
-        double acc = 0.0;
-        if (periodic)
-            for (int64_t i = 0; i < n; ++i) acc += per[i].wt * x[i];
-        solve_tri_rows(n, tri.data(), x.data());
-        if (periodic)
-            for (int64_t i = 0; i < n; ++i) x[i] -= acc * per[i].z;
-    }
-};
-
-// The plan's own solve of one column, as the kernel runs it: block solves,
-// interface unknowns from the stored inverse, correction.
-template <typename Row, typename SolveFn>
-void plan_solve(const HostPlan &hp, int h, bool periodic, int64_t n, SolveFn solve, std::vector<double> &x) {
-    const int lb = hp.lb, P = hp.P, Nr = hp.Nr;
-    const Row *fac = reinterpret_cast<const Row *>(hp.fac.data());
-    std::vector<double> g((size_t)P * lb, 0.0), y(Nr > 0 ? Nr : 1, 0.0);
-    for (int64_t i = 0; i < n; ++i) g[i] = x[i];
-    for (int p = 0; p < P; ++p) solve(lb, fac + (int64_t)hp.map[p] * lb, g.data() + (int64_t)p * lb);
-    auto has_next = [&](int p) { return periodic || p <= P - 2; };
-    auto has_prev = [&](int p) { return periodic || p >= 1; };
-    auto prev = [&](int p) { return p == 0 ? P - 1 : p - 1; };
-    for (int p = 0; p < P; ++p) {
-        if (has_next(p))
-            for (int c = 0; c < h; ++c) y[2 * h * p + c] = g[(int64_t)p * lb + lb - h + c];
-        if (has_prev(p))
-            for (int c = 0; c < h; ++c) y[2 * h * prev(p) + h + c] = g[(int64_t)p * lb + c];
-    }
-    for (int p = 0; p < P; ++p) {
-        double xt[2] = {0.0, 0.0}, xb[2] = {0.0, 0.0};
-        for (int c = 0; c < h; ++c)
-            for (int k = 0; k < Nr; ++k) {
-                if (has_next(p)) xt[c] += hp.rinv[(size_t)(2 * h * p + h + c) * Nr + k] * y[k];
-                if (has_prev(p)) xb[c] += hp.rinv[(size_t)(2 * h * prev(p) + c) * Nr + k] * y[k];
-            }
-        const double *sp = hp.spk.data() + (size_t)hp.map[p] * lb * 2 * h;
-        for (int t = 0; t < lb; ++t) {
-            const int64_t i = (int64_t)p * lb + t;
-            if (i >= n) break;
-            double v = g[i];
-            for (int c = 0; c < h; ++c) v -= sp[t * 2 * h + c] * xt[c];
-            for (int c = 0; c < h; ++c) v -= sp[t * 2 * h + h + c] * xb[c];
-            x[i] = v;
-        }
-    }
-}
-
-// The right-hand sides of the gate, their solutions by the recurrences, and
-// the x that a right-hand side was formed from (empty for the uniform ones);
-// one of these serves every plan of a matrix.
+// The right-hand sides of the gate, their solutions by the recurrences that
+// the sweep kernels run, on the whole matrix (Section 3.3 for a periodic one:
+// y = A'^{-1} d, then x = y - (wt.d) z), and the x that right-hand side q was
+// formed from (q >= kUniformChecks); one of these serves every plan of a matrix.
 struct Gate {
-    std::vector<std::vector<double>> d, x, from;
+    Columns d, x, from;
 };
 
-Gate make_gate(int kind, bool periodic, int64_t n, const double *bands) {
-    const int h = kind / 2;
-    const Reference ref(kind, periodic, n, bands);
+template <class M>
+Gate make_gate(bool periodic, int64_t n, const double *bands) {
+    constexpr int h = M::h;
     uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
     Gate g;
-    for (int q = 0; q < kUniformChecks + kScaledChecks; ++q) {
-        std::vector<double> v(n);
+    g.from.resize((size_t)n * kChecks);
+    for (int q = 0; q < kChecks; ++q)
         for (int64_t i = 0; i < n; ++i) {
             st ^= st << 13;
             st ^= st >> 7;
             st ^= st << 17;
-            v[i] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
+            g.from[i * kChecks + q] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
         }
-        if (q >= kUniformChecks) {
-            std::vector<double> ax(n, 0.0);
+    g.d = g.from;
+    for (int64_t i = 0; i < n; ++i)
+        for (int q = kUniformChecks; q < kChecks; ++q) {
+            double ax = 0.0;
+            for (int k = 0; k < 2 * h + 1; ++k) {
+                int64_t col = i + k - h;
+                if (periodic) col = col < 0 ? col + n : col >= n ? col - n : col;
+                if (col >= 0 && col < n) ax += bands[(int64_t)k * n + i] * g.from[col * kChecks + q];
+            }
+            g.d[i * kChecks + q] = ax;
+        }
+    g.x = g.d;
+    auto cf = [&](int k, int64_t i) -> double {
+        const int64_t col = i + k - h;
+        return !periodic && (col < 0 || col >= n) ? 0.0 : bands[(int64_t)k * n + i];
+    };
+    int64_t bad = -1;
+    std::vector<typename M::Row> rows(n);
+    if constexpr (M::kind == SBS_TRI)
+        if (periodic) {
+            std::vector<PeriodicRow<double>> r(n);
+            if (!factor_periodic_rows(n, cf, r.data(), &bad)) return g;
+            double acc[kChecks] = {};
+            for (int64_t i = 0; i < n; ++i) {
+                rows[i] = {r[i].a_s, r[i].chat, r[i].inv, 0.0};
+                for (int q = 0; q < kChecks; ++q) acc[q] += r[i].wt * g.x[i * kChecks + q];
+            }
+            M::template solve<kChecks>(n, rows.data(), g.x.data());
             for (int64_t i = 0; i < n; ++i)
-                for (int k = 0; k < 2 * h + 1; ++k) {
-                    const int64_t col = i + k - h;
-                    if (periodic || (col >= 0 && col < n)) ax[i] += bands[(int64_t)k * n + i] * v[(col + n) % n];
-                }
-            g.from.push_back(v);
-            v.swap(ax);
-        } else {
-            g.from.emplace_back();
+                for (int q = 0; q < kChecks; ++q) g.x[i * kChecks + q] -= acc[q] * r[i].z;
+            return g;
         }
-        g.d.push_back(v);
-        ref(v);
-        g.x.push_back(std::move(v));
-    }
+    if (M::factor(n, cf, rows.data(), &bad)) M::template solve<kChecks>(n, rows.data(), g.x.data());
     return g;
 }
 
-// The relative difference of b from a; NaN if any entry's is.
-double relative_difference(const std::vector<double> &b, const std::vector<double> &a) {
-    double num = 0.0, den = 0.0;
-    for (size_t i = 0; i < a.size(); ++i) {
-        const double e = std::fabs(b[i] - a[i]);
-        if (!(e <= num)) num = e;
-        if (std::isnan(num)) break;
-        den = std::max(den, std::fabs(a[i]));
-    }
-    return den > 0.0 ? num / den : num;
-}
-
-// Whether a plan's solutions (`plan`, in place on one column) are the gate's.
+// Whether a plan's solutions (`plan`, in place) are the gate's; a NaN is not.
 template <typename PlanSolve>
 bool passes(const Gate &g, PlanSolve plan) {
-    std::vector<double> b;
-    for (size_t q = 0; q < g.d.size(); ++q) {
-        b = g.d[q];
-        plan(b);
-        if (relative_difference(b, g.x[q]) <= kPlanTolerance) continue;
-        if (g.from[q].empty() || !(relative_difference(b, g.from[q]) <= kPlanTolerance)) return false;
-    }
-    return true;
+    Columns b = g.d;
+    plan(b);
+    double num[kChecks] = {}, den[kChecks] = {}, fnum[kChecks] = {}, fden[kChecks] = {};
+    bool nan = false;
+    for (size_t i = 0; i < b.size(); i += kChecks)
+        for (int q = 0; q < kChecks; ++q) {
+            nan |= std::isnan(b[i + q]);
+            num[q] = std::max(num[q], std::fabs(b[i + q] - g.x[i + q]));
+            den[q] = std::max(den[q], std::fabs(g.x[i + q]));
+            fnum[q] = std::max(fnum[q], std::fabs(b[i + q] - g.from[i + q]));
+            fden[q] = std::max(fden[q], std::fabs(g.from[i + q]));
+        }
+    for (int q = 0; q < kChecks; ++q)
+        if (!(num[q] <= kPlanTolerance * den[q]) && !(q >= kUniformChecks && fnum[q] <= kPlanTolerance * fden[q]))
+            return false;
+    return !nan;
 }
 
-// kind is 3 or 5 (the bandwidth); `periodic` wraps a tridiagonal matrix
+// The plan's own solve of the gate's columns, as the kernel runs it: block
+// solves, interface unknowns from the stored inverse, correction.
+template <class M>
+void plan_solve(const HostPlan &hp, bool periodic, int64_t n, Columns &x) {
+    constexpr int h = M::h, C = kChecks;
+    const int lb = hp.lb, P = hp.P, Nr = hp.Nr;
+    const auto *fac = reinterpret_cast<const typename M::Row *>(hp.fac.data());
+    std::vector<double> g((size_t)P * lb * C, 0.0), y((size_t)std::max(Nr, 1) * C, 0.0);
+    std::copy(x.begin(), x.end(), g.begin());
+    for (int p = 0; p < P; ++p)
+        M::template solve<C>(lb, fac + (int64_t)hp.map[p] * lb, g.data() + (int64_t)p * lb * C);
+    auto has_next = [&](int p) { return periodic || p <= P - 2; };
+    auto has_prev = [&](int p) { return periodic || p >= 1; };
+    auto prev = [&](int p) { return p == 0 ? P - 1 : p - 1; };
+    for (int p = 0; p < P; ++p)
+        for (int c = 0; c < h; ++c)
+            for (int q = 0; q < C; ++q) {
+                if (has_next(p)) y[(2 * h * p + c) * C + q] = g[((int64_t)p * lb + lb - h + c) * C + q];
+                if (has_prev(p)) y[(2 * h * prev(p) + h + c) * C + q] = g[((int64_t)p * lb + c) * C + q];
+            }
+    for (int p = 0; p < P; ++p) {
+        double xt[2][C] = {}, xb[2][C] = {};
+        for (int c = 0; c < h; ++c) {
+            if (has_next(p))
+                for (int k = 0; k < Nr; ++k)
+                    for (int q = 0; q < C; ++q)
+                        xt[c][q] += hp.rinv[(size_t)(2 * h * p + h + c) * Nr + k] * y[(size_t)k * C + q];
+            if (has_prev(p))
+                for (int k = 0; k < Nr; ++k)
+                    for (int q = 0; q < C; ++q)
+                        xb[c][q] += hp.rinv[(size_t)(2 * h * prev(p) + c) * Nr + k] * y[(size_t)k * C + q];
+        }
+        const double *sp = hp.spk.data() + (size_t)hp.map[p] * lb * 2 * h;
+        for (int t = 0; t < lb; ++t) {
+            const int64_t i = (int64_t)p * lb + t;
+            if (i >= n) break;
+            for (int q = 0; q < C; ++q) {
+                double v = g[i * C + q];
+                for (int c = 0; c < h; ++c) v -= sp[t * 2 * h + c] * xt[c][q];
+                for (int c = 0; c < h; ++c) v -= sp[t * 2 * h + h + c] * xb[c][q];
+                x[i * C + q] = v;
+            }
+        }
+    }
+}
+
+// `periodic` wraps a tridiagonal matrix
 // round (row 0 couples to row n-1 and back), which needs n to be a whole
 // number of blocks: then block 0's left neighbour is block P-1 and block
 // P-1's right neighbour is block 0, and the interface system gains that pair.
-template <typename Row, typename FactorFn, typename SolveFn>
-bool build_plan(int kind, bool periodic, int64_t n, const double *bands, int lb, FactorFn factor, SolveFn solve,
-                const Gate &gate, HostPlan &hp) {
-    const int h = kind / 2;
+template <class M>
+bool build_plan(bool periodic, int64_t n, const double *bands, int lb, const Gate &gate, HostPlan &hp) {
+    using Row = typename M::Row;
+    constexpr int h = M::h;
     const int P = (int)((n + lb - 1) / lb);
     const int pairs = periodic ? P : P - 1;
     if (P > kMaxBlocks || lb < 2 * h || 2 * h * pairs > kMaxInterface) return false;
@@ -271,25 +292,20 @@ bool build_plan(int kind, bool periodic, int64_t n, const double *bands, int lb,
         }
         return (d >= -h && d <= h) ? bands[(int64_t)(d + h) * n + i] : 0.0;
     };
-    std::vector<double> v(lb);
     for (int p = 0; p < P; ++p) {
         const int64_t r0 = (int64_t)p * lb;
         int64_t bad = -1;
-        if (!factor(lb, [&](int k, int64_t t) { return local(p, k, r0 + t); }, rows.data() + r0, &bad)) return false;
-        // Right spike columns: coupling of row r0+t to column r0+lb+c
-        // (block p+1's first unknowns; none past the last block unless periodic).
-        for (int c = 0; c < h; ++c) {
-            for (int t = 0; t < lb; ++t)
-                v[t] = (p < P - 1 || periodic) ? entry(r0 + t, r0 + lb + c) : 0.0;
-            solve(lb, rows.data() + r0, v.data());
-            for (int t = 0; t < lb; ++t) spk[(size_t)(r0 + t) * 2 * h + c] = v[t];
-        }
-        // Left spike columns: coupling of row r0+t to column r0-h+c.
-        for (int c = 0; c < h; ++c) {
-            for (int t = 0; t < lb; ++t) v[t] = (p > 0 || periodic) ? entry(r0 + t, r0 - h + c) : 0.0;
-            solve(lb, rows.data() + r0, v.data());
-            for (int t = 0; t < lb; ++t) spk[(size_t)(r0 + t) * 2 * h + h + c] = v[t];
-        }
+        if (!M::factor(lb, [&](int k, int64_t t) { return local(p, k, r0 + t); }, rows.data() + r0, &bad)) return false;
+        double *v = spk.data() + (size_t)r0 * 2 * h;
+        for (int t = 0; t < lb; ++t)
+            for (int c = 0; c < h; ++c) {
+                // Right spike columns: coupling of row r0+t to column r0+lb+c
+                // (block p+1's first unknowns; none past the last block unless periodic).
+                if (p < P - 1 || periodic) v[t * 2 * h + c] = entry(r0 + t, r0 + lb + c);
+                // Left spike columns: coupling of row r0+t to column r0-h+c.
+                if (p > 0 || periodic) v[t * 2 * h + h + c] = entry(r0 + t, r0 - h + c);
+            }
+        M::template solve<2 * h>(lb, rows.data() + r0, v);
     }
     // Interface system.  Unknown order: pair q holds (bottom h of block q,
     // top h of block q+1), q = 0..P-2, and q = P-1 (block P-1, block 0) when
@@ -349,7 +365,7 @@ bool build_plan(int kind, bool periodic, int64_t n, const double *bands, int lb,
         }
     }
     hp.rinv.swap(R);
-    return passes(gate, [&](std::vector<double> &x) { plan_solve<Row>(hp, h, periodic, n, solve, x); });
+    return passes(gate, [&](Columns &x) { plan_solve<M>(hp, periodic, n, x); });
 }
 
 // ---------------------------------------------------------------------------
@@ -424,67 +440,65 @@ void sep_window(std::vector<double> &S, const std::vector<double> &scale, int Nr
     }
 }
 
-// The separator plan's own solve of one column, as the kernel runs it:
-// block sweeps (separator rows pass through unchanged), separator
-// right-hand sides yhat, separators z = S^{-1} yhat, interior correction.
-template <typename Row, typename SolveFn>
-void sep_plan_solve(const SepHostPlan &hp, int h, bool periodic, int64_t n, SolveFn solve, std::vector<double> &x) {
-    const int lb = hp.lb, P = hp.P, Nr = hp.Nr, nb = 2 * h + 1;
-    const Row *fac = reinterpret_cast<const Row *>(hp.fac.data());
+// The separator plan's own solve of the gate's columns (x: [n][kChecks]), as
+// the kernel runs it: block sweeps (separator rows pass through unchanged),
+// separator right-hand sides yhat, separators z = S^{-1} yhat, interior
+// correction.
+template <class M>
+void sep_plan_solve(const SepHostPlan &hp, bool periodic, int64_t n, double *x) {
+    constexpr int h = M::h, nb = 2 * h + 1, C = kChecks;
+    const int lb = hp.lb, P = hp.P, Nr = hp.Nr;
+    const auto *fac = reinterpret_cast<const typename M::Row *>(hp.fac.data());
     auto has_sep = [&](int p) { return periodic || p < P - 1; };
     auto has_prev = [&](int p) { return periodic || p >= 1; };
     auto prev = [&](int p) { return p == 0 ? P - 1 : p - 1; };
     auto next = [&](int p) { return p == P - 1 ? 0 : p + 1; };
-    std::vector<double> g((size_t)P * lb, 0.0), f = g, yh(Nr > 0 ? Nr : 1, 0.0), z = yh;
-    for (int64_t i = 0; i < n; ++i) f[i] = g[i] = x[i];
-    for (int p = 0; p < P; ++p) solve(lb, fac + (int64_t)hp.map[p] * lb, g.data() + (int64_t)p * lb);
+    std::vector<double> g((size_t)P * lb * C, 0.0), yh((size_t)std::max(Nr, 1) * C, 0.0), z = yh;
+    std::copy(x, x + n * C, g.begin());
+    for (int p = 0; p < P; ++p)
+        M::template solve<C>(lb, fac + (int64_t)hp.map[p] * lb, g.data() + (int64_t)p * lb * C);
     for (int p = 0; p < P; ++p) {
         if (!has_sep(p)) continue;
         const double *cf = hp.scf.data() + (size_t)hp.map[p] * h * nb;
         for (int c = 0; c < h; ++c) {
-            double v = f[(int64_t)p * lb + lb - h + c];
+            double *y = yh.data() + (size_t)(h * p + c) * C;
+            for (int q = 0; q < C; ++q) y[q] = x[((int64_t)p * lb + lb - h + c) * C + q];
             for (int d = 0; d < nb; ++d) {
                 const int t = lb - h + c + d - h;  // column, relative to the block's first row
-                double val = 0.0;
-                if (t < lb - h) val = g[(int64_t)p * lb + t];
-                else if (t >= lb) val = g[(int64_t)next(p) * lb + t - lb];
-                v -= cf[c * nb + d] * val;
+                if (t >= lb - h && t < lb) continue;
+                const double *v = g.data() + (t < lb ? (int64_t)p * lb + t : (int64_t)next(p) * lb + t - lb) * C;
+                for (int q = 0; q < C; ++q) y[q] -= cf[c * nb + d] * v[q];
             }
-            yh[h * p + c] = v;
         }
     }
-    for (int r = 0; r < Nr; ++r) {
-        double v = 0.0;
-        for (int k = 0; k < Nr; ++k) v += hp.sinv[(size_t)r * Nr + k] * yh[k];
-        z[r] = v;
-    }
+    for (int r = 0; r < Nr; ++r)
+        for (int k = 0; k < Nr; ++k)
+            for (int q = 0; q < C; ++q) z[(size_t)r * C + q] += hp.sinv[(size_t)r * Nr + k] * yh[(size_t)k * C + q];
     for (int p = 0; p < P; ++p) {
         const double *sp = hp.spk.data() + (size_t)hp.map[p] * lb * 2 * h;
         for (int t = 0; t < lb; ++t) {
             const int64_t i = (int64_t)p * lb + t;
             if (i >= n) break;
-            double v;
-            if (has_sep(p) && t >= lb - h) {
-                v = z[h * p + t - (lb - h)];
-            } else {
-                v = g[i];
-                for (int c = 0; c < h; ++c) {
-                    if (has_sep(p)) v -= sp[t * 2 * h + c] * z[h * p + c];
-                    if (has_prev(p)) v -= sp[t * 2 * h + h + c] * z[h * prev(p) + c];
+            const bool sep = has_sep(p) && t >= lb - h;
+            for (int q = 0; q < C; ++q) {
+                double v = sep ? z[(size_t)(h * p + t - (lb - h)) * C + q] : g[i * C + q];
+                for (int c = 0; c < h && !sep; ++c) {
+                    if (has_sep(p)) v -= sp[t * 2 * h + c] * z[(size_t)(h * p + c) * C + q];
+                    if (has_prev(p)) v -= sp[t * 2 * h + h + c] * z[(size_t)(h * prev(p) + c) * C + q];
                 }
+                x[i * C + q] = v;
             }
-            x[i] = v;
         }
     }
 }
 
-// kind 3 or 5; `periodic` wraps a tridiagonal matrix round (needs n a whole
+// `periodic` wraps a tridiagonal matrix round (needs n a whole
 // number P >= 2 of blocks; every block then has a separator).  gate: the
 // accuracy gate (null: the caller checks the whole).
-template <typename Row, typename FactorFn, typename SolveFn>
-bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int lb, FactorFn factor, SolveFn solve,
-                    const Gate *gate, SepHostPlan &hp) {
-    const int h = kind / 2, nb = 2 * h + 1;
+template <class M>
+bool build_sep_plan(bool periodic, int64_t n, const double *bands, int lb, const Gate *gate, SepHostPlan &hp) {
+    using Row = typename M::Row;
+    constexpr int h = M::h, nb = 2 * h + 1;
     const int P = (int)((n + lb - 1) / lb);
     if (periodic && (n % lb != 0 || P < 2)) return false;
     const int nsep = periodic ? P : P - 1;
@@ -509,7 +523,6 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
     };
     std::vector<Row> rows(npad);
     std::vector<double> spk((size_t)npad * 2 * h, 0.0), scf((size_t)P * h * nb, 0.0);
-    std::vector<double> v(lb);
     for (int p = 0; p < P; ++p) {
         const int64_t r0 = (int64_t)p * lb;
         const int ni = interior(p);
@@ -523,18 +536,17 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
             return bands[(int64_t)k * n + i];
         };
         int64_t bad = -1;
-        if (!factor(lb, local, rows.data() + r0, &bad)) return false;
-        for (int c = 0; c < h; ++c) {
-            // V: the block's own separator rows r0 + ni + c
-            for (int t = 0; t < lb; ++t) v[t] = (has_sep(p) && t < ni) ? entry(r0 + t, r0 + ni + c) : 0.0;
-            solve(lb, rows.data() + r0, v.data());
-            for (int t = 0; t < lb; ++t) spk[(size_t)(r0 + t) * 2 * h + c] = t < ni ? v[t] : 0.0;
-            // W: the previous separator, rows r0 - h + c (wrapped for block 0)
-            const int64_t pc = p == 0 ? n - h + c : r0 - h + c;
-            for (int t = 0; t < lb; ++t) v[t] = (has_prev(p) && t < ni) ? entry(r0 + t, pc) : 0.0;
-            solve(lb, rows.data() + r0, v.data());
-            for (int t = 0; t < lb; ++t) spk[(size_t)(r0 + t) * 2 * h + h + c] = t < ni ? v[t] : 0.0;
-        }
+        if (!M::factor(lb, local, rows.data() + r0, &bad)) return false;
+        double *v = spk.data() + (size_t)r0 * 2 * h;
+        for (int t = 0; t < ni; ++t)
+            for (int c = 0; c < h; ++c) {
+                // V: the block's own separator rows r0 + ni + c
+                if (has_sep(p)) v[t * 2 * h + c] = entry(r0 + t, r0 + ni + c);
+                // W: the previous separator, rows r0 - h + c (wrapped for block 0)
+                if (has_prev(p)) v[t * 2 * h + h + c] = entry(r0 + t, p == 0 ? n - h + c : r0 - h + c);
+            }
+        M::template solve<2 * h>(lb, rows.data() + r0, v);
+        std::fill(v + ni * 2 * h, v + lb * 2 * h, 0.0);
         if (!has_sep(p)) continue;
         // band rows of the separator rows, without the separator columns
         for (int c = 0; c < h; ++c)
@@ -579,15 +591,15 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
         for (int k = 0; k < Nr; ++k) scale[r] = std::max(scale[r], std::fabs(S[(size_t)r * Nr + k]));
     // rows of about the same size, by powers of two: the pivots chosen and every
     // rounding are then the same however the matrix's rows are scaled
-    std::vector<int> two(Nr, 0);
+    std::vector<double> two(Nr, 1.0);
     for (int r = 0; r < Nr; ++r) {
-        if (!std::isfinite(scale[r]) || scale[r] == 0.0) return false;
-        two[r] = std::ilogb(scale[r]);
-        for (int k = 0; k < Nr; ++k) S[(size_t)r * Nr + k] = std::ldexp(S[(size_t)r * Nr + k], -two[r]);
+        if (!(scale[r] > 1e-300 && scale[r] < 1e300)) return false;
+        two[r] = std::ldexp(1.0, -std::ilogb(scale[r]));
+        for (int k = 0; k < Nr; ++k) S[(size_t)r * Nr + k] *= two[r];
     }
     if (Nr > 0 && !invert(S, Nr)) return false;
     for (int r = 0; r < Nr; ++r)
-        for (int k = 0; k < Nr; ++k) S[(size_t)r * Nr + k] = std::ldexp(S[(size_t)r * Nr + k], -two[k]);
+        for (int k = 0; k < Nr; ++k) S[(size_t)r * Nr + k] *= two[k];
     sep_window(S, scale, Nr, hp.kofs, hp.kw);
     hp.lb = lb;
     hp.P = P;
@@ -614,7 +626,7 @@ bool build_sep_plan(int kind, bool periodic, int64_t n, const double *bands, int
         }
     }
     hp.sinv.swap(S);
-    return !gate || passes(*gate, [&](std::vector<double> &x) { sep_plan_solve<Row>(hp, h, periodic, n, solve, x); });
+    return !gate || passes(*gate, [&](Columns &x) { sep_plan_solve<M>(hp, periodic, n, x.data()); });
 }
 
 template <typename Row32, typename Row64>
@@ -786,33 +798,24 @@ std::vector<double> sub_bands(int kind, int64_t n, const double *bands, int64_t 
 // off by A_seg^{-1} (coupling) x_out; every entry of A_seg^{-1} (coupling) on
 // the result's rows has to be at most kSegDrop (2^-60: at most 2 h 2^-60 of
 // the system's largest value in all, 1/32 of an FP64 rounding).
-template <typename Row, typename FactorFn, typename SolveFn>
-bool seg_independent(int kind, int64_t n, const double *bands, const HostSeg &s, const std::vector<double> &sub,
-                     FactorFn factor, SolveFn solve) {
-    const int h = kind / 2;
+template <class M>
+bool seg_independent(int64_t n, const double *bands, const HostSeg &s, const std::vector<double> &sub) {
+    constexpr int h = M::h;
     const int64_t ns = s.hi - s.lo;
-    std::vector<Row> rows(ns);
+    std::vector<typename M::Row> rows(ns);
     int64_t bad = -1;
-    if (!factor(ns, [&](int k, int64_t i) { return sub[(size_t)k * ns + i]; }, rows.data(), &bad)) return false;
-    std::vector<double> v(ns);
-    auto decays = [&] {
-        solve(ns, rows.data(), v.data());
-        for (int64_t i = s.a; i < s.b; ++i)
-            if (!(std::fabs(v[i - s.lo]) <= kSegDrop)) return false;
-        return true;
-    };
+    if (!M::factor(ns, [&](int k, int64_t i) { return sub[(size_t)k * ns + i]; }, rows.data(), &bad)) return false;
+    std::vector<double> v((size_t)ns * 2 * h, 0.0);
     for (int c = 0; c < h; ++c) {
-        if (s.lo > 0) {  // column lo - h + c meets rows lo .. lo + c
-            std::fill(v.begin(), v.end(), 0.0);
-            for (int t = 0; t <= c; ++t) v[t] = bands[(int64_t)(c - t) * n + s.lo + t];
-            if (!decays()) return false;
-        }
-        if (s.hi < n) {  // column hi + c meets rows hi - h + c .. hi - 1
-            std::fill(v.begin(), v.end(), 0.0);
-            for (int t = c; t < h; ++t) v[ns - h + t] = bands[(int64_t)(2 * h + c - t) * n + s.hi - h + t];
-            if (!decays()) return false;
-        }
+        if (s.lo > 0)  // column lo - h + c meets rows lo .. lo + c
+            for (int t = 0; t <= c; ++t) v[t * 2 * h + c] = bands[(int64_t)(c - t) * n + s.lo + t];
+        if (s.hi < n)  // column hi + c meets rows hi - h + c .. hi - 1
+            for (int t = c; t < h; ++t)
+                v[(ns - h + t) * 2 * h + h + c] = bands[(int64_t)(2 * h + c - t) * n + s.hi - h + t];
     }
+    M::template solve<2 * h>(ns, rows.data(), v.data());
+    for (int64_t i = (s.a - s.lo) * 2 * h; i < (s.b - s.lo) * 2 * h; ++i)
+        if (!(std::fabs(v[i]) <= kSegDrop)) return false;
     return true;
 }
 
@@ -852,8 +855,9 @@ SegLayout seg_layout(int64_t n, int64_t cap, int64_t halo) {
 // would go from 869 to 909; pentadiagonal n = 300 1223 -> 1130, n = 1500
 // 1436 -> 1352, n = 600 would go from 1295 to 1402, and nine whole blocks,
 // n = 257, from 1123 to 1261.)
-template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
-std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, FactorFn factor, SolveFn solve) {
+template <class M>
+std::vector<HostSeg> build_segments(int64_t n, const double *bands, const Gate &gate) {
+    constexpr int kind = M::kind;
     const int64_t most = (int64_t)seg_max_blocks(kind) * kSegLb, least = (int64_t)seg_half(kind) * kSegLb;
     // blocks of the whole matrix where one workgroup can hold it
     const int64_t whole = n <= kMaxWhole ? (n + kSegLb - 1) / kSegLb : 0;
@@ -887,21 +891,30 @@ std::vector<HostSeg> build_segments(int kind, int64_t n, const double *bands, Fa
                                 bands[b * n + s.hi - 1 - t] == bands[b * n + o.hi - 1 - t];
                 if (alike && (o.lo > 0) == (s.lo > 0) && (o.hi < n) == (s.hi < n)) s.same = (int)q;
             }
-            if (s.same < 0) ok = seg_independent<Row>(kind, n, bands, s, sub[k], factor, solve);
+            if (s.same < 0) ok = seg_independent<M>(n, bands, s, sub[k]);
         }
         if (!ok) continue;
         for (int64_t k = 0; k < ns; ++k) {
             HostSeg &s = segs[k];
             if (s.same >= 0) continue;
-            const Gate gate = make_gate(kind, false, s.hi - s.lo, sub[k].data());
-            if (!build_sep_plan<Row>(kind, false, s.hi - s.lo, sub[k].data(), kSegLb, factor, solve, &gate, s.hp)) {
+            if (!build_sep_plan<M>(false, s.hi - s.lo, sub[k].data(), kSegLb, nullptr, s.hp)) {
                 ok = false;
                 break;
             }
             std::vector<unsigned char> b64;
-            serialise_sep<Row, Row32>(s.hp, b64, s.b32, s.sp);
-            serialise_refine<Row32>(s.hp, s.b32, s.sp, kind, s.hi - s.lo, sub[k].data(), s.rec, s.sp.refine);
+            serialise_sep<typename M::Row, typename M::Row32>(s.hp, b64, s.b32, s.sp);
+            serialise_refine<typename M::Row32>(s.hp, s.b32, s.sp, kind, s.hi - s.lo, sub[k].data(), s.rec, s.sp.refine);
         }
+        // the whole matrix's right-hand sides and solutions, segment by segment
+        ok = ok && passes(gate, [&](Columns &x) {
+            Columns f;
+            for (const HostSeg &s : segs) {
+                f.assign(gate.d.begin() + s.lo * kChecks, gate.d.begin() + s.hi * kChecks);
+                sep_plan_solve<M>(s.same >= 0 ? segs[s.same].hp : s.hp, false, s.hi - s.lo, f.data());
+                std::copy(f.begin() + (s.a - s.lo) * kChecks, f.begin() + (s.b - s.lo) * kChecks,
+                          x.begin() + s.a * kChecks);
+            }
+        });
         if (!ok) continue;
         return segs;
     }
@@ -946,43 +959,41 @@ struct HostCuts {
 // left.  Rows of a periodic matrix are counted round (n > 2 kCutNear + 1).
 constexpr int64_t kCutNear = 256;
 
-template <typename Row, typename FactorFn, typename SolveFn>
-bool cut_window(int kind, bool periodic, int64_t n, const double *bands, int64_t row, FactorFn factor, SolveFn solve,
-                HostCutWin &win) {
-    const int h = kind / 2;
+template <class M>
+bool cut_window(bool periodic, int64_t n, const double *bands, int64_t row, HostCutWin &win) {
+    constexpr int h = M::h;
     const int64_t lo = periodic ? row - kCutNear : std::max<int64_t>(0, row - kCutNear);
     const int64_t hi = periodic ? row + h + kCutNear : std::min<int64_t>(n, row + h + kCutNear), ns = hi - lo;
-    std::vector<Row> rows(ns);
+    std::vector<typename M::Row> rows(ns);
     int64_t bad = -1;
+    auto wrapped = [&](int64_t r) { return r < 0 ? r + n : r >= n ? r - n : r; };
     // entry (i, i + k - h) of A^T is A's entry (i + k - h, i): band 2h - k of that row
     auto tr = [&](int k, int64_t i) -> double {
         const int64_t j = i + k - h;
-        return j < 0 || j >= ns ? 0.0 : bands[(int64_t)(2 * h - k) * n + (lo + j + n) % n];
+        return j < 0 || j >= ns ? 0.0 : bands[(int64_t)(2 * h - k) * n + wrapped(lo + j)];
     };
-    if (!factor(ns, tr, rows.data(), &bad)) return false;
+    if (!M::factor(ns, tr, rows.data(), &bad)) return false;
     std::vector<double> v((size_t)h * ns, 0.0), scale(ns, 0.0);
     for (int64_t i = 0; i < ns; ++i)
         for (int k = 0; k < 2 * h + 1; ++k) {
             const int64_t r = lo + i, col = r + k - h;
             if (periodic || (col >= 0 && col < n))
-                scale[i] = std::max(scale[i], std::fabs(bands[(int64_t)k * n + (r + n) % n]));
+                scale[i] = std::max(scale[i], std::fabs(bands[(int64_t)k * n + wrapped(r)]));
         }
+    for (int c = 0; c < h; ++c) v[(row + c - lo) * h + c] = 1.0;
+    M::template solve<h>(ns, rows.data(), v.data());
     int64_t reach_lo = 0, reach_hi = 0;
     for (int c = 0; c < h; ++c) {
-        double *w = v.data() + (size_t)c * ns;
-        w[row + c - lo] = 1.0;
-        solve(ns, rows.data(), w);
+        auto size = [&](int64_t i) { return std::fabs(v[i * h + c]); };
         double mx = 0.0, mxs = 0.0;
         for (int64_t i = 0; i < ns; ++i) {
-            mx = std::max(mx, std::fabs(w[i]));
-            mxs = std::max(mxs, std::fabs(w[i]) * scale[i]);
+            mx = std::max(mx, size(i));
+            mxs = std::max(mxs, size(i) * scale[i]);
         }
         if (!std::isfinite(mx) || !std::isfinite(mxs)) return false;
         const double most = std::ldexp(mx, -58), mosts = std::ldexp(std::min(mxs, 1.0), -58);
         double s = 0.0, ss = 0.0;
-        auto drops = [&](int64_t i) {
-            return (s += std::fabs(w[i])) <= most && (ss += std::fabs(w[i]) * scale[i]) <= mosts;
-        };
+        auto drops = [&](int64_t i) { return (s += size(i)) <= most && (ss += size(i) * scale[i]) <= mosts; };
         int64_t i = 0, e = ns - 1;
         while (i < row - lo && drops(i)) ++i;
         s = ss = 0.0;
@@ -994,34 +1005,37 @@ bool cut_window(int kind, bool periodic, int64_t n, const double *bands, int64_t
     win.row = row;
     win.first = row - reach_lo;
     win.len = (int)(reach_lo + h + reach_hi);
-    win.w.resize((size_t)win.len * h);
-    for (int i = 0; i < win.len; ++i)
-        for (int c = 0; c < h; ++c) win.w[(size_t)i * h + c] = v[(size_t)c * ns + (win.first - lo) + i];
+    win.w.assign(v.begin() + (win.first - lo) * h, v.begin() + (win.first - lo + win.len) * h);
     return true;
 }
 
-// The cut form's own solve of one column, as the kernels run it.
-template <typename Row, typename SolveFn>
-void cut_solve(const HostCuts &hc, int kind, int64_t n, const double *bands, SolveFn solve, std::vector<double> &x) {
-    const int h = kind / 2;
+// The cut form's own solve of the gate's columns, as the kernels run it.
+template <class M>
+void cut_solve(const HostCuts &hc, int64_t n, const double *bands, Columns &x) {
+    constexpr int h = M::h, C = kChecks;
     for (size_t k = 0; k < hc.wins.size(); ++k) {
         const HostCutWin &w = hc.wins[k], &src = w.same >= 0 ? hc.wins[w.same] : w;
-        double z[2] = {0.0, 0.0};
-        for (int i = 0; i < src.len; ++i)
-            for (int c = 0; c < h; ++c) z[c] += src.w[(size_t)i * h + c] * x[(w.first + i + n) % n];
-        for (int c = 0; c < h; ++c) x[w.row + c] = z[c];
+        double z[2][C] = {};
+        for (int i = 0; i < src.len; ++i) {
+            const double *f = x.data() + (w.first + i + n) % n * C;
+            for (int c = 0; c < h; ++c)
+                for (int q = 0; q < C; ++q) z[c][q] += src.w[(size_t)i * h + c] * f[q];
+        }
+        for (int c = 0; c < h; ++c) std::copy(z[c], z[c] + C, x.data() + (w.row + c) * C);
     }
     for (const HostCutSeg &s : hc.segs) {
-        std::vector<double> f(x.begin() + s.a, x.begin() + s.b);
+        double *f = x.data() + s.a * C;
         const int64_t ns = s.b - s.a;
         for (int t = 0; t < h; ++t)
-            for (int c = 0; c < h; ++c) {
-                if (s.has_lo && c >= t && t < ns)
-                    f[t] -= bands[(int64_t)(c - t) * n + s.a + t] * x[(s.a - h + c + n) % n];
-                if (s.has_hi && c <= t) f[ns - h + t] -= bands[(int64_t)(2 * h + c - t) * n + s.b - h + t] * x[s.b + c];
-            }
-        sep_plan_solve<Row>(s.same >= 0 ? hc.segs[s.same].hp : s.hp, h, false, ns, solve, f);
-        std::copy(f.begin(), f.end(), x.begin() + s.a);
+            for (int c = 0; c < h; ++c)
+                for (int q = 0; q < C; ++q) {
+                    if (s.has_lo && c >= t && t < ns)
+                        f[t * C + q] -= bands[(int64_t)(c - t) * n + s.a + t] * x[(s.a - h + c + n) % n * C + q];
+                    if (s.has_hi && c <= t)
+                        f[(ns - h + t) * C + q] -=
+                            bands[(int64_t)(2 * h + c - t) * n + s.b - h + t] * x[(s.b + c) * C + q];
+                }
+        sep_plan_solve<M>(s.same >= 0 ? hc.segs[s.same].hp : s.hp, false, ns, f);
     }
 }
 
@@ -1050,10 +1064,9 @@ std::vector<HostCutSeg> lay_cuts(int h, bool periodic, int64_t n, int64_t run) {
 // the last would be longer or (periodic) too short for the windows of the cuts
 // on either side.  False if a window is too wide, a plan is missing, or the
 // result is not the recurrences' within kPlanTolerance.
-template <typename Row, typename Row32, typename FactorFn, typename SolveFn>
-bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorFn factor, SolveFn solve,
-                const Gate &gate, HostCuts &hc) {
-    const int h = kind / 2;
+template <class M>
+bool build_cuts(bool periodic, int64_t n, const double *bands, const Gate &gate, HostCuts &hc) {
+    constexpr int kind = M::kind, h = M::h;
     const int64_t Q = (n + h + kCutRows + h - 1) / (kCutRows + h);
     if (Q < 2 || Q > kMaxCutSegs || (periodic && n < 2 * kCutNear + 2)) return false;
     // the whole blocks nearest to an equal share from below, from above, then less
@@ -1085,7 +1098,7 @@ bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorF
                 w.first = row + (o.first - o.row);
                 w.len = o.len;
             }
-            if (w.same < 0 && !cut_window<Row>(kind, periodic, n, bands, row, factor, solve, w)) return false;
+            if (w.same < 0 && !cut_window<M>(periodic, n, bands, row, w)) return false;
             hc.wins.push_back(std::move(w));
         }
         // a window must not reach another cut: its rows are overwritten
@@ -1106,13 +1119,11 @@ bool build_cuts(int kind, bool periodic, int64_t n, const double *bands, FactorF
         sub.push_back(sub_bands(kind, n, bands, s.a, s.b));
         for (size_t q = 0; q + 1 < sub.size() && s.same < 0; ++q)
             if (hc.segs[q].same < 0 && sub[q] == sub.back()) s.same = (int)q;
-        if (s.same < 0 &&
-            !build_sep_plan<Row>(kind, false, s.b - s.a, sub.back().data(), kSegLb, factor, solve, nullptr, s.hp))
-            return false;
+        if (s.same < 0 && !build_sep_plan<M>(false, s.b - s.a, sub.back().data(), kSegLb, nullptr, s.hp)) return false;
     }
-    if (!passes(gate, [&](std::vector<double> &x) { cut_solve<Row>(hc, kind, n, bands, solve, x); })) return false;
+    if (!passes(gate, [&](Columns &x) { cut_solve<M>(hc, n, bands, x); })) return false;
     for (HostCutSeg &s : hc.segs)
-        if (s.same < 0) serialise_sep<Row, Row32>(s.hp, s.b64, s.b32, s.sp);
+        if (s.same < 0) serialise_sep<typename M::Row, typename M::Row32>(s.hp, s.b64, s.b32, s.sp);
     return true;
 }
 
@@ -1151,18 +1162,13 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     const bool tri = h->kind == SBS_TRI || periodic;
     // (longer matrices have no plan of the whole and no cut form)
     const Gate gate = h->n <= (int64_t)kMaxCutSegs * (kCutRows + 2)
-                          ? make_gate(tri ? SBS_TRI : SBS_PENTA, periodic, h->n, bands)
+                          ? (tri ? make_gate<Tri>(periodic, h->n, bands) : make_gate<Penta>(false, h->n, bands))
                           : Gate();
     for (int q = 0; q < 3; ++q) {
         HostPlan hp;
         const int lb = kPartLbs[q];
-        bool ok;
-        if (tri)
-            ok = build_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, gate,
-                                            hp);
-        else
-            ok = build_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows, gate,
-                                              hp);
+        const bool ok = tri ? build_plan<Tri>(periodic, h->n, bands, lb, gate, hp)
+                            : build_plan<Penta>(false, h->n, bands, lb, gate, hp);
         if (!ok) continue;
         PartPlan &pp = h->part[q];
         pp.periodic = periodic;
@@ -1179,13 +1185,8 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     for (int q = 0; q < 3; ++q) {
         SepHostPlan hp;
         const int lb = kPartLbs[q];
-        bool ok;
-        if (tri)
-            ok = build_sep_plan<TriRow<double>>(SBS_TRI, periodic, h->n, bands, lb, FactorTri{}, solve_tri_rows, &gate,
-                                                hp);
-        else
-            ok = build_sep_plan<PentaRow<double>>(SBS_PENTA, false, h->n, bands, lb, FactorPenta{}, solve_penta_rows,
-                                                  &gate, hp);
+        const bool ok = tri ? build_sep_plan<Tri>(periodic, h->n, bands, lb, &gate, hp)
+                            : build_sep_plan<Penta>(false, h->n, bands, lb, &gate, hp);
         if (!ok) continue;
         SepPlan &sp = h->sep[q];
         sp.periodic = periodic;
@@ -1206,13 +1207,8 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     // Segments for the mixed-precision kernels: overlapping runs of rows, or the
     // 32-row separator plan itself where the whole matrix is one.
     std::vector<HostSeg> segs;
-    if (!periodic && h->n > (int64_t)seg_half(h->kind) * kSegLb) {
-        if (tri)
-            segs = build_segments<TriRow<double>, TriRow<float>>(SBS_TRI, h->n, bands, FactorTri{}, solve_tri_rows);
-        else
-            segs = build_segments<PentaRow<double>, PentaRow<float>>(SBS_PENTA, h->n, bands, FactorPenta{},
-                                                                     solve_penta_rows);
-    }
+    if (!periodic && h->n > (int64_t)seg_half(h->kind) * kSegLb)
+        segs = tri ? build_segments<Tri>(h->n, bands, gate) : build_segments<Penta>(h->n, bands, gate);
     for (const HostSeg &s : segs)
         if (s.same < 0) total += align256(s.b32.size()) + align256(s.rec.size());
     if (!segs.empty() && h->n <= kMaxWhole) {
@@ -1225,10 +1221,8 @@ sbs_status build_partitions(sbs_lhs *h, const double *bands) {
     total += align256(nseg * sizeof(RefSeg));
     HostCuts hc;
     if (h->n > kCutRows) {
-        const bool ok = tri ? build_cuts<TriRow<double>, TriRow<float>>(SBS_TRI, periodic, h->n, bands, FactorTri{},
-                                                                        solve_tri_rows, gate, hc)
-                            : build_cuts<PentaRow<double>, PentaRow<float>>(SBS_PENTA, false, h->n, bands, FactorPenta{},
-                                                                            solve_penta_rows, gate, hc);
+        const bool ok = tri ? build_cuts<Tri>(periodic, h->n, bands, gate, hc)
+                            : build_cuts<Penta>(false, h->n, bands, gate, hc);
         if (!ok) hc = HostCuts();
     }
     for (const HostCutSeg &s : hc.segs) total += align256(s.b64.size()) + align256(s.b32.size());
