@@ -494,6 +494,10 @@ __global__ __launch_bounds__(1024) void k_refine_segs(const RefSeg *__restrict__
     }
 }
 
+// Waits until the wave's vector memory operations, stores and the write-back of
+// a release among them, have completed (s_waitcnt vmcnt(0) alone).
+__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 // Serving: tiles of refined FP32 requests, two corrections, one (request,
 // segment, group of 64 systems) each.  The one-wave tiles they replace run the
 // five passes of a tile one after another through HBM (84 bytes per unknown),
@@ -502,9 +506,11 @@ __global__ __launch_bounds__(1024) void k_refine_segs(const RefSeg *__restrict__
 // A burst of 192 requests (n 64 to 8192, m up to 4096, half of them FP32)
 // went from 7.7 to 2.4 ms.  A workgroup takes the next tile from
 // the counter until the table is exhausted, so every workgroup exits.
-// Completion as in the one-wave tile kernels: once every wave has stored its
-// rows (the barrier), wave 0 releases them at system scope with its decrement
-// of the request's count, and raises the request's flag with the last one.
+// Completion: every wave waits for its own stores (a barrier alone waits for LDS
+// only), the barrier follows, and wave 0 writes the L2 they are in back at system
+// scope, waits for that, takes one from the request's count of tiles and raises
+// the request's flag with the last one.  Both waits are spelled out: a release
+// fence leaves its own out where the wave has no store of its own in flight.
 // Wave 0's branches are taken by the whole wave.
 template <int KIND>
 __global__ __launch_bounds__(1024) void k_refine_tiles(const Tile *__restrict__ tiles, int ntiles, int *counter,
@@ -523,11 +529,14 @@ __global__ __launch_bounds__(1024) void k_refine_tiles(const Tile *__restrict__ 
         const cptr<Tile> tl = (cptr<Tile>)(tiles + t);
         const RefSeg sg = load_seg(static_cast<const RefSeg *>(tl->fac));
         refine_task<KIND>(sg, p, lane, lds, static_cast<const float *>(tl->in), tl->x, tl->m, tl->col0, 2);
+        wait_vmem();
         __syncthreads();
         if (p == 0) {
             const int one = lane == 0 ? 1 : 0;
             const int req = __builtin_amdgcn_readfirstlane(tl->req);
-            int before = __hip_atomic_fetch_add(&left[req], -one, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_SYSTEM);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+            wait_vmem();
+            int before = __hip_atomic_fetch_add(&left[req], -one, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM);
             before = __builtin_amdgcn_readfirstlane(before);
             if (before == 1) __hip_atomic_store(&done[req], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
         }
