@@ -145,15 +145,21 @@ struct Gate {
 template <class M>
 Gate make_gate(bool periodic, int64_t n, const double *bands) {
     constexpr int h = M::h;
-    uint64_t st = 0x9e3779b97f4a7c15ull;  // xorshift64, fixed seed
+    // xorshift64, a fixed seed for each column (side by side, as the solves are)
+    uint64_t st[kChecks];
+    for (int q = 0; q < kChecks; ++q) st[q] = 0x9e3779b97f4a7c15ull * (2 * q + 1);
     Gate g;
     g.from.resize((size_t)n * kChecks);
-    for (int q = 0; q < kChecks; ++q)
-        for (int64_t i = 0; i < n; ++i) {
-            st ^= st << 13;
-            st ^= st >> 7;
-            st ^= st << 17;
-            g.from[i * kChecks + q] = (double)(st >> 11) * 0x1.0p-52 - 1.0;  // U[-1, 1)
+    for (int64_t i = 0; i < n; ++i)
+        for (int q = 0; q < kChecks; ++q) {
+            st[q] ^= st[q] << 13;
+            st[q] ^= st[q] >> 7;
+            st[q] ^= st[q] << 17;
+            // U[-1, 1): the top bits as the mantissa of a number in [2, 4)
+            const uint64_t bits = 0x4000000000000000ull | st[q] >> 12;
+            double u;
+            std::memcpy(&u, &bits, 8);
+            g.from[i * kChecks + q] = u - 3.0;
         }
     g.d = g.from;
     for (int64_t i = 0; i < n; ++i)
@@ -196,20 +202,26 @@ template <typename PlanSolve>
 bool passes(const Gate &g, PlanSolve plan) {
     Columns b = g.d;
     plan(b);
-    double num[kChecks] = {}, den[kChecks] = {}, fnum[kChecks] = {}, fden[kChecks] = {};
-    bool nan = false;
-    for (size_t i = 0; i < b.size(); i += kChecks)
-        for (int q = 0; q < kChecks; ++q) {
-            nan |= std::isnan(b[i + q]);
-            num[q] = std::max(num[q], std::fabs(b[i + q] - g.x[i + q]));
-            den[q] = std::max(den[q], std::fabs(g.x[i + q]));
-            fnum[q] = std::max(fnum[q], std::fabs(b[i + q] - g.from[i + q]));
-            fden[q] = std::max(fden[q], std::fabs(g.from[i + q]));
-        }
-    for (int q = 0; q < kChecks; ++q)
-        if (!(num[q] <= kPlanTolerance * den[q]) && !(q >= kUniformChecks && fnum[q] <= kPlanTolerance * fden[q]))
-            return false;
-    return !nan;
+    // largest entry of `a` and of b - a, column by column (a NaN in b makes sum one)
+    double num[kChecks], den[kChecks], sum[kChecks];
+    auto compare = [&](const Columns &a) {
+        for (int q = 0; q < kChecks; ++q) num[q] = den[q] = sum[q] = 0.0;
+        for (size_t i = 0; i < b.size(); i += kChecks)
+            for (int q = 0; q < kChecks; ++q) {
+                const double e = std::fabs(b[i + q] - a[i + q]), v = std::fabs(a[i + q]);
+                num[q] = e > num[q] ? e : num[q];
+                den[q] = v > den[q] ? v : den[q];
+                sum[q] += b[i + q] * 0.0;
+            }
+    };
+    auto agrees = [&](int q) { return num[q] <= kPlanTolerance * den[q] && sum[q] == 0.0; };
+    compare(g.x);
+    bool all = true, scaled = true;
+    for (int q = 0; q < kChecks; ++q) (q < kUniformChecks ? all : scaled) &= agrees(q);
+    if (!all || scaled) return all;
+    compare(g.from);
+    for (int q = kUniformChecks; q < kChecks; ++q) all &= agrees(q);
+    return all;
 }
 
 // The plan's own solve of the gate's columns, as the kernel runs it: block
