@@ -844,7 +844,7 @@ __device__ __forceinline__ void stage_blob(unsigned char *lds, const unsigned ch
 template <int KIND, typename T, typename Tin, typename Tout, int LB, int MAXT, int CN = 0, bool ROWS = false>
 __global__ __launch_bounds__(MAXT) void k_part(const unsigned char *__restrict__ blob, int fac_bytes, int spk_bytes,
                                                int rinv_bytes, int n, int P, int Nr, int S, int ngroups, int periodic,
-                                               const BandRow *__restrict__ bands, BandCoef coef, int steps,
+                                               int steps, const BandRow *__restrict__ bands, BandCoef coef,
                                                const Tin *in, Tout *out, int64_t m) {
     using R = Rec<KIND, T>;
     using Row = typename R::Row;
@@ -1644,7 +1644,7 @@ hipError_t go_part(const sbs_lhs *h, const PartChoice &c, const void *in, void *
                        static_cast<const unsigned char *>(f64 ? pp.blob64 : pp.blob32),
                        (int)(f64 ? pp.fac_bytes64 : pp.fac_bytes32), (int)(f64 ? pp.spk_bytes64 : pp.spk_bytes32),
                        (int)(f64 ? pp.rinv_bytes64 : pp.rinv_bytes32), (int)h->n, pp.P, pp.Nr, c.S, ngroups,
-                       (int)pp.periodic, h->bands, h->coef, steps, static_cast<const T *>(in), static_cast<T *>(out),
+                       (int)pp.periodic, steps, h->bands, h->coef, static_cast<const T *>(in), static_cast<T *>(out),
                        m);
     return hipGetLastError();
 }
@@ -1668,7 +1668,7 @@ hipError_t go_part_rows(const sbs_lhs *h, const PartChoice &c, double *x, int64_
     const int grid = (int)std::min<int64_t>(ngroups, (int64_t)cus * std::max(1, c.wgs));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(c.threads), c.lds, s, static_cast<const unsigned char *>(pp.blob64),
                        (int)pp.fac_bytes64, (int)pp.spk_bytes64, (int)pp.rinv_bytes64, (int)h->n, pp.P, pp.Nr, c.S,
-                       ngroups, (int)pp.periodic, h->bands, h->coef, 1, x, x, m);
+                       ngroups, (int)pp.periodic, 1, h->bands, h->coef, x, x, m);
     return hipGetLastError();
 }
 

@@ -27,6 +27,7 @@
 // copied into LDS once per persistent workgroup (where the whole plan does
 // not fit, only S^{-1} is, and the rest is read from global memory).
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -110,10 +111,14 @@ struct SepArgs {
     int fac_bytes, spk_bytes, scf_bytes, sinv_bytes, map_bytes;
     int n, P, Nr, S, ngroups, periodic, flags;
     int kofs, kw;  // window of the S^{-1} product (kw = 0: every column)
-    int steps;     // Crank-Nicolson steps to run (1 for a solve)
     int64_t m;
     BandCoef coef;  // Crank-Nicolson steps: the matrix's constant band values
-    const BandRow *bands;  // or its band rows
+};
+// And those of the kernels for several steps, band rows and the cut form only: the
+// arguments a plain solve does not read make its launch longer (see k_sep).
+struct SepMoreArgs : SepArgs {
+    int steps;             // Crank-Nicolson steps to run
+    const BandRow *bands;  // the matrix's band rows
     const CutSeg *segs;  // the cut form: Q segments
     int Q, per, per_last;  // and the workgroups of each, and of the last
     const void *ucut;      // its Crank-Nicolson steps: the unknowns of the cut rows, [cut][H][m]
@@ -394,8 +399,9 @@ __device__ __forceinline__ void block_sweeps(const typename RowOf<KIND, T>::type
 // m may be odd: a lane at or past the last system takes the last two and
 // stores the last one only, since the other may be another workgroup's.
 template <int KIND, typename T, int LB, int VEC, int MAXT, bool GF, int CN = 0, bool SEG = false>
-__global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ blob, SepArgs a, const T *in,
-                                              T *out) {
+__global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ blob,
+                                              std::conditional_t<SEG || CN == 1 || CN == 2, SepMoreArgs, SepArgs> a,
+                                              const T *in, T *out) {
     using Row = typename RowOf<KIND, T>::type;
     constexpr int H = KIND / 2, NB = 2 * H + 1, NI = LB - H;
     constexpr bool MMA = sizeof(T) == 8;
@@ -579,7 +585,9 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             cr[c][d] = (2 * H - c + d < NB) ? cfp[c * NB + 2 * H - c + d] : T(0);
         }
     for (; g < a.ngroups; g += grid) {
-        for (int step = CN && CN != 3 ? a.steps : 1; step > 0; --step) {
+        int step = 1;
+        if constexpr (CN == 1 || CN == 2) step = a.steps;
+        for (; step > 0; --step) {
             // the lane's offsets into the separator buffers, made opaque each
             // group so that the addresses derived from them are formed where they
             // are used instead of being kept live (and spilled) across the loop
@@ -1294,7 +1302,7 @@ hipError_t run_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_
     if (c.threads > maxt || ngroups * cp.Q > 0x7fffffff) return hipErrorInvalidValue;
     const hipError_t e = tc == 0 ? cut_rows<double>(h, x, m, ucut, s) : cut_rows<float>(h, x, m, ucut, s);
     if (e != hipSuccess) return e;
-    SepArgs a{};
+    SepMoreArgs a{};
     a.coef = h->coef;
     a.bands = h->bands;
     a.ucut = ucut;
@@ -1340,7 +1348,7 @@ hipError_t launch_sep(const sbs_lhs *h, const SepChoice &c, int tc, void *x, int
     if (c.threads > maxt) return hipErrorInvalidValue;
     const int64_t ngroups = (m + c.S - 1) / c.S;
     if (ngroups > 0x7fffffff) return hipErrorInvalidValue;
-    SepArgs a;
+    SepMoreArgs a{};
     const bool f64 = tc == 0;
     a.fac_bytes = (int)(f64 ? sp.fac_bytes64 : sp.fac_bytes32);
     a.spk_bytes = (int)(f64 ? sp.spk_bytes64 : sp.spk_bytes32);

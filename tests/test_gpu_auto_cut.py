@@ -1,0 +1,76 @@
+"""Which solves and Crank-Nicolson calls AUTO cuts into segments (sbs_auto_cut),
+and single steps that run that way against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1909_04539_amd import sbs
+from test_cut_host import colrel, constant, dominant
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def matrix(kind, n, which):
+    return dominant(kind, n, n) if which == "random" else constant(kind, n, 2000.0 if which == "slow" else 0.5)
+
+
+# past 2048 rows always, unless the inverse decays too slowly for the windows;
+# one system has no pair; a periodic matrix without whole blocks has no other
+# partitioned form; short matrices are one segment
+@pytest.mark.parametrize("kind,n,which,m,cut", [
+    (3, 2049, "constant", 64, True), (3, 3001, "random", 2, True), (3, 3001, "random", 1, False),
+    (5, 2500, "constant", 513, True), (5, 5143, "random", 64, True), (13, 2600, "random", 33, True),
+    (13, 1027, "constant", 64, True), (3, 5000, "slow", 64, False), (5, 5000, "slow", 64, False),
+    (13, 3001, "slow", 64, False), (3, 256, "random", 4096, False), (5, 600, "constant", 64, False)])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_solves(kind, n, which, m, cut, dtype):
+    x = torch.zeros((n, m), dtype=dtype, device=DEV)
+    with sbs.SharedLhs(kind, matrix(kind, n, which)) as h:
+        got = sbs.sbs_auto_cut(h.handle, x)
+    assert (got is not None) == cut, got
+    if cut:
+        segments, S = got
+        assert 1 < segments <= n // 128 + 1 and S in (8, 16, 32, 64, 128)
+
+
+@pytest.mark.parametrize("kind,n,m", [(3, 2057, 2), (3, 2500, 64), (3, 5001, 333), (5, 2100, 5000), (5, 2500, 130),
+                                      (5, 4099, 77), (13, 600, 50), (13, 1001, 129), (13, 2500, 2)])
+@pytest.mark.parametrize("which", ["constant", "random"])
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 1e-5)])
+def test_one_step(kind, n, m, which, dtype, tol):
+    print(f"case kind={kind} n={n} m={m} {which} {dtype}", flush=True)
+    B = matrix(kind, n, which)
+    c = torch.from_numpy(np.random.default_rng(n * m).uniform(-1, 1, (n, m))).to(dtype)
+    with sbs.SharedLhs(kind, B) as h:
+        x = c.to(DEV)
+        assert sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None
+        h.cn_step(x, 1)
+        torch.cuda.synchronize()
+    cols = np.unique(np.r_[0, m // 2, m - 1, np.random.default_rng(m).integers(0, m, 20)])
+    ref = oracle.cn_steps(kind, B, np.ascontiguousarray(c.double().numpy()[:, cols]), 1)
+    assert colrel(x.double().cpu().numpy()[:, cols], ref) <= tol
+
+
+def test_several_steps_keep_the_systems_whole_where_they_can():
+    # steps of a call are the same arithmetic however a caller groups them
+    x = torch.zeros((4000, 64), dtype=torch.float64, device=DEV)
+    with sbs.SharedLhs(3, constant(3, 4000)) as h:
+        assert sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None
+        assert sbs.sbs_auto_cut(h.handle, x, cn_steps=2) is None
+    with sbs.SharedLhs(3, constant(3, 6000)) as h:  # no whole form fits
+        y = torch.zeros((6000, 64), dtype=torch.float64, device=DEV)
+        assert sbs.sbs_auto_cut(h.handle, y, cn_steps=2) is not None
+
+
+def test_bad_arguments():
+    L = sbs.lib()
+    x = torch.zeros((300, 8), dtype=torch.float64, device=DEV)
+    import ctypes
+    a, b = ctypes.c_int32(), ctypes.c_int32()
+    with sbs.SharedLhs(3, constant(3, 300)) as h:
+        ok = (h.handle, 8, sbs.SBS_F64, x.data_ptr(), 0, ctypes.byref(a), ctypes.byref(b))
+        assert L.sbs_auto_cut(*ok) == 0
+        for k, bad in ((0, None), (1, 0), (2, 7), (4, -1), (5, None), (6, None)):
+            assert L.sbs_auto_cut(*[bad if i == k else v for i, v in enumerate(ok)]) == 1
