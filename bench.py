@@ -57,6 +57,17 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
+def auto_shape(sbs, lhs, rhs):
+    """What AUTO runs for rhs: the cut form's segments, the partitioned shape of
+    whole systems, or None (the sweeps)."""
+    cut = sbs.sbs_auto_cut(lhs.handle, rhs)
+    if cut:
+        return {"form": "cut", "segments": cut[0], "lb": 32, "systems_per_lane": 2, "systems_per_workgroup": cut[1]}
+    shape = sbs.sbs_partition_shape(lhs.handle, rhs)           # (form, lb, vec, S)
+    return shape and {"form": ["pair", "separator"][shape[0]], "lb": shape[1], "systems_per_lane": shape[2],
+                      "systems_per_workgroup": shape[3]}
+
+
 def timed_steps(step, K, W, torch):
     """W untimed steps, then K timed steps bracketed by synchronisation; HIP
     events on the launch stream give the device time of the same region."""
@@ -169,8 +180,9 @@ def bench_headline(args, torch, sbs, W):
     kernel = KERNEL_OF[ran]
     shape = None
     if ran == VARIANTS["partition"]:
-        shape = sbs.sbs_partition_shape(lhs.handle, rhs)       # (form, lb, vec, S)
-        kernel = "k_sep" if shape and shape[0] == 1 else "k_part"
+        shape = auto_shape(sbs, lhs, rhs)
+        # (the cut form's segments run in the separator kernel)
+        kernel = "k_sep" if shape and shape["form"] != "pair" else "k_part"
     step = lambda: lhs.solve(rhs, variant)
     wall, dev = timed_steps(step, args.steps, args.warmup, torch)
     # the kernel alone, two more ways: the median of 20 back-to-back launches
@@ -190,8 +202,7 @@ def bench_headline(args, torch, sbs, W):
     res = {
         "wall_s": wall, "dev_s": dev, "unknowns": unknowns,
         "variant": {v: k for k, v in VARIANTS.items()}[ran], "kernel": kernel,
-        "shape": None if shape is None else {"form": ["pair", "separator"][shape[0]], "lb": shape[1],
-                                             "systems_per_lane": shape[2], "systems_per_workgroup": shape[3]},
+        "shape": shape,
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(kernel),
                      "kernel": kernel, "kernel_us_mean_of_timed_steps": round(dev * 1e6, 2),
@@ -244,14 +255,13 @@ def bench_penta_large(args, torch, sbs, W):
     rhs = torch.rand((n, m), dtype=torch.float64, device="cuda:0", generator=g)
     lhs = sbs.SharedLhs(5, B)
     ran = sbs.sbs_auto_variant(lhs.handle, m)
-    shape = sbs.sbs_partition_shape(lhs.handle, rhs) if ran == VARIANTS["partition"] else None
+    shape = auto_shape(sbs, lhs, rhs) if ran == VARIANTS["partition"] else None
     wall, dev = timed_steps(lambda: lhs.solve(rhs), 10, 2, torch)
     wall, dev_chunked = timed_steps(lambda: lhs.solve(rhs, VARIANTS["chunked"]), 10, 2, torch)
     lhs.close()
     u = n * m
     return {"workload": "penta_f64_n2048_m65536_random_bands", "variant": {v: k for k, v in VARIANTS.items()}[ran],
-            "shape": None if shape is None else {"form": ["pair", "separator"][shape[0]], "block_rows": shape[1],
-                                                 "systems_per_lane": shape[2], "systems_per_workgroup": shape[3]},
+            "shape": shape,
             "unknowns_per_s": u / dev, "us_per_solve": dev * 1e6,
             "hbm_frac_16B": round(16 * u / dev / 1e9 / HBM_PEAK_GBS, 4),
             "chunked_us_per_solve": dev_chunked * 1e6}

@@ -204,10 +204,22 @@ sbs_status sbs_solve_batch_partition(sbs_handle h, void *rhs, int64_t m,
  * them, and the segments of at most 256 rows between them are then solved
  * independently.  What is dropped of those rows moves an unknown by less than
  * 2^-54 of the system's largest, however the matrix's rows are scaled.  This
- * call and sbs_auto_variant report the whole-system form there too. */
+ * call and sbs_auto_variant report the whole-system form there too;
+ * sbs_auto_cut says which of the two runs. */
 sbs_status sbs_partition_shape(sbs_handle h, int64_t m, int32_t dtype,
                                const void *rhs, int32_t *form, int32_t *lb,
                                int32_t *vec, int32_t *S);
+
+/* Whether AUTO cuts the systems (see sbs_partition_shape) for m systems of this
+ * dtype at rhs: *segments receives the number of segments and *S the systems
+ * per workgroup, both 0 where each system is solved whole.  cn_steps 0 asks
+ * about a solve, k >= 1 about one sbs_cn_step call of k steps (outside graph
+ * capture and with memory for the unknowns between the segments).  Host only,
+ * rhs is not read.  Errors: SBS_ERR_INVALID_ARG (NULL handle or output, m < 1,
+ * cn_steps < 0, dtype). */
+sbs_status sbs_auto_cut(sbs_handle h, int64_t m, int32_t dtype,
+                        const void *rhs, int32_t cn_steps, int32_t *segments,
+                        int32_t *S);
 
 /* The variant SBS_VARIANT_AUTO runs for m systems of this dtype: the
  * partitioned variant when a plan exists and fits, otherwise resident

@@ -251,22 +251,58 @@ bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, int steps) {
     return h->n > 2048 || (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27));
 }
 
+// How a Crank-Nicolson call runs: the form, and the kernels' variant (cn: 1 band
+// rows, 2 constant bands by value with no band rows in LDS, 3 see launch_partition).
+struct CnChoice {
+    enum Form { sweeps, separator, pair, cut } form = sweeps;
+    int cn = 1;
+    SepChoice sc;
+    PartChoice pc;
+    CutChoice cc;
+};
+
+CnChoice choose_cn(const sbs_lhs *h, int t, int64_t m, const void *c, int steps, bool cut_ok) {
+    CnChoice k;
+    k.cn = h->constant_bands ? 2 : 1;
+    auto as = [&](CnChoice::Form f) { return k.form = f, k; };
+    if (cut_ok && takes_cut_cn(h, t, m, steps) && choose_cut_cn(h, t, m, k.cn, &k.cc)) return as(CnChoice::cut);
+    if (steps > 1) {
+        if (choose_sep_steps(h, t, m, c, k.cn, &k.sc)) return as(CnChoice::separator);
+        // no separator plan that fits: the pair form's steps, if the bands are
+        // constant (n = 4000, m = 2000, 8 steps: 89 us; cut form 285, sweeps 3499)
+        if (h->constant_bands && choose_partition(h, t, m, &k.pc, 3)) return k.cn = 3, as(CnChoice::pair);
+    }
+    // One step: pentadiagonal, constant bands and a separator shape that fills
+    // every CU with whole row runs: the separator kernel's step (coefficients
+    // by value).  Hyperdiffusion n = 1024, m = 65536: 234.4 us against 246.2 us
+    // in the pair form; for tridiagonal matrices the pair form's step is the
+    // faster (periodic diffusion, same size: 221.6 us against 233.5 us).
+    if (steps == 1 && h->constant_bands && h->kind == SBS_PENTA && choose_sep(h, t, m, c, &k.sc, 3) &&
+        sep_fills(h, t, m, k.sc))
+        return as(CnChoice::separator);
+    if (choose_partition(h, t, m, &k.pc, k.cn)) return as(CnChoice::pair);
+    // no pair plan that fits: the separator form (pentadiagonal n = 1000 with
+    // varying bands, m = 3000: 14 us a step against 128 us), the cut form, or
+    // the sweeps
+    if (choose_sep_steps(h, t, m, c, k.cn, &k.sc)) return as(CnChoice::separator);
+    if (cut_ok && choose_cut_cn(h, t, m, k.cn, &k.cc)) return as(CnChoice::cut);
+    return k;
+}
+
 // Steps in the cut form, with the unknowns of the cut rows in memory from the
 // device's stream-ordered pool for the length of the call.
-// False: the matrix has no cut form, a graph is being captured (no allocation
-// belongs into it), or there is no memory; other forms then run.
-bool cut_cn(const sbs_lhs *h, int t, void *c, int64_t m, int cn, int steps, hipStream_t s, sbs_status *st) {
-    CutChoice cut;
+// False: a graph is being captured (no allocation belongs into it), or there is
+// no memory; other forms then run.
+bool cut_cn(const sbs_lhs *h, int t, void *c, int64_t m, const CnChoice &k, int steps, hipStream_t s, sbs_status *st) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!choose_cut_cn(h, t, m, cn, &cut) || hipStreamIsCapturing(s, &cap) != hipSuccess ||
-        cap != hipStreamCaptureStatusNone)
-        return false;
     void *work = nullptr;
-    if (hipMallocAsync(&work, cut_cn_bytes(h, t, m), s) != hipSuccess) {
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess ||
+        (cap == hipStreamCaptureStatusNone && hipMallocAsync(&work, cut_cn_bytes(h, t, m), s) != hipSuccess)) {
         (void)hipGetLastError();  // not this call's error
         return false;
     }
-    const hipError_t e = launch_cut_cn(h, cut, t, c, m, cn, steps, work, s);
+    if (!work) return false;
+    const hipError_t e = launch_cut_cn(h, k.cc, t, c, m, k.cn, steps, work, s);
     const hipError_t f = hipFreeAsync(work, s);
     *st = e == hipSuccess && f == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     return true;
@@ -573,38 +609,39 @@ sbs_status sbs_cn_step(sbs_handle h, void *c, int64_t m, int32_t dtype, int32_t 
     if (m > (int64_t)0x7fffffff * kWave) return SBS_ERR_INVALID_ARG;
     const int t = dtype == SBS_F64 ? 0 : 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int cn = h->constant_bands ? 2 : 1;  // constant bands: coefficients by value, no band rows in LDS
-    sbs_status st = SBS_OK;
-    if (takes_cut_cn(h, t, m, steps) && cut_cn(h, t, c, m, cn, steps, s, &st)) return st;
-    SepChoice sc;
-    PartChoice pc;
-    if (steps > 1) {
-        if (choose_sep_steps(h, t, m, c, cn, &sc))
-            return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
-        // no separator plan that fits: the pair form's steps, if the bands are
-        // constant (n = 4000, m = 2000, 8 steps: 89 us; cut form 285, sweeps 3499)
-        if (h->constant_bands && choose_partition(h, t, m, &pc, 3))
-            return launch_partition(h, pc, t, t, t, c, c, m, s, 3, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    CnChoice k = choose_cn(h, t, m, c, steps, true);
+    if (k.form == CnChoice::cut) {
+        sbs_status st = SBS_OK;
+        if (cut_cn(h, t, c, m, k, steps, s, &st)) return st;
+        k = choose_cn(h, t, m, c, steps, false);
     }
-    // One step: pentadiagonal, constant bands and a separator shape that fills
-    // every CU with whole row runs: the separator kernel's step (coefficients
-    // by value).  Hyperdiffusion n = 1024, m = 65536: 234.4 us against 246.2 us
-    // in the pair form; for tridiagonal matrices the pair form's step is the
-    // faster (periodic diffusion, same size: 221.6 us against 233.5 us).
-    if (steps == 1 && h->constant_bands && h->kind == SBS_PENTA) {
-        if (choose_sep(h, t, m, c, &sc, 3) && sep_fills(h, t, m, sc))
-            return launch_sep(h, sc, t, c, m, s, 1) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+    hipError_t e = hipSuccess;
+    if (k.form == CnChoice::separator)
+        e = launch_sep(h, k.sc, t, c, m, s, steps);
+    else if (k.form == CnChoice::pair && k.cn == 3)
+        e = launch_partition(h, k.pc, t, t, t, c, c, m, s, 3, steps);
+    else
+        for (int q = 0; q < steps && e == hipSuccess; ++q)
+            e = k.form == CnChoice::pair ? launch_partition(h, k.pc, t, t, t, c, c, m, s, k.cn) : launch_cn(h, t, c, m, s);
+    return e == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
+}
+
+sbs_status sbs_auto_cut(sbs_handle h, int64_t m, int32_t dtype, const void *rhs, int32_t cn_steps, int32_t *segments,
+                        int32_t *S) {
+    if (!h || m < 1 || cn_steps < 0 || (dtype != SBS_F64 && dtype != SBS_F32) || !segments || !S)
+        return SBS_ERR_INVALID_ARG;
+    const int t = dtype == SBS_F64 ? 0 : 1;
+    CutChoice cut;
+    if (cn_steps) {
+        const CnChoice k = choose_cn(h, t, m, rhs, cn_steps, true);
+        if (k.form == CnChoice::cut) cut = k.cc;
+    } else {
+        SepChoice sc;
+        PartChoice pc;
+        pick_partition(h, t, m, rhs, true, &sc, &pc, &cut);
     }
-    const bool pairs = choose_partition(h, t, m, &pc, cn);
-    // no pair plan that fits: the separator form (pentadiagonal n = 1000 with
-    // varying bands, m = 3000: 14 us a step against 128 us), the cut form, or
-    // the sweeps
-    if (!pairs && choose_sep_steps(h, t, m, c, cn, &sc))
-        return launch_sep(h, sc, t, c, m, s, steps) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
-    if (!pairs && cut_cn(h, t, c, m, cn, steps, s, &st)) return st;
-    for (int k = 0; k < steps; ++k)
-        if ((pairs ? launch_partition(h, pc, t, t, t, c, c, m, s, cn) : launch_cn(h, t, c, m, s)) != hipSuccess)
-            return SBS_ERR_DEVICE;
+    *segments = cut.S ? h->cut.Q : 0;
+    *S = cut.S;
     return SBS_OK;
 }
 

@@ -76,6 +76,7 @@ def lib() -> ctypes.CDLL:
         "sbs_auto_variant": ([vp, i64, i32, P(i32)], i32),
         "sbs_solve_batch_partition": ([vp, vp, i64, i32, i32, i32, i32, i32, i32, vp], i32),
         "sbs_partition_shape": ([vp, i64, i32, vp, P(i32), P(i32), P(i32), P(i32)], i32),
+        "sbs_auto_cut": ([vp, i64, i32, vp, i32, P(i32), P(i32)], i32),
         "sbs_solve_batch_refined": ([vp, vp, vp, i64, i32, vp, sz, vp], i32),
         "sbs_refined_workspace_bytes": ([vp, i64], sz),
         "sbs_solve_batch_refined_noalloc": ([vp, vp, vp, i64, i32, vp], i32),
@@ -242,6 +243,16 @@ def sbs_partition_shape(h: int, rhs: torch.Tensor):
         return None
     _check(st, "sbs_partition_shape")
     return tuple(o.value for o in out)
+
+
+def sbs_auto_cut(h: int, rhs: torch.Tensor, cn_steps: int = 0):
+    """(segments, systems per workgroup) where AUTO cuts the systems of rhs, or
+    None where each is solved whole; cn_steps >= 1: for a call of so many
+    Crank-Nicolson steps."""
+    out = [ctypes.c_int32() for _ in range(2)]
+    _check(lib().sbs_auto_cut(h, rhs.shape[1], _dtype_code(rhs), rhs.data_ptr(), cn_steps,
+                              *[ctypes.byref(o) for o in out]), "sbs_auto_cut")
+    return tuple(o.value for o in out) if out[0].value else None
 
 
 def sbs_refined_workspace_bytes(h: int, m: int) -> int:
