@@ -236,19 +236,48 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
     return form;
 }
 
-// Whether a Crank-Nicolson call takes the cut form although other forms fit.
+// Whether a Crank-Nicolson call of one step takes the cut form although other
+// forms fit.
 // It crosses HBM once per step, the others once per call, so only for one step
 // (several are then the same arithmetic however a caller groups them): past
 // 2048 rows, where the pair form (constant bands) has short row runs and few
-// waves (diffusion n = 2500, m = 8192: 85 against 293 us, four steps 321 and
-// 187 us; n = 4000, m = 2000: 39 and 44 us, 145 and 64 us), and with band rows
-// where those fill LDS (tridiagonal n = 2000, m = 10000: 89 against 234 us;
+// waves (diffusion n = 2500, m = 8192: 92 against 122 us, four steps 321 and
+// 187 us; n = 4000, m = 2000: 38 and 44 us, 145 and 64 us), and with band rows
+// where those fill LDS (tridiagonal n = 2000, m = 2000: 31 against 66 us;
 // n = 600, m = 100000: 254 and 327 us; n = 1000, m = 8192: 41 and 42 us,
 // m = 1000: 30 and 20 us; constant bands n = 1000, m = 60000: 236 and 222 us).
-bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, int steps) {
-    if (steps > 1) return false;
+//
+// pc: the pair form's shape, if it has one (null: not).  For tridiagonal
+// matrices that keeps its single launch where the cut form's second one, or its
+// rounds of workgroups, cost more (whole form against cut form):
+//  - constant bands on up to half the CUs (n = 2500: m = 64 19 against 24 us,
+//    m = 500 27 and 29, m = 1000 36 and 31), and up to 2176 rows for the 3000 to
+//    8192 systems that make few rounds of the cut form's 9 segments (periodic
+//    n = 2112: m = 4000 53 and 62, m = 8000 105 and 114; n = 2100: 55 and 57, 107
+//    and 104, m = 2000 48 and 35, m = 16000 223 and 194);
+//  - band rows of at most 1728 rows in FP64 with 16 systems per workgroup while
+//    these are one round, from 1537 rows on two (n = 1030: m = 500 20 against
+//    29 us, m = 4000 28 and 33, m = 16000 96 and 84; n = 1728: m = 4000 37 and
+//    39, m = 8000 65 and 75; n = 1150, m = 8000 65 and 55), with fewer systems up
+//    to 1536 rows and half the CUs (n = 1300: m = 500 27 and 29, m = 1000 35 and
+//    29; n = 1800: m = 64 27 and 23); in FP32 up to 1000 systems (n = 1450:
+//    m = 500 22 and 28, m = 1000 29 and 30, m = 8000 48 and 42; n = 1600:
+//    m = 4000 37 and 31; n = 2000: m = 500 35 and 27);
+//  - large batches of fewer than 384 rows in FP64 (n = 300, m = 100000: 148
+//    against 157 us; n = 400: 186 and 175), and of 769 to 960 rows under 300 MB,
+//    whose workgroups of 32 systems are 800 lanes or more (n = 800: m = 32768
+//    115 against 126 us, m = 50000 183 and 181; n = 900: m = 32768 126 and 131,
+//    m = 50000 206 and 188; n = 700: m = 32768 131 and 104, n = 1000: 179 and 138).
+bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, const sbs::PartChoice *pc) {
     const int64_t bytes = h->n * m * (t == 0 ? 8 : 4);
-    return h->n > 2048 || (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27));
+    if (!(h->n > 2048 || (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27)))) return false;
+    if (!pc || h->kind == SBS_PENTA) return true;
+    if (h->n <= 1024) return t == 1 || (h->n >= 384 && !(h->n > 768 && h->n <= 960 && bytes < 300000000));
+    const int64_t cus = device_cus(h->device), groups = (m + pc->S - 1) / pc->S;
+    if (h->constant_bands) return groups > cus / 2 && !(h->n <= 2176 && m >= 3000 && m <= 8192);
+    if (t == 1) return h->n > 1728 || m > 1000;
+    if (pc->S >= 16) return h->n > 1728 || groups > cus * (h->n > 1536 ? 2 : 1);
+    return h->n > 1536 || groups > cus / 2;
 }
 
 // How a Crank-Nicolson call runs: the form, and the kernels' variant (cn: 1 band
@@ -265,13 +294,15 @@ CnChoice choose_cn(const sbs_lhs *h, int t, int64_t m, const void *c, int steps,
     CnChoice k;
     k.cn = h->constant_bands ? 2 : 1;
     auto as = [&](CnChoice::Form f) { return k.form = f, k; };
-    if (cut_ok && takes_cut_cn(h, t, m, steps) && choose_cut_cn(h, t, m, k.cn, &k.cc)) return as(CnChoice::cut);
     if (steps > 1) {
         if (choose_sep_steps(h, t, m, c, k.cn, &k.sc)) return as(CnChoice::separator);
         // no separator plan that fits: the pair form's steps, if the bands are
         // constant (n = 4000, m = 2000, 8 steps: 89 us; cut form 285, sweeps 3499)
         if (h->constant_bands && choose_partition(h, t, m, &k.pc, 3)) return k.cn = 3, as(CnChoice::pair);
     }
+    const bool pairs = choose_partition(h, t, m, &k.pc, k.cn);
+    if (cut_ok && steps == 1 && takes_cut_cn(h, t, m, pairs ? &k.pc : nullptr) && choose_cut_cn(h, t, m, k.cn, &k.cc))
+        return as(CnChoice::cut);
     // One step: pentadiagonal, constant bands and a separator shape that fills
     // every CU with whole row runs: the separator kernel's step (coefficients
     // by value).  Hyperdiffusion n = 1024, m = 65536: 234.4 us against 246.2 us
@@ -280,7 +311,7 @@ CnChoice choose_cn(const sbs_lhs *h, int t, int64_t m, const void *c, int steps,
     if (steps == 1 && h->constant_bands && h->kind == SBS_PENTA && choose_sep(h, t, m, c, &k.sc, 3) &&
         sep_fills(h, t, m, k.sc))
         return as(CnChoice::separator);
-    if (choose_partition(h, t, m, &k.pc, k.cn)) return as(CnChoice::pair);
+    if (pairs) return as(CnChoice::pair);
     // no pair plan that fits: the separator form (pentadiagonal n = 1000 with
     // varying bands, m = 3000: 14 us a step against 128 us), the cut form, or
     // the sweeps

@@ -35,7 +35,7 @@ def test_solves(kind, n, which, m, cut, dtype):
         assert 1 < segments <= n // 128 + 1 and S in (8, 16, 32, 64, 128)
 
 
-@pytest.mark.parametrize("kind,n,m", [(3, 2057, 2), (3, 2500, 64), (3, 5001, 333), (5, 2100, 5000), (5, 2500, 130),
+@pytest.mark.parametrize("kind,n,m", [(3, 2057, 1501), (3, 2500, 1100), (3, 5001, 333), (5, 2100, 5000), (5, 2500, 130),
                                       (5, 4099, 77), (13, 600, 50), (13, 1001, 129), (13, 2500, 2)])
 @pytest.mark.parametrize("which", ["constant", "random"])
 @pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 1e-5)])
@@ -51,6 +51,20 @@ def test_one_step(kind, n, m, which, dtype, tol):
     cols = np.unique(np.r_[0, m // 2, m - 1, np.random.default_rng(m).integers(0, m, 20)])
     ref = oracle.cn_steps(kind, B, np.ascontiguousarray(c.double().numpy()[:, cols]), 1)
     assert colrel(x.double().cpu().numpy()[:, cols], ref) <= tol
+
+
+# one launch of the pair form where the cut form's two cost more; the large
+# batches beside those it keeps are cut
+@pytest.mark.parametrize("kind,n,which,m,cut", [
+    (3, 2500, "constant", 64, False), (3, 2500, "constant", 512, False), (3, 2500, "constant", 1024, True),
+    (13, 2112, "constant", 4000, False), (13, 4096, "constant", 512, True), (3, 1030, "random", 500, False),
+    (3, 1030, "random", 4096, False), (3, 1030, "random", 16000, True), (3, 1300, "random", 64, False),
+    (3, 1300, "random", 1000, True), (13, 1728, "random", 8000, False), (3, 300, "random", 70000, False),
+    (3, 800, "random", 32768, False), (3, 1000, "random", 20000, True), (5, 1030, "random", 64, True)])
+def test_one_step_keeps_the_pair_form(kind, n, which, m, cut):
+    x = torch.zeros((n, m), dtype=torch.float64, device=DEV)
+    with sbs.SharedLhs(kind, matrix(kind, n, which)) as h:
+        assert (sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None) == cut
 
 
 def test_several_steps_keep_the_systems_whole_where_they_can():
