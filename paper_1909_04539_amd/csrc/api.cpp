@@ -160,42 +160,71 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 //    From 1025 rows on where the separator form's runs are under 128 bytes and
 //    there are systems enough for the cut form's (pentadiagonal n = 1600,
 //    m = 1500: 40 against 26 us, n = 1300 with varying bands 42 and 24 us), or
-//    its last round of workgroups is nearly empty (tridiagonal n = 1800,
-//    m = 4500: 49 against 39 us), and for the pair form, pentadiagonal FP64
+//    its last round of workgroups is nearly empty and the cut form is one round
+//    (m = 4400: pentadiagonal n = 1800, 245 workgroups, 34 against 31 us,
+//    tridiagonal, 280, 31 and 38 us), and for the pair form, pentadiagonal FP64
 //    (n = 1200 with varying bands, m = 1500: 50 against 25 us, m = 64 22 and
-//    16 us) or from 1729 on (tridiagonal FP32 n = 1950, m = 777: 21 against
-//    14 us; n = 1600: 17 and 19 us).
+//    16 us) or from 1729 on while they stay in the cache below (tridiagonal FP32
+//    n = 1950, m = 777: 21 against 14 us; n = 1600: 17 and 19 us).
 //  - Else never for what stays in the 256 MB memory-side cache from one launch to
 //    the next (n = 1000, m = 8192: 24 against 31 us; n = 2000, m = 4096: 30
 //    against 31 us; from 98 MB on, n = 1500, m = 8192: 50 against 46 us).
-//  - From 1025 rows on the whole form has runs under 256 bytes or few workgroups
-//    (n = 1100, m = 50000: 223 against 203, 234 against 210 us; n = 2048,
-//    m = 65536 pentadiagonal: 609 against 506 us); in FP32 from 601 rows on
-//    (tridiagonal n = 768, m = 160000: 322 against 226 us; n = 512: 176 against
-//    187 us).
+//  - From 1025 rows on by where the whole form's 128-byte runs lie.  In rows that
+//    start at multiples of 128 bytes a run is one cache line (m = 20000:
+//    tridiagonal n = 1500 104 against 110 us, n = 2048 138 and 143 us,
+//    pentadiagonal n = 1300 97 and 111, n = 1900 138 and 146 us), in others part
+//    of two (m = 25000: 153 and 141, 205 and 186, 140 and 136, 198 and 184 us);
+//    rows a multiple of 128 KiB apart (64 KiB from 1857 rows on) put a system's
+//    blocks into few memory channels (m = 16384: 109 and 91, 148 and 113, 99 and
+//    90, 147 and 118 us).  So for lines, other rows apart, the whole form; but not
+//    with fewer lanes than 47 blocks of FP64 (37 of FP32) make, tridiagonal
+//    (n = 1100, m = 20000: 97 and 87 us, n = 1300 112 and 103 us; FP32 n = 1100,
+//    m = 40000 87 and 84 us, n = 1300 98 and 103 us), and not for pentadiagonal
+//    band rows (n = 1100, m = 20000: 102 and 94 us) or, in FP32, up to 1984 rows
+//    (band rows 1856; m = 40000: n = 1700 164 and 134 us, n = 1900 187 and 160,
+//    n = 2048 157 and 161; band rows n = 1700 165 and 136, n = 1900 154 and 159).
+//    Up to 1024 rows in FP32 from 601 rows on (tridiagonal n = 768, m = 160000:
+//    322 against 226 us; n = 512: 176 against 187 us).
 //  - Odd batches the whole form reads 8 (4) bytes per lane (n = 700, m = 99999:
 //    338 against 281, 362 against 288 us); from 449 rows on in FP64 tridiagonal
 //    (260 MB: n = 480 129 against 118 us, n = 400 122 against 127), else from
 //    321 (pentadiagonal FP32 n = 343 151 against 142 us, n = 270 159 and 177).
-//  - FP64 up to 1024 rows the whole form reads everything once (n = 768,
-//    m = 60000: 149 against 154 us), but with rows a multiple of 128 KiB apart its
-//    256-byte runs of some 30 blocks meet in few memory channels (n = 1024:
-//    m = 65536 253 against 229 us, m = 49152 179 against 167 us, m = 60000 212
-//    against 221 us; n = 896, m = 65536: 198 against 203 us).
-bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, const sbs::SepChoice &sc) {
+//  - FP64 up to 1024 rows the whole form reads everything once in 256-byte runs
+//    (n = 768, m = 60000: 149 against 154 us).  With rows a multiple of 128 KiB
+//    apart its 32 blocks of 32 rows meet in few memory channels, where the cut
+//    form's four segments are full ones (from 1009 rows on, tridiagonal from 993
+//    on; states in rotation, n = 1024, m = 32768, 49152 and 65536: tridiagonal 121
+//    against 111 us, 177 and 168, 243 and 221, pentadiagonal 118 and 116, 175 and
+//    174, 240 and 227, with band rows 126 and 117, 180 and 175, 258 and 227; past
+//    512 MiB even: m = 81920 297 and 293, 297 and 300; n = 1000: tridiagonal 116
+//    and 115, 172 and 170, 236 and 220, pentadiagonal m = 32768 114 and 120;
+//    n = 961, m = 49152: 165 and 167, 164 and 179; other rows apart: n = 1024,
+//    m = 60000 212 and 221).
+//
+// cc: the cut form's shape for these systems.
+bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, const sbs::SepChoice &sc,
+               const sbs::PartChoice &pc, const sbs::CutChoice &cc) {
     if (form == 0 || (form == 1 && sc.gf) || h->n > 2048) return true;
-    const int64_t elem = t == 0 ? 8 : 4, bytes = h->n * m * elem;
+    const int64_t elem = t == 0 ? 8 : 4, pitch = m * elem, bytes = h->n * pitch;
+    const int64_t cus = device_cus(h->device);
     if (h->n > 1024) {
-        if (form == 2 && (h->n > 1728 || (t == 0 && h->kind == SBS_PENTA))) return true;
-        const int64_t at_once = (int64_t)device_cus(h->device) * std::max(1, sc.wgs);
-        const int64_t groups = form == 1 ? (m + sc.S - 1) / sc.S : 0;
-        if (form == 1 && (sc.S * elem < 128 ? m >= 128 : groups > at_once && groups * 4 <= at_once * 5)) return true;
+        if (form == 2 && (t == 0 && h->kind == SBS_PENTA ? true : h->n > 1728 && bytes < 90000000)) return true;
+        if (form == 1 && sc.S * elem < 128 && m >= 128) return true;
+        const int64_t at_once = cus * std::max(1, sc.wgs), groups = form == 1 ? (m + sc.S - 1) / sc.S : 0;
+        const int64_t cut_wgs = (m + cc.S - 1) / cc.S * h->cut.Q;
+        if (form == 1 && groups > at_once && groups * 4 <= at_once * 5 && (t == 1 || cut_wgs <= cus * cc.wgs)) return true;
     }
     if (bytes < 90000000) return false;
-    if (h->n > 1024) return true;
+    if (h->n > 1024) {
+        const bool lines = (form == 1 ? sc.S : pc.S) * elem >= 128 && pitch % 128 == 0;
+        if (!lines || pitch % (128 * 1024) == 0 || (pitch % (64 * 1024) == 0 && h->n > 1856)) return true;
+        if (h->kind == SBS_PENTA) return t == 0 ? !h->constant_bands : h->n <= (h->constant_bands ? 1984 : 1856);
+        return h->n <= (t == 0 ? 46 * 32 : 36 * 32);
+    }
     if (bytes < int64_t(1) << 27) return false;
     if (m % 2 || !aligned(rhs, 2 * elem)) return h->n > (t == 0 && h->kind != SBS_PENTA ? 448 : 320);
-    return t == 0 ? h->n > 960 && m * elem % (128 * 1024) == 0 : h->n > 600;
+    if (t == 1) return h->n > 600;
+    return h->n > (h->kind == SBS_PENTA ? 1008 : 992) && pitch % (128 * 1024) == 0 && bytes <= int64_t(1) << 29;
 }
 
 // The choice depends on the handle, the dtype, m, whether rhs is aligned for
@@ -228,7 +257,7 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
     }
     const int form = pick_uncached(h, t, m, rhs, for_auto, sc, pc);
     sbs::CutChoice cc;
-    if (for_auto && takes_cut(h, t, m, rhs, form, *sc)) sbs::choose_cut(h, t, m, &cc);
+    if (for_auto && sbs::choose_cut(h, t, m, &cc) && !takes_cut(h, t, m, rhs, form, *sc, *pc, cc)) cc = sbs::CutChoice();
     if (cut) *cut = cc;
     std::lock_guard<std::mutex> g(mu);
     if (known.size() >= 4096) known.clear();  // bounded: many batch sizes only cost a new choice

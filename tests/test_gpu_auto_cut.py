@@ -35,6 +35,21 @@ def test_solves(kind, n, which, m, cut, dtype):
         assert 1 < segments <= n // 128 + 1 and S in (8, 16, 32, 64, 128)
 
 
+# 1025 to 2048 rows by where the rows start: at multiples of 128 bytes (whole
+# lines), between them, or at multiples of 128 KiB; a last round of workgroups
+# that the cut form makes one of, and one it does not; up to 1024 rows
+@pytest.mark.parametrize("kind,n,which,m,cut", [
+    (3, 1500, "constant", 20000, False), (3, 2048, "random", 10000, False), (3, 1500, "constant", 25000, True),
+    (3, 1500, "constant", 16384, True), (3, 1100, "constant", 20000, True), (5, 1300, "constant", 20000, False),
+    (5, 1300, "constant", 25000, True), (5, 1500, "random", 10000, True), (3, 1800, "constant", 4400, False),
+    (5, 1800, "constant", 4400, True), (5, 1024, "constant", 65536, True), (5, 1024, "constant", 60000, False),
+    (5, 1000, "constant", 65536, False), (3, 1000, "constant", 65536, True), (5, 961, "constant", 49152, False)])
+def test_large_batches(kind, n, which, m, cut):
+    x = torch.empty((n, m), dtype=torch.float64, device=DEV)
+    with sbs.SharedLhs(kind, matrix(kind, n, which)) as h:
+        assert (sbs.sbs_auto_cut(h.handle, x) is not None) == cut
+
+
 @pytest.mark.parametrize("kind,n,m", [(3, 2057, 1501), (3, 2500, 1100), (3, 5001, 333), (5, 2100, 5000), (5, 2500, 130),
                                       (5, 4099, 77), (13, 600, 50), (13, 1001, 129), (13, 2500, 2)])
 @pytest.mark.parametrize("which", ["constant", "random"])
