@@ -1312,10 +1312,15 @@ hipError_t run_cut(const sbs_lhs *h, const CutChoice &c, int tc, void *x, int64_
     a.m = m;
     a.segs = cp.segs;
     a.Q = cp.Q;
-    // the GPU's workgroups shared out by the segments' rows (all but the last
-    // have the same number)
-    const int64_t all = (int64_t)cu_count(h->device) * c.wgs, rest = cp.rows * (cp.Q - 1);
-    a.per = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, all * cp.rows / (rest + cp.last)));
+    // the GPU's workgroups shared out by the segments' rows (all but the last have
+    // the same number) and what a group costs however few rows it has, about 48
+    // rows (pentadiagonal n = 3124, m = 3736, a last segment of 28 rows: by the rows
+    // alone four workgroups took its 30 groups in eight rounds, 69 us, now 53;
+    // tridiagonal n = 2336, m = 12000 152 and 109 us; with 24 rows the first stays,
+    // with 80 longer last segments take too many, n = 4660, m = 12000 199 and 206)
+    constexpr int64_t kGroupRows = 48;
+    const int64_t all = (int64_t)cu_count(h->device) * c.wgs, rows = cp.rows + kGroupRows;
+    a.per = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, all * rows / (rows * (cp.Q - 1) + cp.last + kGroupRows)));
     a.per_last = (int)std::max<int64_t>(1, std::min<int64_t>(ngroups, all - (int64_t)a.per * (cp.Q - 1)));
     const unsigned char *blob = nullptr;
     void *args[] = {&blob, &a, &x, &x};

@@ -103,3 +103,18 @@ def test_bad_arguments():
         assert L.sbs_auto_cut(*ok) == 0
         for k, bad in ((0, None), (1, 0), (2, 7), (4, -1), (5, None), (6, None)):
             assert L.sbs_auto_cut(*[bad if i == k else v for i, v in enumerate(ok)]) == 1
+
+
+@pytest.mark.parametrize("kind,n,m", [(5, 3124, 3736), (3, 2336, 6001), (13, 2600, 2000)])
+def test_short_last_segment(kind, n, m):
+    # the last segment (28, 23 and 29 rows) takes more workgroups than its rows alone give it
+    B = constant(kind, n)
+    x = np.random.default_rng(n).uniform(-1, 1, (n, m))
+    t = torch.from_numpy(x).to(DEV)
+    with sbs.SharedLhs(kind, B) as h:
+        assert sbs.sbs_auto_cut(h.handle, t) is not None
+        h.solve(t)
+        torch.cuda.synchronize()
+    cols = np.unique(np.r_[0, 1, 127, 128, m // 2, m - 2, m - 1, np.random.default_rng(m).integers(0, m, 40)])
+    ref = oracle.solve(kind, B, np.ascontiguousarray(x[:, cols]))
+    assert colrel(t.cpu().numpy()[:, cols], ref) <= 1e-13
