@@ -493,17 +493,17 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
 
     const int Ls = S / VEC;  // lanes per block row
     const int l = threadIdx.x, p0 = l / Ls, sl = l - p0 * Ls;
-    // lanes past the last block (the workgroup is whole waves) run it once more:
-    // the same values to the same places.  In the cut form, where a short last
-    // segment may leave whole waves over, they write nothing.
+    // lanes past the last block (the workgroup is whole waves) have no rows and
+    // no separators: they load and store nothing
     const int p = min(p0, P - 1);
-    const bool active = !SEG || p0 < P;
+    const bool active = p0 < P;
+    const int rows = active ? n : 0;
     const int r0 = p * LB;
-    const bool has_sep = a.periodic || p < P - 1, has_prev = a.periodic || p > 0;
+    const bool has_sep = active && (a.periodic || p < P - 1), has_prev = active && (a.periodic || p > 0);
     const int pp = p == 0 ? P - 1 : p - 1;
     const int s0 = sl * VEC;  // the lane's first system within the group
     const int64_t m = a.m;
-    const bool full = r0 + LB <= n;
+    const bool full = r0 + LB <= rows;
     const int grid = SEG ? seg_grid : gridDim.x;
     int b = SEG ? seg_b : blockIdx.x;
     if ((a.flags & 1) && grid % 8 == 0) b = (b % 8) * (grid / 8) + b / 8;
@@ -518,7 +518,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
     // SEG: the unknowns of the cut rows before the lane's block and after it (a
     // single block has both only if the matrix is periodic, so tridiagonal:
     // pentadiagonal lanes need one of the two and keep it in `before`)
-    const bool at_lo = SEG && cut_lo && p == 0, at_hi = SEG && cut_hi && p == P - 1;
+    const bool at_lo = SEG && cut_lo && p0 == 0, at_hi = SEG && cut_hi && p0 == P - 1;
     T before[H][VEC], after[H][VEC];
     auto load_group = [&](int g) {
         const T *src = in + (int64_t)r0 * m + col(g);
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
         } else {
 #pragma unroll
             for (int t = 0; t < LB; ++t) {
-                if (r0 + t < n) {
+                if (r0 + t < rows) {
                     load_vec<T, VEC>(src + (int64_t)t * m, x[t]);
                 } else {
 #pragma unroll
@@ -638,7 +638,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             // this block's last interior rows (redl); one barrier.  (In this order
             // the first rows' values are dropped before the last rows' are used,
             // which keeps the FP64 pentadiagonal kernel within its registers.)
-            if (has_prev && active) {
+            if (has_prev) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
 #pragma unroll
@@ -650,7 +650,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                         lredr[o_prev + v * ldr + c] = yh;
                     }
             }
-            if (has_sep && active) {
+            if (has_sep) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v)
 #pragma unroll
@@ -699,8 +699,8 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             } else {
                 // rows of S^{-1} for the own and the previous separator (a block
                 // without one reads the other's rows and discards the result)
-                const T *rr = lsinv + (size_t)H * (has_sep ? p : pp) * Nr;
-                const T *rl = lsinv + (size_t)H * (has_prev ? pp : p) * Nr;
+                const T *rr = lsinv + (size_t)H * (a.periodic || p < P - 1 ? p : pp) * Nr;
+                const T *rl = lsinv + (size_t)H * (a.periodic || p > 0 ? pp : p) * Nr;
                 T ar[H][VEC], al[H][VEC];
 #pragma unroll
                 for (int c = 0; c < H; ++c)
@@ -774,7 +774,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                             x[t][v] = v2[v];
                             asm volatile("" : "+v"(x[t][v]));
                         }
-                    } else if (active && (full || r0 + t < n)) {
+                    } else if (full || r0 + t < rows) {
                         if (ANYM && one)
                             __builtin_nontemporal_store(v2[VEC - 1], dst + (int64_t)t * m + VEC - 1);
                         else
@@ -846,13 +846,13 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
                         for (int c = 0; c < H; ++c) up[c][v] = c + 1 < H ? up[c + 1][v] : x[t][v];
                     }
                     if constexpr (CN == 3) {
-                        if (full || r0 + t < n) store_vec_nt<T, VEC>(q, v2);
+                        if (full || r0 + t < rows) store_vec_nt<T, VEC>(q, v2);
                         q += m;
                         asm volatile("" : "+v"(q));
                     } else {
                         // rows past the matrix stay 0
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < n ? v2[v] : T(0);
+                        for (int v = 0; v < VEC; ++v) x[t][v] = full || r0 + t < rows ? v2[v] : T(0);
                     }
                     if (t % G == G - 1) pin(v2[0]);
                 }
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             const bool one = last_only(g);
 #pragma unroll
             for (int t = 0; t < LB; ++t) {
-                if (active && (full || r0 + t < n)) {
+                if (full || r0 + t < rows) {
                     if (ANYM && one)
                         __builtin_nontemporal_store(x[t][VEC - 1], q + VEC - 1);
                     else
@@ -876,7 +876,7 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
             }
             if constexpr (SEG) {
                 // the cut after the segment: c' = 2 u - A u = 2 u - c
-                if (at_hi && active) {
+                if (at_hi) {
                     T *qc = out + (int64_t)n * m + col(g);
 #pragma unroll
                     for (int c = 0; c < H; ++c) {
@@ -1078,9 +1078,13 @@ bool sep_fit(const sbs_lhs *h, int tc, int64_t m, const void *x, int q, int vec,
     const void *fn = nullptr;
     int maxt = 0;
     if (sep_fn(h->kind, tc, sp.lb, vec, gf, cn, &fn, &maxt) != hipSuccess) return false;
-    // whole waves, so that the matrix cores can form the separators (pentadiagonal
-    // n = 544, m = 16384, 272 lanes: per-lane dot products took 63 us)
-    const int lanes = (S / vec) * sp.P, threads = (lanes + kWave - 1) / kWave * kWave;
+    // whole waves, so that the matrix cores can form the separators, where these are
+    // at least one row of tiles (pentadiagonal n = 400, m = 42058, 24 separators:
+    // 65 us, with per-lane dot products 71; n = 274, m = 99320, 16: 115 and 121;
+    // n = 160, 8 of them: 27 and 26 us, tridiagonal n = 72, m = 400000, 4: 98 and
+    // 94 us)
+    const int lanes = (S / vec) * sp.P;
+    const int threads = sp.Nr >= 16 ? (lanes + kWave - 1) / kWave * kWave : lanes;
     if (threads > maxt) return false;
     // the separators in redL: one matrix-core tile per wave
     if (alias && (lanes % kWave || ((sp.Nr + 15) / 16) * ((S + 15) / 16) > threads / kWave)) return false;
@@ -1160,7 +1164,7 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
 // blocks 746 us; n = 2000, m = 20000: 16 systems 685 us, 32 (16 waves) 939 us).
 bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn, SepChoice *out) {
     const int64_t unknowns = h->n * m;
-    auto waves = [](const SepChoice &c) { return c.wgs * (c.threads / kWave); };
+    auto waves = [](const SepChoice &c) { return c.wgs * ((c.threads + kWave - 1) / kWave); };
     auto try_shape = [&](int q, int vec, int S, SepChoice *c) { return sep_fit(h, tc, m, x, q, vec, S, 0, c, cn); };
     // the shape of block length q with the most waves per CU, earlier S on a tie
     auto most = [&](int q, int vec, std::initializer_list<int> Ss, SepChoice *best) {
