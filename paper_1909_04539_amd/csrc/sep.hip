@@ -1118,8 +1118,13 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
                 SepChoice c;
                 // two pentadiagonal FP64 systems per lane of 16 rows spill 40
                 // registers: 32-row blocks instead (n = 300, m = 60000: 60 against
-                // 93 us; n = 384, m = 120000: 161 against 166 us)
-                if (tc == 0 && h->kind == SBS_PENTA && vec == 2 && h->sep[q].lb == 16 && h->n > 32) continue;
+                // 93 us; n = 84, m = 90000 26 and 31 us), but not in short systems
+                // or small batches, whose chain of rows the shorter blocks halve
+                // (n = 40, m = 42058: 12.8 against 11.7 us; n = 84, m = 17928 12.3 and
+                // 11.3 us; n = 57, m = 42058 14.1 and 14.2, n = 130 23.7 and 28.7)
+                if (tc == 0 && h->kind == SBS_PENTA && vec == 2 && h->sep[q].lb == 16 && h->n > 56 &&
+                    h->n * m > (int64_t(1) << 21))
+                    continue;
                 if (vec == 2 && (m % 2 || reinterpret_cast<uintptr_t>(x) % (2 * elem))) continue;  // pairs aligned
                 if (!sep_fit(h, tc, m, x, q, vec, S, kSepDefaultFlags, &c, cn)) continue;
                 const int64_t groups = (m + S - 1) / S;
