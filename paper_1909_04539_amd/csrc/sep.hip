@@ -1163,10 +1163,18 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
 // m = 10000: 254 us, the cut form 703, one launch of the sweeps per step 2007
 // us).  Four systems per workgroup, 32-byte row runs, only for batches of up to
 // 4M unknowns or without a cut form (n = 2000 with band rows, m = 10000: 851
-// us, the cut form 660; m = 1000: 100 and 200 us).  FP32: one system per lane,
+// us, the cut form 660; m = 1000: 100 and 200 us).  Short systems have few lanes in
+// a workgroup of 16 systems, so they take more, also of the shortest blocks
+// (3 steps, pentadiagonal: n = 17, m = 500000 128 systems 54 us, 16 774 us, three
+// launches of one step 117 us; n = 56, m = 300000 64 systems 93 us, 16 253 us;
+// n = 200, m = 100001 64 systems 108 us, 16 141 us; tridiagonal n = 24, m = 100000
+// 16-row blocks, 64 systems 19 us, 16 27 us; n = 32, m = 20000 32 systems 10.9 us,
+// 16 12.0; n = 80 16.4 and 17.4 us).  FP32: one system per lane,
 // 32-row blocks up to 8M unknowns, else 64-row ones in the widest workgroup of
 // up to 12 waves (n = 1400, m = 40000: 32 systems 392 us, 16 517 us, 32-row
-// blocks 746 us; n = 2000, m = 20000: 16 systems 685 us, 32 (16 waves) 939 us).
+// blocks 746 us; n = 2000, m = 20000: 16 systems 685 us, 32 (16 waves) 939 us;
+// a system of up to 32 rows is one 32-row block: pentadiagonal n = 22,
+// m = 821696, 2 steps 47 us, as a 64-row one 84 us).
 bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn, SepChoice *out) {
     const int64_t unknowns = h->n * m;
     auto waves = [](const SepChoice &c) { return c.wgs * ((c.threads + kWave - 1) / kWave); };
@@ -1187,7 +1195,7 @@ bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn
     if (tc == 1) {
         if (unknowns > (int64_t(1) << 23)) {
             for (int S : {64, 32, 16})
-                if (try_shape(2, 1, S, &c) && c.threads <= 768) return *out = c, true;
+                if (try_shape(h->n <= 32 ? 1 : 2, 1, S, &c) && c.threads <= 768) return *out = c, true;
         }
         return (most(1, 1, {h->n >= 512 ? 16 : 32, 16, 8}, &c) || most(2, 1, {16, 8}, &c) ||
                 (!cut && most(2, 1, {4}, &c))) &&
@@ -1195,9 +1203,10 @@ bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn
     }
     const bool few = unknowns <= (int64_t(1) << 22);
     if (few) {
-        const int S = h->sep[0].P >= 32 ? 8 : 16;
+        const int P = h->sep[0].P, S = P >= 32 ? 8 : P <= 3 && m >= 65536 ? 64 : P <= 5 && m >= 8192 ? 32 : 16;
         if (try_shape(0, 1, S, &c) || try_shape(0, 1, 8, &c)) return *out = c, true;
     }
+    if (!few && h->sep[1].P <= 7 && try_shape(1, 2, h->sep[1].P == 1 ? 128 : 64, &c)) return *out = c, true;
     return ((m >= 2 && most(1, 2, {16, 32, 64}, &c)) || most(2, 1, {8, 16}, &c) || (m >= 2 && try_shape(1, 2, 8, &c)) ||
             ((few || !cut) && (most(2, 1, {4}, &c) || (m >= 2 && try_shape(1, 2, 4, &c)))) || try_shape(0, 1, 8, &c) ||
             try_shape(1, 1, 8, &c)) &&
