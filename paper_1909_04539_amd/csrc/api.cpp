@@ -261,7 +261,10 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
     if (cut) *cut = cc;
     std::lock_guard<std::mutex> g(mu);
     if (known.size() >= 4096) known.clear();  // bounded: many batch sizes only cost a new choice
-    known[key] = Pick{form, *sc, *pc, cc};
+    try {
+        known[key] = Pick{form, *sc, *pc, cc};
+    } catch (const std::bad_alloc &) {  // chosen again next time
+    }
     return form;
 }
 
@@ -346,6 +349,27 @@ CnChoice choose_cn(const sbs_lhs *h, int t, int64_t m, const void *c, int steps,
     // the sweeps
     if (choose_sep_steps(h, t, m, c, k.cn, &k.sc)) return as(CnChoice::separator);
     if (cut_ok && choose_cut_cn(h, t, m, k.cn, &k.cc)) return as(CnChoice::cut);
+    return k;
+}
+
+// choose_cn, made once for a handle, dtype, m, alignment, one step or several, and
+// kept as pick_partition keeps its choices (weighing the shapes takes 5 us).
+CnChoice pick_cn(const sbs_lhs *h, int t, int64_t m, const void *c, int steps, bool cut_ok) {
+    static std::mutex mu;
+    static std::map<std::tuple<uint64_t, int, int64_t, bool, bool, bool>, CnChoice> known;
+    const auto key = std::make_tuple(h->id, t, m, aligned(c, 2 * (t == 0 ? 8 : 4)), steps > 1, cut_ok);
+    {
+        std::lock_guard<std::mutex> g(mu);
+        auto it = known.find(key);
+        if (it != known.end()) return it->second;
+    }
+    const CnChoice k = choose_cn(h, t, m, c, steps, cut_ok);
+    std::lock_guard<std::mutex> g(mu);
+    if (known.size() >= 4096) known.clear();
+    try {
+        known[key] = k;
+    } catch (const std::bad_alloc &) {  // chosen again next time
+    }
     return k;
 }
 
@@ -669,11 +693,11 @@ sbs_status sbs_cn_step(sbs_handle h, void *c, int64_t m, int32_t dtype, int32_t 
     if (m > (int64_t)0x7fffffff * kWave) return SBS_ERR_INVALID_ARG;
     const int t = dtype == SBS_F64 ? 0 : 1;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    CnChoice k = choose_cn(h, t, m, c, steps, true);
+    CnChoice k = pick_cn(h, t, m, c, steps, true);
     if (k.form == CnChoice::cut) {
         sbs_status st = SBS_OK;
         if (cut_cn(h, t, c, m, k, steps, s, &st)) return st;
-        k = choose_cn(h, t, m, c, steps, false);
+        k = pick_cn(h, t, m, c, steps, false);
     }
     hipError_t e = hipSuccess;
     if (k.form == CnChoice::separator)
@@ -693,7 +717,7 @@ sbs_status sbs_auto_cut(sbs_handle h, int64_t m, int32_t dtype, const void *rhs,
     const int t = dtype == SBS_F64 ? 0 : 1;
     CutChoice cut;
     if (cn_steps) {
-        const CnChoice k = choose_cn(h, t, m, rhs, cn_steps, true);
+        const CnChoice k = pick_cn(h, t, m, rhs, cn_steps, true);
         if (k.form == CnChoice::cut) cut = k.cc;
     } else {
         SepChoice sc;
