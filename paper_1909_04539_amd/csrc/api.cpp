@@ -282,8 +282,9 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
 // pc: the pair form's shape, if it has one (null: not).  For tridiagonal
 // matrices that keeps its single launch where the cut form's second one, or its
 // rounds of workgroups, cost more (whole form against cut form):
-//  - constant bands on up to half the CUs (n = 2500: m = 64 19 against 24 us,
-//    m = 500 27 and 29, m = 1000 36 and 31), and up to 2176 rows for the 3000 to
+//  - constant bands on up to three quarters of the CUs (n = 2500: m = 64 19
+//    against 24 us, m = 500 27 and 29, m = 1000 36 and 31; n = 2221, m = 682 30
+//    and 32), and up to 2176 rows for the 3000 to
 //    8192 systems that make few rounds of the cut form's 9 segments (periodic
 //    n = 2112: m = 4000 53 and 62, m = 8000 105 and 114; n = 2100: 55 and 57, 107
 //    and 104, m = 2000 48 and 35, m = 16000 223 and 194);
@@ -306,7 +307,7 @@ bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, const sbs::PartChoice *pc)
     if (!pc || h->kind == SBS_PENTA) return true;
     if (h->n <= 1024) return t == 1 || (h->n >= 384 && !(h->n > 768 && h->n <= 960 && bytes < 300000000));
     const int64_t cus = device_cus(h->device), groups = (m + pc->S - 1) / pc->S;
-    if (h->constant_bands) return groups > cus / 2 && !(h->n <= 2176 && m >= 3000 && m <= 8192);
+    if (h->constant_bands) return groups > cus * 3 / 4 && !(h->n <= 2176 && m >= 3000 && m <= 8192);
     if (t == 1) return h->n > 1728 || m > 1000;
     if (pc->S >= 16) return h->n > 1728 || groups > cus * (h->n > 1536 ? 2 : 1);
     return h->n > 1536 || groups > cus / 2;
