@@ -452,8 +452,11 @@ sbs_status refined_run(const sbs_lhs *h, const float *b, double *x, int64_t m, i
     // workgroups of it fit on a CU, else on the separator plan, else on longer
     // segments; then the pair form.
     RefwChoice rc;
-    const bool halves = h->nseg > 1 && h->segP <= seg_half(h->kind) &&
-                        (!h->seg_small || m <= (int64_t)64 * device_cus(h->device));
+    // (not where the whole systems are one round of workgroups and the segments
+    // two: n = 436, m = 11589 28 against 34 us)
+    const int64_t groups = (m + kWave - 1) / kWave, cus = device_cus(h->device);
+    const bool halves = h->nseg > 1 && h->segP <= seg_half(h->kind) && (!h->seg_small || m <= 32 * cus) &&
+                        (groups > cus || groups * h->nseg <= 2 * cus);
     if (!halves && choose_refine_wave(h, m, &rc))
         return launch_refine_wave(h, rc, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;
     if (h->nseg > 0) return launch_refine_segs(h, b, x, m, sweeps, s) == hipSuccess ? SBS_OK : SBS_ERR_DEVICE;

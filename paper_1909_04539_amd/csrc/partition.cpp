@@ -859,14 +859,17 @@ SegLayout seg_layout(int64_t n, int64_t cap, int64_t halo) {
 // computes while the other loads and stores, at about 36 us a block and 512K
 // systems (pentadiagonal 49), one workgroup of twice the blocks at 55 (70 to
 // 80): short ones unless their halos make 1.45 (1.4) times the blocks.  Batches
-// that do not fill the GPU (16384 systems) take them up to 1.75 times, since
+// that do not fill the GPU (32 systems a CU) take them up to 1.75 times, since
 // they spread the rows over more CUs (n = 512, m = 1000: tridiagonal 19 -> 11
-// us, pentadiagonal 27 -> 14; m = 64000 115 and 122, 160 and 170).
+// us, pentadiagonal 27 -> 14; n = 480, m = 8000 20 and 18, m = 12876 30 and 34;
+// m = 64000 115 and 122, 160 and 170).
 // (256M unknowns, tridiagonal with 32-row halos n = 512 869 -> 805 us, n = 600
 // 916 -> 827, n = 1500 951 -> 772; with 48-row ones n = 400 927 -> 711, n = 512
 // would go from 869 to 909; pentadiagonal n = 300 1223 -> 1130, n = 1500
 // 1436 -> 1352, n = 600 would go from 1295 to 1402, and nine whole blocks,
-// n = 257, from 1123 to 1261.)
+// n = 257, from 1123 to 1261.  Near 1.4 the two are close: n = 512 with random
+// bands, halos of 32 or 40 rows, 22 blocks in three segments for 16, m = 400000
+// 672 -> 637 us, m = 1M 1700 -> 1660.)
 template <class M>
 std::vector<HostSeg> build_segments(int64_t n, const double *bands, const Gate &gate) {
     constexpr int kind = M::kind;
