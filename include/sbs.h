@@ -146,6 +146,13 @@ sbs_status sbs_factor_uniform(int32_t kind, int64_t n, const double *coeffs,
  *  m      number of systems, m >= 0 (m == 0 queues nothing and returns OK).
  *  dtype  SBS_F64 (FP64 throughout) or SBS_F32 (FP32 storage and FP32
  *         arithmetic with the FP32 rounding of the FP64 factor).
+ * A NaN or infinity in a right-hand side makes its own row's unknown not
+ * finite, and touches no other system.  How far it spreads in its own depends
+ * on the form that runs: the sweeps carry it over the whole system, systems
+ * that are cut (see sbs_partition_shape) over the segments beside it, so rows
+ * some hundred rows away may look sound.  Likewise what a right-hand side adds
+ * to unknowns so far away that it is below 2^-54 of the system's largest may
+ * be left out there instead of rounded.
  * Errors: SBS_ERR_INVALID_ARG (NULL handle/rhs with m > 0, m < 0, dtype),
  *         SBS_ERR_DEVICE.
  */
