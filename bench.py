@@ -241,8 +241,8 @@ def bench_penta_general(args, torch, sbs, W):
 
 def bench_penta_large(args, torch, sbs, W):
     """Pentadiagonal systems of 2048 rows with random diagonally dominant
-    bands (every block of a partition plan distinct): what AUTO runs (the
-    separator form with its plan read from global memory, 16 systems per
+    bands (every block of a partition plan distinct): what AUTO runs (the cut
+    form: the matrix in segments of at most 256 rows, 128 systems per
     workgroup), beside the chunked sweep (24 B per unknown moved, of 16 B
     algorithmic)."""
     n, m = 2048, 65536

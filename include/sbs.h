@@ -309,7 +309,8 @@ size_t sbs_refined_static_scratch_bytes(void);
  * systems of decaying inverse run segment by segment, with the unknowns
  * between the segments (under 1/100 of the array) in memory from the device's
  * stream-ordered pool for the length of the call; while a graph is captured,
- * or without that memory, they run as one sweep per step.
+ * or without that memory, another form runs: for most of them one sweep per
+ * step.
  *  c      device, interleaved (n, m), dtype SBS_F64 or SBS_F32; overwritten.
  *  steps  >= 0 (0 and m == 0 do nothing).
  * Any kind of handle.  Asynchronous on `stream`.
