@@ -291,25 +291,47 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
 //  - band rows of at most 1728 rows in FP64 with 16 systems per workgroup while
 //    these are one round, from 1537 rows on two (n = 1030: m = 500 20 against
 //    29 us, m = 4000 28 and 33, m = 16000 96 and 84; n = 1728: m = 4000 37 and
-//    39, m = 8000 65 and 75; n = 1150, m = 8000 65 and 55), with fewer systems up
-//    to 1536 rows and half the CUs (n = 1300: m = 500 27 and 29, m = 1000 35 and
-//    29; n = 1800: m = 64 27 and 23); in FP32 up to 1000 systems (n = 1450:
-//    m = 500 22 and 28, m = 1000 29 and 30, m = 8000 48 and 42; n = 1600:
-//    m = 4000 37 and 31; n = 2000: m = 500 35 and 27);
+//    39, m = 8000 65 and 75; n = 1150, m = 8000 65 and 55; n = 1514, m = 6000 64 and
+//    55).  A last block that is not full runs row by row; without one, from 1280
+//    rows on, up to three rounds where the cut form makes as many (n = 1472:
+//    m = 5000, one round for two, 51 and 39 us, m = 6000, two, 50 and 55,
+//    m = 10000, two for three, 76 and 65, m = 12000, three, 82 and 85, m = 16000
+//    110 and 100; n = 1216, m = 8000 56 and 54).  With fewer systems up to 1536
+//    rows and half the CUs (n = 1300: m = 500 27 and 29, m = 1000 35 and 29;
+//    n = 1800: m = 64 27 and 23);
+//  - band rows in FP32 up to 1000 systems (n = 1450: m = 500 22 and 28; n = 1600:
+//    m = 4000 37 and 31; n = 1553, m = 1100 32 and 27; n = 2000: m = 500 35 and
+//    27), with whole 64-row blocks up to 5 systems a CU (n = 1600, m = 1100 29 and
+//    31), and from 1150 rows on with 32-row blocks while the workgroups are one
+//    round (n = 1408: m = 1500 24 and 30, m = 3000 25 and 32, m = 4400 34 and 33;
+//    n = 1100, m = 2000 34 and 26), past 6 systems a CU only with a last block
+//    that is whole or up to half full (n = 1411, m = 4096 25 and 28, n = 1406 32
+//    and 28, n = 1207, m = 1100 25 and 30);
 //  - large batches of fewer than 384 rows in FP64 (n = 300, m = 100000: 148
 //    against 157 us; n = 400: 186 and 175), and of 769 to 960 rows under 300 MB,
 //    whose workgroups of 32 systems are 800 lanes or more (n = 800: m = 32768
 //    115 against 126 us, m = 50000 183 and 181; n = 900: m = 32768 126 and 131,
 //    m = 50000 206 and 188; n = 700: m = 32768 131 and 104, n = 1000: 179 and 138).
-bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, const sbs::PartChoice *pc) {
+bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, const sbs::PartChoice *pc, const sbs::CutChoice &cc) {
     const int64_t bytes = h->n * m * (t == 0 ? 8 : 4);
     if (!(h->n > 2048 || (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27)))) return false;
     if (!pc || h->kind == SBS_PENTA) return true;
     if (h->n <= 1024) return t == 1 || (h->n >= 384 && !(h->n > 768 && h->n <= 960 && bytes < 300000000));
     const int64_t cus = device_cus(h->device), groups = (m + pc->S - 1) / pc->S;
     if (h->constant_bands) return groups > cus * 3 / 4 && !(h->n <= 2176 && m >= 3000 && m <= 8192);
-    if (t == 1) return h->n > 1728 || m > 1000;
-    if (pc->S >= 16) return h->n > 1728 || groups > cus * (h->n > 1536 ? 2 : 1);
+    const int lb = h->part[pc->plan].lb;
+    const int64_t ragged = h->n % lb;
+    if (t == 1) {
+        if (h->n > 1728) return true;
+        if (h->n >= 1150 && lb == 32 && (ragged <= 16 || m <= 6 * cus)) return groups > cus;
+        return m > (lb == 64 && !ragged ? std::max<int64_t>(1000, 5 * cus) : 1000);
+    }
+    if (pc->S >= 16 && ragged) return h->n > 1728 || groups > cus * (h->n > 1536 ? 2 : 1);
+    if (pc->S >= 16) {
+        const int64_t slots = cus * cc.wgs, cut_rounds = ((m + cc.S - 1) / cc.S * h->cut.Q + slots - 1) / slots;
+        const int64_t rounds = (groups + cus - 1) / cus;
+        return h->n > 1728 || (rounds > 1 && (h->n < 1280 || rounds > 3 || cut_rounds < rounds));
+    }
     return h->n > 1536 || groups > cus / 2;
 }
 
@@ -334,7 +356,8 @@ CnChoice choose_cn(const sbs_lhs *h, int t, int64_t m, const void *c, int steps,
         if (h->constant_bands && choose_partition(h, t, m, &k.pc, 3)) return k.cn = 3, as(CnChoice::pair);
     }
     const bool pairs = choose_partition(h, t, m, &k.pc, k.cn);
-    if (cut_ok && steps == 1 && takes_cut_cn(h, t, m, pairs ? &k.pc : nullptr) && choose_cut_cn(h, t, m, k.cn, &k.cc))
+    if (cut_ok && steps == 1 && choose_cut_cn(h, t, m, k.cn, &k.cc) &&
+        takes_cut_cn(h, t, m, pairs ? &k.pc : nullptr, k.cc))
         return as(CnChoice::cut);
     // One step: pentadiagonal, constant bands and a separator shape that fills
     // every CU with whole row runs: the separator kernel's step (coefficients

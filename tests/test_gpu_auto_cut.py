@@ -82,6 +82,21 @@ def test_one_step_keeps_the_pair_form(kind, n, which, m, cut):
         assert (sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None) == cut
 
 
+# rounds of workgroups of the two forms: as many (whole blocks keep the pair form,
+# a ragged last one does not), fewer of the cut form's; FP32 while the pair form's are one round
+@pytest.mark.parametrize("n,m,dtype,cut", [
+    (1472, 6000, torch.float64, False), (1472, 5000, torch.float64, True), (1472, 12000, torch.float64, False),
+    (1472, 10000, torch.float64, True), (1472, 20000, torch.float64, True), (1216, 6000, torch.float64, True),
+    (1471, 6000, torch.float64, True), (1599, 8000, torch.float64, False), (1406, 4096, torch.float32, True),
+    (1207, 1100, torch.float32, False), (1553, 1100, torch.float32, True),
+    (1408, 3000, torch.float32, False), (1408, 4096, torch.float32, False), (1408, 4400, torch.float32, True),
+    (1100, 2000, torch.float32, True), (1600, 1100, torch.float32, False), (1600, 3000, torch.float32, True)])
+def test_one_step_by_rounds(n, m, dtype, cut):
+    x = torch.zeros((n, m), dtype=dtype, device=DEV)
+    with sbs.SharedLhs(3, matrix(3, n, "random")) as h:
+        assert (sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None) == cut
+
+
 def test_several_steps_keep_the_systems_whole_where_they_can():
     # steps of a call are the same arithmetic however a caller groups them
     x = torch.zeros((4000, 64), dtype=torch.float64, device=DEV)
