@@ -473,7 +473,10 @@ __global__ __launch_bounds__(MAXT) void k_sep(const unsigned char *__restrict__ 
         lmap = reinterpret_cast<const int *>(lds + sinv_at + a.sinv_bytes);
     }
     const int plan_lds = GF ? a.sinv_bytes : blob_bytes;
-    const int ldr = Nr + 1;  // odd stride: the systems' columns fall in different banks
+    // odd stride: the systems' columns fall in different banks (two Crank-Nicolson
+    // steps of 1024 tridiagonal systems, FP32, n = 2048, 63 separators: at a stride
+    // of 64 78 us, of 63 29 us; n = 1024, 31 separators, 28 and 18 us)
+    const int ldr = Nr | 1;
     T *lredl = reinterpret_cast<T *>(lds + plan_lds);
     T *lredr = reinterpret_cast<T *>(lds + plan_lds + sep_red_bytes<T>(S, Nr));
     // flags bit 5 (GF only, set by the launch when the LDS has no room for a
@@ -1172,7 +1175,7 @@ bool choose_sep(const sbs_lhs *h, int tc, int64_t m, const void *x, SepChoice *o
 // 16 12.0; n = 80 16.4 and 17.4 us).  FP32: one system per lane,
 // 32-row blocks up to 8M unknowns, else 64-row ones in the widest workgroup of
 // up to 12 waves (n = 1400, m = 40000: 32 systems 392 us, 16 517 us, 32-row
-// blocks 746 us; n = 2000, m = 20000: 16 systems 685 us, 32 (16 waves) 939 us;
+// blocks 746 us; n = 2000, m = 16000, 8 steps: 16 systems 192 us;
 // a system of up to 32 rows is one 32-row block: pentadiagonal n = 22,
 // m = 821696, 2 steps 47 us, as a 64-row one 84 us).
 bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn, SepChoice *out) {

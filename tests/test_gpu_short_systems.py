@@ -47,3 +47,12 @@ def test_fp64(kind, n, m, which):
 def test_fp32(kind, n, m):
     run(kind, n, m, "random", torch.float32, 0, 2e-5)
     run(kind, n, m, "random", torch.float32, 3, 2e-5)
+
+
+# longer ones whose separators, one fewer than the blocks (as many, periodic),
+# would lie a multiple of the LDS's banks apart
+@pytest.mark.parametrize("kind,n", [(3, 512), (3, 1024), (3, 1010), (3, 2048), (13, 992), (13, 1024), (5, 1024)])
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-12), (torch.float32, 2e-5)])
+def test_separators_at_odd_strides(kind, n, dtype, tol):
+    run(kind, n, 1501, "random", dtype, 2, tol)
+    run(kind, n, 1501, "constant", dtype, 3, tol)
