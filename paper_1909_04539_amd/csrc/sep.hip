@@ -1081,13 +1081,13 @@ bool sep_fit(const sbs_lhs *h, int tc, int64_t m, const void *x, int q, int vec,
     const void *fn = nullptr;
     int maxt = 0;
     if (sep_fn(h->kind, tc, sp.lb, vec, gf, cn, &fn, &maxt) != hipSuccess) return false;
-    // whole waves, so that the matrix cores can form the separators, where these are
+    // whole waves, so that the matrix cores can form the separators (FP64), where these are
     // at least one row of tiles (pentadiagonal n = 400, m = 42058, 24 separators:
     // 65 us, with per-lane dot products 71; n = 274, m = 99320, 16: 115 and 121;
     // n = 160, 8 of them: 27 and 26 us, tridiagonal n = 72, m = 400000, 4: 98 and
-    // 94 us)
+    // 94 us; FP32 pentadiagonal n = 1536, m = 100 13.4 us, of 48 lanes 12.6)
     const int lanes = (S / vec) * sp.P;
-    const int threads = sp.Nr >= 16 ? (lanes + kWave - 1) / kWave * kWave : lanes;
+    const int threads = tc == 0 && sp.Nr >= 16 ? (lanes + kWave - 1) / kWave * kWave : lanes;
     if (threads > maxt) return false;
     // the separators in redL: one matrix-core tile per wave
     if (alias && (lanes % kWave || ((sp.Nr + 15) / 16) * ((S + 15) / 16) > threads / kWave)) return false;
