@@ -278,6 +278,9 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
 // where those fill LDS (tridiagonal n = 2000, m = 2000: 31 against 66 us;
 // n = 600, m = 100000: 254 and 327 us; n = 1000, m = 8192: 41 and 42 us,
 // m = 1000: 30 and 20 us; constant bands n = 1000, m = 60000: 236 and 222 us).
+// Pentadiagonal matrices have no pair form past 1792 rows, and 8 systems per
+// workgroup in the separator form (constant bands, n = 2000: m = 500 28 against
+// 26 us, m = 4096 47 and 42, m = 32768 452 and 277, the sweeps 345).
 //
 // pc: the pair form's shape, if it has one (null: not).  For tridiagonal
 // matrices that keeps its single launch where the cut form's second one, or its
@@ -314,7 +317,9 @@ int pick_partition(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for
 //    m = 50000 206 and 188; n = 700: m = 32768 131 and 104, n = 1000: 179 and 138).
 bool takes_cut_cn(const sbs_lhs *h, int t, int64_t m, const sbs::PartChoice *pc, const sbs::CutChoice &cc) {
     const int64_t bytes = h->n * m * (t == 0 ? 8 : 4);
-    if (!(h->n > 2048 || (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27)))) return false;
+    if (!(h->n > 2048 || (h->kind == SBS_PENTA && h->n > 1792) ||
+          (!h->constant_bands && (h->n > 1024 || bytes >= int64_t(1) << 27))))
+        return false;
     if (!pc || h->kind == SBS_PENTA) return true;
     if (h->n <= 1024) return t == 1 || (h->n >= 384 && !(h->n > 768 && h->n <= 960 && bytes < 300000000));
     const int64_t cus = device_cus(h->device), groups = (m + pc->S - 1) / pc->S;

@@ -97,6 +97,14 @@ def test_one_step_by_rounds(n, m, dtype, cut):
         assert (sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None) == cut
 
 
+# pentadiagonal constant bands where no pair form fits
+@pytest.mark.parametrize("n,m,cut", [(1750, 4096, False), (1792, 4096, False), (1800, 4096, True), (2048, 20000, True)])
+def test_one_step_of_constant_pentadiagonal_bands(n, m, cut):
+    x = torch.zeros((n, m), dtype=torch.float64, device=DEV)
+    with sbs.SharedLhs(5, constant(5, n)) as h:
+        assert (sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None) == cut
+
+
 def test_several_steps_keep_the_systems_whole_where_they_can():
     # steps of a call are the same arithmetic however a caller groups them
     x = torch.zeros((4000, 64), dtype=torch.float64, device=DEV)
