@@ -159,13 +159,18 @@ int pick_uncached(const sbs_lhs *h, int t, int64_t m, const void *rhs, bool for_
 //    us, pentadiagonal 73 and 23; n = 4096, m = 2048 40 and 33, 96 and 36 us).
 //    From 1025 rows on where the separator form's runs are under 128 bytes and
 //    there are systems enough for the cut form's (pentadiagonal n = 1600,
-//    m = 1500: 40 against 26 us, n = 1300 with varying bands 42 and 24 us), or
+//    m = 1500: 40 against 26 us, n = 1300 with varying bands 42 and 24 us; FP32,
+//    constant bands, n = 1536: m = 128 13 and 16 us, m = 500 37 and 19), or
 //    its last round of workgroups is nearly empty and the cut form is one round
 //    (m = 4400: pentadiagonal n = 1800, 245 workgroups, 34 against 31 us,
 //    tridiagonal, 280, 31 and 38 us), and for the pair form, pentadiagonal FP64
 //    (n = 1200 with varying bands, m = 1500: 50 against 25 us, m = 64 22 and
-//    16 us) or from 1729 on while they stay in the cache below (tridiagonal FP32
-//    n = 1950, m = 777: 21 against 14 us; n = 1600: 17 and 19 us).
+//    16 us) or while they stay in the cache below from 1729 on, in FP32 from eight
+//    segments on and unless the pair form's workgroups are nearly a whole round, or
+//    part of one with rows at whole cache lines (tridiagonal FP32 n = 1950, m = 777:
+//    21 against 14 us, m = 6000 26 and 26, m = 8000 29 and 32; n = 1920, m = 4096 18
+//    and 20, m = 5000 31 and 25; n = 1600, m = 777 17 and 19, n = 1792 periodic,
+//    m = 1000 18 and 21).
 //  - Else never for what stays in the 256 MB memory-side cache from one launch to
 //    the next (n = 1000, m = 8192: 24 against 31 us; n = 2000, m = 4096: 30
 //    against 31 us; from 98 MB on, n = 1500, m = 8192: 50 against 46 us).
@@ -208,8 +213,12 @@ bool takes_cut(const sbs_lhs *h, int t, int64_t m, const void *rhs, int form, co
     const int64_t elem = t == 0 ? 8 : 4, pitch = m * elem, bytes = h->n * pitch;
     const int64_t cus = device_cus(h->device);
     if (h->n > 1024) {
-        if (form == 2 && (t == 0 && h->kind == SBS_PENTA ? true : h->n > 1728 && bytes < 90000000)) return true;
-        if (form == 1 && sc.S * elem < 128 && m >= 128) return true;
+        if (form == 2 && t == 0 && (h->kind == SBS_PENTA || (h->n > 1728 && bytes < 90000000))) return true;
+        if (form == 2 && t == 1 && h->n > 1798 && bytes < 90000000) {
+            const bool one_round = (m + pc.S - 1) / pc.S <= cus;
+            if (!(one_round && (m > 24 * cus || (m >= 8 * cus && pitch % 128 == 0)))) return true;
+        }
+        if (form == 1 && sc.S * elem < 128 && m >= (t == 1 && h->constant_bands ? 256 : 128)) return true;
         const int64_t at_once = cus * std::max(1, sc.wgs), groups = form == 1 ? (m + sc.S - 1) / sc.S : 0;
         const int64_t cut_wgs = (m + cc.S - 1) / cc.S * h->cut.Q;
         if (form == 1 && groups > at_once && groups * 4 <= at_once * 5 && (t == 1 || cut_wgs <= cus * cc.wgs)) return true;

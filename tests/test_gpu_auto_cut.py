@@ -105,6 +105,16 @@ def test_one_step_of_constant_pentadiagonal_bands(n, m, cut):
         assert (sbs.sbs_auto_cut(h.handle, x, cn_steps=1) is not None) == cut
 
 
+# FP32 solves: a whole round of the pair form's workgroups, and seven segments
+@pytest.mark.parametrize("kind,n,m,cut", [(3, 1950, 777, True), (3, 1950, 6000, True), (3, 1950, 8192, False),
+                                          (13, 1920, 4096, False), (3, 1920, 5000, True),
+                                          (3, 1950, 8300, True), (13, 1792, 1000, False), (3, 1800, 1000, True), (5, 1536, 500, True)])
+def test_fp32_beside_the_pair_form(kind, n, m, cut):
+    x = torch.zeros((n, m), dtype=torch.float32, device=DEV)
+    with sbs.SharedLhs(kind, matrix(kind, n, "random")) as h:
+        assert (sbs.sbs_auto_cut(h.handle, x) is not None) == cut
+
+
 def test_several_steps_keep_the_systems_whole_where_they_can():
     # steps of a call are the same arithmetic however a caller groups them
     x = torch.zeros((4000, 64), dtype=torch.float64, device=DEV)
