@@ -1210,6 +1210,7 @@ bool choose_sep_steps(const sbs_lhs *h, int tc, int64_t m, const void *x, int cn
         if (try_shape(0, 1, S, &c) || try_shape(0, 1, 8, &c)) return *out = c, true;
     }
     if (!few && h->sep[1].P <= 7 && try_shape(1, 2, h->sep[1].P == 1 ? 128 : 64, &c)) return *out = c, true;
+    if (!few && !h->sep[1].ok && h->sep[0].P <= 7 && try_shape(0, 1, 64, &c)) return *out = c, true;
     return ((m >= 2 && most(1, 2, {16, 32, 64}, &c)) || most(2, 1, {8, 16}, &c) || (m >= 2 && try_shape(1, 2, 8, &c)) ||
             ((few || !cut) && (most(2, 1, {4}, &c) || (m >= 2 && try_shape(1, 2, 4, &c)))) || try_shape(0, 1, 8, &c) ||
             try_shape(1, 1, 8, &c)) &&
